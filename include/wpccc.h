@@ -152,9 +152,10 @@ typedef struct {
                        (A_k / r_k^(lam+1), B_(k+1) r_(k+1)^lam), read at half the
                        bytes and combined with the R factors in FP64 (one
                        rounding per stored integral).  LU, solves, the angular
-                       sums and RK4 stay FP64.  A 1C mixed plan runs one launch
-                       per stage (WPCCC_ENOTSUP with WPCCC_LAUNCH_PERSISTENT)
-                       and has no adjoint. */
+                       sums and RK4 stay FP64.  A 1C mixed plan takes no
+                       WPCCC_LAUNCH_PERSISTENT (WPCCC_ENOTSUP) and has no
+                       adjoint; with WPCCC_LAUNCH_AUTO its chunks run in
+                       either form, as timed. */
     int graph;      /* 1C, batched: replay each 64-step chunk of wpccc_propagate
                        from a captured HIP graph (step lengths and positions
                        read from device memory); 2C: replay the steps of
@@ -174,9 +175,11 @@ typedef struct {
                        forms below, timed at plan creation;
                        WPCCC_LAUNCH_STAGES: one launch per stage;
                        WPCCC_LAUNCH_PERSISTENT: one cooperative launch per
-                       chunk whose workgroups stay resident and meet at a
-                       per-path barrier between stages (WPCCC_ENOTSUP at plan
-                       creation when its grid cannot be resident at once).
+                       chunk whose workgroups stay resident and exchange the
+                       stages' inputs in tagged words (WPCCC_ENOTSUP at plan
+                       creation when the row tiles of all paths could not be
+                       resident at once; a basis that no split fits runs
+                       kernel by kernel).
                        Both forms give bitwise the same amplitudes. */
     int radial;     /* 1C: how the radial integrals F of Eq. D2 are evaluated at R:
                        WPCCC_RADIAL_EXACT (default): the r-grid quadrature at the
@@ -185,9 +188,10 @@ typedef struct {
                        F tabulated on the r-grid nodes and interpolated at R by
                        the five-point Lagrange polynomial in r on the stencil of
                        the node nearest in sqrt(r / r_max), the multipole form
-                       F(r_max) (r_max / R)^(lam+1) beyond the grid.  FP64, one
-                       launch per stage (WPCCC_ENOTSUP with WPCCC_MIXED or
-                       WPCCC_LAUNCH_PERSISTENT), no adjoint. */
+                       F(r_max) (r_max / R)^(lam+1) beyond the grid.  FP64
+                       (WPCCC_ENOTSUP with WPCCC_MIXED or
+                       WPCCC_LAUNCH_PERSISTENT; with WPCCC_LAUNCH_AUTO its
+                       chunks run in either form, as timed), no adjoint. */
     int stage_cache; /* 1C: WPCCC_CACHE_AUTO (default: timed at plan creation
                        where both forms apply), WPCCC_CACHE_ON or WPCCC_CACHE_OFF
                        (see wpccc_plan_stage_cache; WPCCC_ENOTSUP where the
@@ -284,13 +288,14 @@ int wpccc_plan_stage_cache(wpccc_plan_t plan, int* cached);
 
 /* Launch form a one-centre plan's wpccc_propagate uses for its RK4 stages
  * (WPCCC_LAUNCH_STAGES or WPCCC_LAUNCH_PERSISTENT, as requested or as chosen
- * by timing at plan creation); WPCCC_LAUNCH_STAGES for a two-centre plan. */
+ * by timing at plan creation); WPCCC_LAUNCH_STAGES for a two-centre plan and
+ * for the WPCCC_MIXED and WPCCC_RADIAL_INTERP forms. */
 int wpccc_plan_stage_launch(wpccc_plan_t plan, int* launch);
 
 /* Returns the first device-side error latched since the last call (after
  * synchronising `stream`), then clears it: WPCCC_OK, WPCCC_ENUMERIC, (2C)
  * WPCCC_ESINGULAR with the path and pivot row in the message, or WPCCC_EHIP
- * when a barrier of the persistent stage kernel gave up waiting. */
+ * when a workgroup of the persistent stage kernel gave up waiting. */
 int wpccc_plan_status(wpccc_plan_t plan, void* stream);
 
 /* Couplings of path j at one z, with the interaction-picture phases

@@ -23,6 +23,7 @@
 // in a different association order.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -32,8 +33,19 @@ namespace wpccc {
 
 namespace {
 
+// The arithmetic that the stage kernels (one launch per stage) and the
+// persistent chunk kernel share is written with explicit fused operations, so
+// that both round alike whatever the compiler contracts around them.
 __device__ inline double2 cmul(double2 a, double2 b) {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return make_double2(__builtin_fma(a.x, b.x, -(a.y * b.y)), __builtin_fma(a.x, b.y, a.y * b.x));
+}
+// conj(ph) u
+__device__ inline double2 dephase(double2 ph, double2 u) {
+    return make_double2(__builtin_fma(ph.x, u.x, ph.y * u.y), __builtin_fma(ph.x, u.y, -(ph.y * u.x)));
+}
+// F at R from a table entry and the two R factors of its multipole
+__device__ inline double radial_f(double a, double b, double fa, double fb) {
+    return __builtin_fma(a, fa, b * fb);
 }
 
 // Partial moments, one thread per Frow entry d = (a, b, lambda); phiT is [n_r+1][n_f].
@@ -227,7 +239,7 @@ __device__ inline double interp_value(const double* ftab, int n_frow, int n_r, i
                                       int lam) {
     if (kidx < 0) return ftab[(size_t)n_r * n_frow + d] * rp[lam];
     double f = 0.0;
-    for (int i = 0; i < 5; ++i) f += rp[i] * ftab[(size_t)(kidx + i) * n_frow + d];
+    for (int i = 0; i < 5; ++i) f = __builtin_fma(rp[i], ftab[(size_t)(kidx + i) * n_frow + d], f);
     return f;
 }
 
@@ -243,6 +255,7 @@ __global__ __launch_bounds__(64) void k_prologue(PrologueArgs a) {
     const Meta& m = *a.meta;
     const int j = a.traj0 + blockIdx.y;
     const int p = blockIdx.x;
+    if (p == 0 && blockIdx.y == 0 && threadIdx.x == 0) *a.epoch += kChunkEpoch;
     const double z = a.zdev ? a.zdev[(size_t)(*a.chunk) * kChunkPoints + p] : a.z[p];
     const double b = a.tb.bvec[j], v = a.tb.vvec[j];
     const double R = sqrt(b * b + z * z);
@@ -293,24 +306,24 @@ constexpr int kGBatch = 4;   // angular coefficients per thread held in register
 
 // RK4 combinations (Algorithm 1) of stage `stage` with slope K and step h:
 // the next stage input (stages 1-3) and the new accumulator (stages 1-3) or
-// the new amplitude (stage 4).
+// the new amplitude (stage 4); w = rk4_weight(stage, h).
+__device__ inline double rk4_weight(int stage, double h) { return (stage == 1 || stage == 4) ? h / 6.0 : h / 3.0; }
 __device__ inline double2 rk4_next_input(int stage, double2 x0, double2 K, double h) {
     const double c = (stage == 3) ? h : 0.5 * h;
-    return make_double2(x0.x + c * K.x, x0.y + c * K.y);
+    return make_double2(__builtin_fma(c, K.x, x0.x), __builtin_fma(c, K.y, x0.y));
 }
-__device__ inline double2 rk4_accumulate(int stage, double2 x0, double2 xa, double2 K, double h) {
-    if (stage == 1) return make_double2(x0.x + h / 6.0 * K.x, x0.y + h / 6.0 * K.y);
-    if (stage == 4) return make_double2(xa.x + h / 6.0 * K.x, xa.y + h / 6.0 * K.y);
-    return make_double2(xa.x + h / 3.0 * K.x, xa.y + h / 3.0 * K.y);
+__device__ inline double2 rk4_accumulate(int stage, double2 x0, double2 xa, double2 K, double w) {
+    const double2 x = stage == 1 ? x0 : xa;
+    return make_double2(__builtin_fma(w, K.x, x.x), __builtin_fma(w, K.y, x.y));
 }
 
 // The RK4 combination of stage a.stage for output oi with slope K and step h.
 __device__ inline void rk4_update(const StageArgs& a, size_t oi, double2 K, double2 x0, double2 xa, double h) {
     if (a.stage < 4) {
         a.u_out[oi] = rk4_next_input(a.stage, x0, K, h);
-        a.Xacc[oi] = rk4_accumulate(a.stage, x0, xa, K, h);
+        a.Xacc[oi] = rk4_accumulate(a.stage, x0, xa, K, rk4_weight(a.stage, h));
     } else {
-        const double2 xn = rk4_accumulate(4, x0, xa, K, h);
+        const double2 xn = rk4_accumulate(4, x0, xa, K, rk4_weight(4, h));
         if (!isfinite(xn.x) || !isfinite(xn.y)) atomicOr(a.flag, 1);
         (a.Xout ? a.Xout : a.X)[oi] = xn;
     }
@@ -346,8 +359,8 @@ __device__ inline void stage_phase2(const double* Fs, const double2* xs, const i
                 // rows r0 + k >= nrows read rows of F that this stage did not
                 // fill (inside the ROWS-row buffer); their sums are dropped
                 const double fk = f[k * nV + n];
-                re[k] += fk * y.x;
-                im[k] += fk * y.y;
+                re[k] = __builtin_fma(fk, y.x, re[k]);
+                im[k] = __builtin_fma(fk, y.y, im[k]);
             }
         }
 #pragma unroll
@@ -356,38 +369,91 @@ __device__ inline void stage_phase2(const double* Fs, const double2* xs, const i
     }
 }
 
-// phase 3 of a stage: y[r][q'] = sum_g G_l'[q'][g] W[r][g] for output o =
-// (r, q') (o < n_out), summed by the S lanes s = 0..S-1 of the output; every
-// lane of the wave takes part in the reduction and returns the output's sum.
-__device__ inline double2 stage_phase3(const double* Gs, const double2* Ws, int o, int s, int S, int n_out, int nmp,
-                                       int gcols) {
-    double re = 0.0, im = 0.0;
-    if (o < n_out) {
-        const int r = o / nmp, qp = o - r * nmp;
-        const double* g = Gs + qp * gcols;
-        const double2* w = Ws + r * gcols;
-        double re1 = 0.0, im1 = 0.0;
-        int c = s;
-        for (; c + S < gcols; c += 2 * S) {
-            const double g0 = g[c], g1 = g[c + S];
-            const double2 w0 = w[c], w1 = w[c + S];
-            re += g0 * w0.x;
-            im += g0 * w0.y;
-            re1 += g1 * w1.x;
-            im1 += g1 * w1.y;
-        }
-        if (c < gcols) {
-            re += g[c] * w[c].x;
-            im += g[c] * w[c].y;
-        }
-        re += re1;
-        im += im1;
+// Value of another lane of the wave's 16-lane rows (DPP, no LDS traffic).
+template <int CTRL>
+__device__ inline double dpp_move(double x) {
+    const int lo = __double2loint(x), hi = __double2hiint(x);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, hi, CTRL, 0xf, 0xf, true),
+                            __builtin_amdgcn_update_dpp(0, lo, CTRL, 0xf, 0xf, true));
+}
+
+// Sum over the S lanes (a power of two, S-aligned) of an output, every lane
+// returning it.  Neighbours first: after the pairs and the quads hold equal
+// values, mirroring half a row (row) brings the other quad's (half's) sum.
+__device__ inline void lane_sum(double& re, double& im, int S) {
+    if (S >= 2) {
+        re += dpp_move<0xB1>(re);    // quad_perm [1, 0, 3, 2]
+        im += dpp_move<0xB1>(im);
     }
-    for (int off = S >> 1; off > 0; off >>= 1) {
+    if (S >= 4) {
+        re += dpp_move<0x4E>(re);    // quad_perm [2, 3, 0, 1]
+        im += dpp_move<0x4E>(im);
+    }
+    if (S >= 8) {
+        re += dpp_move<0x141>(re);   // row_half_mirror
+        im += dpp_move<0x141>(im);
+    }
+    if (S >= 16) {
+        re += dpp_move<0x140>(re);   // row_mirror
+        im += dpp_move<0x140>(im);
+    }
+    for (int off = 16; off < S; off <<= 1) {
         re += __shfl_xor(re, off, 64);
         im += __shfl_xor(im, off, 64);
     }
-    return make_double2(re, im);
+}
+
+// An output's sum over the columns g is taken in kChains chains, g = c, c + 8,
+// c + 16, ... for chain c, each in ascending order, whose sums are then added
+// in pairs (0 + 1, 2 + 3, ...), the pairs in pairs and so on.  Every kernel
+// that forms y = G W follows this order, so the split of the rows over
+// workgroups and of the columns over lanes changes no bit of the result.
+constexpr int kChains = 8;
+
+// The sum for one output by S lanes, lane s taking chains s, s + S, ...; every
+// lane of the wave takes part and returns the output's sum.
+template <int S>
+__device__ inline double2 phase3_sum(const double* g, const double2* w, int s, int gcols, bool valid) {
+    constexpr int U = kChains / S;
+    double re[U], im[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) re[u] = im[u] = 0.0;
+    if (valid)
+        for (int c0 = s; c0 < gcols; c0 += kChains)
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (c0 + u * S < gcols) {
+                    const double gv = g[c0 + u * S];
+                    const double2 wv = w[c0 + u * S];
+                    re[u] = __builtin_fma(gv, wv.x, re[u]);
+                    im[u] = __builtin_fma(gv, wv.y, im[u]);
+                }
+#pragma unroll
+    for (int u = 0; u < U; ++u) lane_sum(re[u], im[u], S);
+#pragma unroll
+    for (int d = 1; d < U; d *= 2)
+#pragma unroll
+        for (int u = 0; u + d < U; u += 2 * d) {
+            re[u] += re[u + d];
+            im[u] += im[u + d];
+        }
+    return make_double2(re[0], im[0]);
+}
+
+// phase 3 of a stage: y[r][q'] = sum_g G_l'[q'][g] W[r][g] for output o =
+// (r, q') (o < n_out) by the S lanes s = 0..S-1 of the output.
+__device__ inline double2 stage_phase3(const double* Gs, const double2* Ws, int o, int s, int S, int n_out, int nmp,
+                                       int gcols) {
+    const bool valid = o < n_out;
+    const int r = valid ? o / nmp : 0, qp = valid ? o - r * nmp : 0;
+    const double* g = Gs + qp * gcols;
+    const double2* w = Ws + r * gcols;
+    switch (S) {
+        case 8: return phase3_sum<8>(g, w, s, gcols, valid);
+        case 4: return phase3_sum<4>(g, w, s, gcols, valid);
+        case 2: return phase3_sum<2>(g, w, s, gcols, valid);
+        default: return phase3_sum<1>(g, w, s, gcols, valid);
+    }
 }
 
 // phase 3 of the large-basis form: as stage_phase3, with the angular factor
@@ -417,13 +483,13 @@ __device__ inline double2 stage_phase3_global(const double* gc, const int* gp, c
     return make_double2(re, im);
 }
 
-// Lanes per output of phase 3: the largest power of two S <= 64 with
+// Lanes per output of phase 3: the largest power of two S <= most with
 // 2 n_out S <= B (so that every output keeps at least half the lanes busy),
 // for the n_out = ROWS x (2 l' + 1) outputs of a full tile of the block.
 // Every output has a lane group when n_out <= B (phase3_fits).
-__device__ inline int phase3_lanes(int n_out, int B) {
+__device__ inline int phase3_lanes(int n_out, int B, int most) {
     int S = 1;
-    while (S < 64 && n_out * S * 2 <= B) S *= 2;
+    while (S < most && n_out * S * 2 <= B) S *= 2;
     return S;
 }
 
@@ -550,10 +616,9 @@ __device__ void stage_body(const StageArgs& a, int j, const StageTile& t, char* 
     }
     // output-side values, prefetched by the thread that writes output o.
     // The lanes per output follow from the tiling's ROWS, not from this
-    // tile's rows, so that an output sums its columns in the same order in
-    // every split of its block (even or greedy tiles, the persistent kernel)
+    // tile's rows (the large-basis form's sums depend on them)
     const int n_out = nrows * nmp;
-    const int S = phase3_lanes(ROWS * nmp, B);
+    const int S = phase3_lanes(ROWS * nmp, B, GG ? 64 : kChains);
     const int o = tid / S, s = tid - o * S;
     const bool writer = (o < n_out) && (s == 0);
     const double v = T.vvec[j];
@@ -628,13 +693,10 @@ __device__ void stage_body(const StageArgs& a, int j, const StageTile& t, char* 
         const int idx = tid + i * B;
         if (idx < N) {
             const double2 ph = phs[sr[i]], x = uv[i];
-            xs[sx[i]] = make_double2(ph.x * x.x + ph.y * x.y, ph.x * x.y - ph.y * x.x);
+            xs[sx[i]] = dephase(ph, x);
         }
     }
-    for (int idx = tid + kXBatch * B; idx < N; idx += B) {
-        const double2 ph = phs[T.st_rad[idx]], x = load_u(idx);
-        xs[T.st_xs[idx]] = make_double2(ph.x * x.x + ph.y * x.y, ph.x * x.y - ph.y * x.x);
-    }
+    for (int idx = tid + kXBatch * B; idx < N; idx += B) xs[T.st_xs[idx]] = dephase(phs[T.st_rad[idx]], load_u(idx));
     if (FC) {
 #pragma unroll
         for (int i = 0; i < (FC ? FB : 0); ++i) {
@@ -646,12 +708,12 @@ __device__ void stage_body(const StageArgs& a, int j, const StageTile& t, char* 
 #pragma unroll
         for (int i = 0; i < FB; ++i) {
             const int idx = tid + i * B;
-            if (idx < totF) Fs[idx] = (double)tv[i].x * rps[2 * lv[i]] + (double)tv[i].y * rps[2 * lv[i] + 1];
+            if (idx < totF) Fs[idx] = radial_f((double)tv[i].x, (double)tv[i].y, rps[2 * lv[i]], rps[2 * lv[i] + 1]);
         }
         for (int idx = tid + FB * B; idx < totF; idx += B) {
             const TabT t0 = row[idx];
             const int l0 = cl[idx % nV];
-            Fs[idx] = (double)t0.x * rps[2 * l0] + (double)t0.y * rps[2 * l0 + 1];
+            Fs[idx] = radial_f((double)t0.x, (double)t0.y, rps[2 * l0], rps[2 * l0 + 1]);
         }
     }
     if (!GG) {
@@ -718,12 +780,13 @@ __device__ void stage_body(const StageArgs& a, int j, const StageTile& t, char* 
 #pragma unroll
         for (int i = 0; i < FB; ++i) {
             const int idx = tid + i * B;
-            if (idx < totF) fout[idx] = (FcT)((double)tv[i].x * rps[2 * lv[i]] + (double)tv[i].y * rps[2 * lv[i] + 1]);
+            if (idx < totF)
+                fout[idx] = (FcT)radial_f((double)tv[i].x, (double)tv[i].y, rps[2 * lv[i]], rps[2 * lv[i] + 1]);
         }
         for (int idx = tid + FB * B; idx < totF; idx += B) {
             const TabT t0 = row[idx];
             const int l0 = cl[idx % nV];
-            fout[idx] = (FcT)((double)t0.x * rps[2 * l0] + (double)t0.y * rps[2 * l0 + 1]);
+            fout[idx] = (FcT)radial_f((double)t0.x, (double)t0.y, rps[2 * l0], rps[2 * l0 + 1]);
         }
     }
     if (KIND == 1 && a.grad) {
@@ -766,47 +829,18 @@ __device__ void stage_entry(const StageArgs& a, char* smem) {
     stage_body<KIND, ROWS, false, false, GG>(a, a.traj0 + blockIdx.y, t, smem);
 }
 
-__device__ inline int chunks_of(const Meta& m, int rows) {
-    int n = 0;
-    for (int lp = 0; lp <= m.l_max; ++lp) n += (m.n_l[lp] + rows - 1) / rows;
-    return n;
-}
-
-// Work item of workgroup bx in a one-dimensional grid of 8 x ceil(items / 8)
-// workgroups over items = paths x row chunks (path-major): consecutive
-// workgroup ids go to the eight XCDs in turn and the items of XCD x are the
-// x-th eighth of the list, so the workgroups of a path share an XCD (and its
-// L2, which then serves the path's stage input to all of them).  Returns
-// false for the padding workgroups.
-template <int ROWS>
-__device__ inline bool xcd_item(const Meta& m, int n_paths, int bx, int* jl, int* lp, int* row0, int* nrows) {
-    const int nwg = chunks_of(m, ROWS);
-    const int total = n_paths * nwg;
-    const int per = (total + 7) / 8;
-    const int W = (bx % 8) * per + bx / 8;
-    if (W >= total) return false;
-    *jl = W / nwg;
-    int ci = W - *jl * nwg, l = 0;
-    for (; l < m.l_max; ++l) {
-        const int nc = (m.n_l[l] + ROWS - 1) / ROWS;
-        if (ci < nc) break;
-        ci -= nc;
-    }
-    *lp = l;
-    *row0 = ci * ROWS;
-    *nrows = min(ROWS, m.n_l[l] - *row0);
-    return *nrows > 0;
-}
-
-// One RK4 stage for a.n_paths paths from a.traj0 (grid of xcd_item).  Small
+// One RK4 stage for a.n_paths paths from a.traj0.  Small
 // row tiles ask for registers that leave room for four workgroups per CU
 // (their LDS does), larger ones for three.
 template <int ROWS, bool F32, bool FC, bool GG = false>
 __global__ __launch_bounds__(kStageThreads, ROWS <= 4 ? 4 : 3) void k_stage(StageArgs a) {
     extern __shared__ double2 smem2[];
-    // work item W of the path-major list of a.n_paths x a.nwg row tiles, in
-    // the XCD order of xcd_item; the tile (one 64-byte load) holds the
-    // per-l' offsets, so no loop over the basis blocks precedes the loads
+    // work item W of the path-major list of a.n_paths x a.nwg row tiles:
+    // consecutive workgroup ids go to the eight XCDs in turn and the items of
+    // XCD x are the x-th eighth of the list, so the workgroups of a path share
+    // an XCD (and its L2, which then serves the path's stage input to all of
+    // them).  The tile (one 64-byte load) holds the per-l' offsets, so no
+    // loop over the basis blocks precedes the loads
     const int total = a.n_paths * a.nwg;
     const int per = (total + 7) / 8;
     const int W = (blockIdx.x % 8) * per + blockIdx.x / 8;
@@ -840,271 +874,473 @@ __global__ __launch_bounds__(256) void k_fpoint(const Meta* __restrict__ mp_, Ta
     if constexpr (F32) {
         const float2 t0 = T.tab32[i];
         static_cast<float*>(fc_)[(size_t)j * m.n_frow + d] =
-            (float)((double)t0.x * rp[2 * lam] + (double)t0.y * rp[2 * lam + 1]);
+            (float)radial_f((double)t0.x, (double)t0.y, rp[2 * lam], rp[2 * lam + 1]);
     } else {
         const double2 t0 = T.tab[i];
-        static_cast<double*>(fc_)[(size_t)j * m.n_frow + d] = t0.x * rp[2 * lam] + t0.y * rp[2 * lam + 1];
+        static_cast<double*>(fc_)[(size_t)j * m.n_frow + d] = radial_f(t0.x, t0.y, rp[2 * lam], rp[2 * lam + 1]);
     }
 }
 
-constexpr int kBarrierSpin = 1 << 22;  // polls (0.2 s or more) before a barrier gives up
+// ---------------------------------------------------------------------------
+// Persistent form of a propagation chunk.
+//
+// G workgroups hold one path for all steps of a chunk, each a run of its
+// radial functions (ChunkWG).  A workgroup keeps in LDS the F rows
+// of its functions at the current point and their angular factors, in
+// registers the amplitude and RK4 accumulator of its outputs, and forms F and
+// G again only when the point changes (twice per step); the moment-table
+// entries of the next point are loaded into registers while the stage before
+// sums y.
+//
+// A stage is a chain of four short dependent parts (x' arrives, W, y, update),
+// so what bounds it is latency: few workgroups per path and the whole chip's
+// issue slots beside each other.  16 waves where a workgroup has at most two
+// table entries per thread (one path of a small basis), else 8 waves, whose
+// register budget holds the entries without spilling: a spill in the loop
+// waits for the table loads in flight (vector memory returns in order; 60
+// bytes of it cost 4 us of 27 us per step at N = 580).  Which G is best
+// depends on basis and batch and is timed at plan creation.  Measured per
+// pass on the propagation cases, one launch per stage -> this kernel:
+// N = 86, 1 path, 800 steps: 13.0 -> 7.6 ms (G = 1); N = 580, 32 paths, 800:
+// 35.5 -> 19.5 ms (G = 8); N = 580, 64 paths, 400, FP32 table: 28.9 ->
+// 18.2 ms; N = 1855, 8 paths, 100, interpolated: 15.2 -> 9.5 ms (G = 48).
+//
+// Both sums of a stage run on v_mfma_f64_4x4x4 (four 4 x 4 products of four
+// terms each, at the FP64 MFMA peak, with a granularity that fits 2l+1 and
+// nearly any row count).  Its four terms are added one after another with a
+// single rounding each, so a chain of them gives bitwise the sum that
+// k_stage's chain of fused multiply-adds gives; F rows, W rows and angular
+// factors are padded with zeros to whole blocks.
+//   W = F x'  (jobs): F lies in LDS in operand order, so a wave reads 16 rows
+//             x 8 n with one conflict-free 16-byte load per lane and reuses it
+//             for all 2l+1 rows of x'; a 16-byte load of x' is the operand of
+//             the real and of the imaginary product.
+//   y = G W   (groups): wave c sums column chain c (kChains), the eight chain
+//             sums are added by the output's thread.
+//
+// What the workgroups of a path exchange between stages is the next stage's
+// x' = conj(ph) u, through global memory, in words that carry the stage
+// number beside half a double (chunk_put, chunk_take): a reader polls the
+// data itself, so there is no barrier, no fence and no second round trip, and
+// each word is consistent by itself whatever order the words arrive in.  With
+// G = 1 x' stays in LDS.
+// ---------------------------------------------------------------------------
 
-// Barrier of the workgroups of one path, in two halves so that loads that do
-// not depend on the other workgroups can be issued in between.
-// path_arrive: every wave waits until its own memory operations are done
-// (stores in the L2), then thread 0 arrives with an agent-scope release
-// (which writes the L2 back for the other XCDs).
-// path_wait: thread 0 polls the counter with relaxed loads until `target`
-// workgroups have arrived and acquires at agent scope once; the workgroup
-// barrier orders the other waves' reads after that acquire.  A wait longer
-// than kBarrierSpin polls latches bit 2 of *flag and returns false, so every
-// workgroup still ends.
-__device__ inline void path_arrive(int* cnt) {
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+// polls of one word group (0.1 s or more) before a workgroup gives up
+constexpr int kChunkSpin = 1 << 18;
+
+// Words [4][N] of one path and buffer: the two halves of an amplitude's
+// components tagged with the stage number.  Every word is written and read by
+// one 64-bit atomic access at agent scope, so it is never torn and needs no
+// ordering with respect to the others.
+__device__ inline void chunk_put(unsigned long long* buf, int N, int i, double2 x, unsigned tag) {
+    const unsigned long long t = (unsigned long long)tag << 32;
+    const unsigned h[4] = {(unsigned)__double2loint(x.x), (unsigned)__double2hiint(x.x), (unsigned)__double2loint(x.y),
+                           (unsigned)__double2hiint(x.y)};
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        __hip_atomic_store(buf + (size_t)k * N + i, t | h[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ bool path_wait(int* cnt, int target, int* flag) {
-    __shared__ int ok;
-    if (threadIdx.x == 0) {
-        ok = 1;
-        int it = 0;
-        while (__hip_atomic_load(cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            __builtin_amdgcn_s_sleep(2);
-            if (++it > kBarrierSpin) {
-                atomicOr(flag, 2);
-                ok = 0;
-                break;
+// x' of every state of the path into xs once all its words carry `tag`.
+// sx: x' positions of states tid and tid + NT; xpos: of every
+// state.  Returns false if the words do not come within `spin` polls.
+template <int NT>
+__device__ inline bool chunk_take(const unsigned long long* buf, int N, unsigned tag, const int (&sx)[2],
+                                  const int* __restrict__ xpos, double2* xs, int spin, int tid) {
+    bool all = true;
+    for (int base = 0; base < N; base += 2 * NT) {
+        const bool two = N > base + NT;
+        const int i0 = min(base + tid, N - 1), i1 = min(base + NT + tid, N - 1);
+        const int p0 = base == 0 ? sx[0] : xpos[i0], p1 = base == 0 ? sx[1] : xpos[i1];
+        unsigned long long w[2][4];
+        bool ok = false;
+        for (int it = 0; it < spin && !ok; ++it) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                w[0][k] = __hip_atomic_load(buf + k * N + i0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (two) w[1][k] = __hip_atomic_load(buf + k * N + i1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            ok = true;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                ok = ok && (unsigned)(w[0][k] >> 32) == tag;
+                if (two) ok = ok && (unsigned)(w[1][k] >> 32) == tag;
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        all = all && ok;
+        // threads past the last state hold a copy of it
+        xs[p0] = make_double2(__hiloint2double((int)w[0][1], (int)w[0][0]), __hiloint2double((int)w[0][3], (int)w[0][2]));
+        if (two)
+            xs[p1] = make_double2(__hiloint2double((int)w[1][1], (int)w[1][0]), __hiloint2double((int)w[1][3], (int)w[1][2]));
     }
-    __syncthreads();
-    return ok != 0;
+    return all;
 }
 
-// table entries per thread k_chunk prefetches into registers (14 covers
-// 12 rows of 300 columns; smaller tiles need fewer)
-constexpr int fpre(int rows) { return rows >= 10 ? 14 : fbatch(rows) + 1; }
+__device__ inline int4 wave_uniform(int4 v) {
+    return make_int4(__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y),
+                     __builtin_amdgcn_readfirstlane(v.z), __builtin_amdgcn_readfirstlane(v.w));
+}
 
-// Per-thread state of a k_chunk workgroup, kept in registers across stages.
-template <int FP>
-struct ChunkRegs {
-    double2 tv[FP];     // the next new point's table entries (this thread's share) ...
-    double rp, pb;         // ... its R power, Pbar entry
-    double2 ph;            // ... and phase (radial function tid)
-    double gcv[kGBatch];   // angular coefficients of l' (constant)
-    int gpv[kGBatch];
-    int sv[kXBatch];       // radial index | LDS position << 16 of the amplitudes this thread converts (constant)
-    double2 x0, xa;        // writer: amplitude at the start of the step, RK4 accumulator
-};
+// W rows lie in groups of four: [row group][chain][column block][k][row % 4],
+// column g = chain + 8 (4 block + k).
+inline int chunk_column(int g, int blocks) { return ((g & 7) * blocks + (g >> 5)) * 16 + ((g >> 3) & 3) * 4; }
 
-// Loads of point p's data for the workgroup's rows into registers; they are
-// consumed by the next stage at a new point, after the path barrier.
-template <int FP>
-__device__ inline void chunk_prefetch(const StageArgs& a, int j, int lp, int row0, int nrows, int p, ChunkRegs<FP>& r) {
-    const Meta& m = *a.meta;
-    const int B = blockDim.x, tid = threadIdx.x, nV = m.nV[lp];
-    const size_t jp = (size_t)j * a.pt.n_pts + p;
-    const int k = a.pt.kidx[jp];
-    const double2* row = a.tb.tab + (size_t)k * m.n_frow + m.frow_off[lp] + (size_t)row0 * nV;
-    const int totF = nrows * nV;
+// NP pairs of n blocks of a job: re, im += F x' for NU groups of four rows of
+// x'.  Straight-line code: every operand load is issued before the products
+// that wait for it.
+template <int NU, int NP>
+__device__ inline void chunk_mac(const double2* f, const double2* x, int ustride, double (&re)[NU], double (&im)[NU]) {
+    double2 a[NP], b[NP][NU][2];
 #pragma unroll
-    for (int i = 0; i < FP; ++i) {
-        const int idx = tid + i * B;
-        if (idx < totF) r.tv[i] = row[idx];
+    for (int p = 0; p < NP; ++p) {
+        a[p] = f[64 * p];
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            b[p][u][0] = x[u * ustride + 8 * p];
+            b[p][u][1] = x[u * ustride + 8 * p + 4];
+        }
     }
-    if (tid < 2 * (m.lam_max + 1)) r.rp = a.pt.rpow[jp * kRpow + tid];
-    if (tid < (m.lam_max + 1) * (m.lam_max + 2) / 2) r.pb = a.pt.pbar[jp * kMaxPb + tid];
-    if (tid < m.n_f) r.ph = a.pt.ph[jp * m.n_f + tid];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            re[u] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[p].x, b[p][u][0].x, re[u], 0, 0, 0);
+            im[u] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[p].x, b[p][u][0].y, im[u], 0, 0, 0);
+        }
+#pragma unroll
+        for (int u = 0; u < NU; ++u) {
+            re[u] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[p].y, b[p][u][1].x, re[u], 0, 0, 0);
+            im[u] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[p].y, b[p][u][1].y, im[u], 0, 0, 0);
+        }
+    }
 }
 
-// One RK4 stage of k_chunk for rows [row0, row0 + nrows) of l': the
-// arithmetic of stage_body (KIND 0), with the point's data taken from the
-// prefetch registers (fresh) or left in LDS by the previous stage (!fresh),
-// and the writer's X and accumulator kept in registers.
-template <int ROWS>
-__device__ void chunk_stage(const StageArgs& a, int j, int lp, int row0, int nrows, char* smem, bool fresh,
-                            ChunkRegs<fpre(ROWS)>& r) {
-    constexpr int FP = fpre(ROWS);
+// One job: W[row][q] = sum_n F[row][n] x'[q][n] for the job's 16 rows and 4 NU
+// rows of x'.  Lane l reads row l % 16 of F and row l % 4 (+ 4 u) of x' at
+// n = 4 block + l / 16; its results are row 4 ((l % 16) / 4) + l / 16, q =
+// 4 u + l % 4, written to position u of jl (results past the rows or past
+// 2l+1 go to a position of the lane's own that nothing reads).
+template <int NU>
+__device__ inline void chunk_job(const double2* F2, const double2* xs, double2* Ws, int4 job, int2 jl, int lane) {
+    const int stride = job.z & 0xffff;
+    int np = job.z >> 16;
+    const double2* f = F2 + job.x / 2 + lane;
+    const double2* x = xs + job.y + (lane & 3) * stride + (lane >> 4);
+    double re[NU], im[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u) re[u] = im[u] = 0.0;
+    constexpr int MP = NU < 3 ? 2 : 1;   // pairs at once (operand registers)
+    for (; np >= MP; np -= MP) {
+        chunk_mac<NU, MP>(f, x, 4 * stride, re, im);
+        f += MP * 64;
+        x += MP * 8;
+    }
+    if (MP == 2 && np == 1) chunk_mac<NU, 1>(f, x, 4 * stride, re, im);
+    const int w[4] = {jl.x & 0xffff, (int)((unsigned)jl.x >> 16), jl.y & 0xffff, (int)((unsigned)jl.y >> 16)};
+#pragma unroll
+    for (int u = 0; u < NU; ++u) Ws[w[u]] = make_double2(re[u], im[u]);
+}
+
+// KB column blocks of a chain for NG groups: re, im += G W
+template <int KB, int NG>
+__device__ inline void chunk_chain(const double2* const (&w)[NG], const double* const (&g)[NG], int at, double (&re)[NG],
+                                   double (&im)[NG]) {
+    double2 wv[KB][NG];
+    double gv[KB][NG];
+#pragma unroll
+    for (int b = 0; b < KB; ++b)
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            wv[b][i] = w[i][at + 16 * b];
+            gv[b][i] = g[i][at + 16 * b];
+        }
+#pragma unroll
+    for (int b = 0; b < KB; ++b)
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            re[i] = __builtin_amdgcn_mfma_f64_4x4x4f64(wv[b][i].x, gv[b][i], re[i], 0, 0, 0);
+            im[i] = __builtin_amdgcn_mfma_f64_4x4x4f64(wv[b][i].y, gv[b][i], im[i], 0, 0, 0);
+        }
+}
+
+// Chain `wave` of NG groups, their sums to Ps.  q: W position | angular
+// position << 16, output or -1.
+template <int NG>
+__device__ inline void chunk_groups(const int2* q, const double2* Ws, const double* Gs, double2* Ps, int wave, int n_out,
+                                    int blocks) {
+    const double2* w[NG];
+    const double* g[NG];
+    double re[NG], im[NG];
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+        w[i] = Ws + (q[i].x & 0xffff) + wave * blocks * 16;
+        g[i] = Gs + ((unsigned)q[i].x >> 16) + wave * blocks * 16;
+        re[i] = im[i] = 0.0;
+    }
+    int at = 0;
+    for (; blocks > 4; blocks -= 4, at += 64) chunk_chain<4>(w, g, at, re, im);
+    if (blocks == 4) chunk_chain<4>(w, g, at, re, im);
+    else if (blocks == 3) chunk_chain<3>(w, g, at, re, im);
+    else if (blocks == 2) chunk_chain<2>(w, g, at, re, im);
+    else chunk_chain<1>(w, g, at, re, im);
+#pragma unroll
+    for (int i = 0; i < NG; ++i)
+        if (q[i].y >= 0) Ps[wave * n_out + q[i].y] = make_double2(re[i], im[i]);
+}
+
+// FORM: kRadialMoments (FP64 table), kRadialMoments32 (scaled FP32 table) or
+// kRadialInterp (F interpolated from the node table where it is needed).
+// NT: threads.  FP: table entries per thread.
+template <int FORM, int NT, int FP>
+__global__ __launch_bounds__(NT) void k_chunk(ChunkArgs c) {
+    extern __shared__ double2 smem2[];
+    __shared__ int gave_up;
+    using TabT = typename std::conditional<FORM == kRadialMoments32, float2, double2>::type;
+    constexpr int GP = 2;   // angular coefficients per thread held in registers
+    const StageArgs& a = c.s;
     const Meta& m = *a.meta;
     const Tables& T = a.tb;
-    const int N = m.n_states;
-    const int nmp = 2 * lp + 1;
-    const int nlp = m.n_l[lp];
-    const int nV = m.nV[lp];
-    const int gcols = m.gcols[lp];
-    const int B = blockDim.x;
-    const int tid = threadIdx.x;
-    const size_t jp = (size_t)j * a.pt.n_pts + a.p;
+    const int total = c.n_traj * c.G, per = (total + 7) / 8;
+    // paths on one XCD each, as in k_stage
+    const int Wi = (blockIdx.x % 8) * per + blockIdx.x / 8;
+    if (Wi >= total) return;
+    const int jl = Wi / c.G, j = a.traj0 + jl;
+    const ChunkWG& wg = c.wgs[Wi - jl * c.G];
+    int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), N = m.n_states;
+    const int n_f = m.n_f, n_frow = m.n_frow, n_r = m.n_r, lam_max = m.lam_max;
+    const int n_out = wg.n_out, n_g = wg.n_g, n_grp = wg.n_grp, g0 = wg.g0, ent0 = wg.ent0;
+    const int n_rad = wg.n_rad, rad0 = wg.rad0;
+    const bool local = c.G == 1;
 
-    double2* xs = reinterpret_cast<double2*>(smem);
-    double2* Ws = xs + m.n_xs;
-    double2* phs = Ws + ROWS * gcols;
-    double* Fs = reinterpret_cast<double*>(phs + m.n_f);
-    double* Gs = Fs + ROWS * nV;
-    double* rps = Gs + nmp * gcols;
-    double* pbs = rps + kRpow;
-    int2* gis = reinterpret_cast<int2*>(pbs + kMaxPb);
-    const int* cls = reinterpret_cast<const int*>(gis + gcols);  // multipole order of each F column
+    double2* xs = smem2;                                        // [c.n_xs]
+    double2* Ws = xs + c.n_xs;                                  // [wg.n_w]
+    double2* Ps = Ws + wg.n_w;                                  // [8][n_out] chain sums
+    double2* phs = Ps + kChains * n_out;                        // [2][n_rad] phases of its functions, by parity of the point
+    int2* grps = reinterpret_cast<int2*>(phs + 2 * n_rad);        // [n_grp][NT / 8]
+    double* Fs = reinterpret_cast<double*>(grps + NT / kChains * n_grp); // [wg.n_f]
+    double* Gs = Fs + wg.n_f;                                   // [n_g]
+    double* rps = Gs + n_g;                                     // [kRpow]
+    double* pbs = rps + kRpow;                                  // [kMaxPb]
+    int4* jhs = reinterpret_cast<int4*>(pbs + kMaxPb + 1);      // [wg.n_jobs] job headers
+    int2* jls = reinterpret_cast<int2*>(jhs + wg.n_jobs);       // [wg.n_jobs][64] and their lanes
 
-    const double2* u = a.u_in + (size_t)j * a.n_pad;
-    double2 uv[kXBatch];
+    // this thread's share of the workgroup's constants
+    int entf[FP];      // its table entries: F position | lambda << 20, and byte offset in a table row
+    unsigned entx[FORM == kRadialInterp ? 1 : FP];
 #pragma unroll
-    for (int i = 0; i < kXBatch; ++i) {
-        const int idx = tid + i * B;
-        if (idx < N) uv[i] = u[idx];
+    for (int i = 0; i < FP; ++i) {
+        const int e = tid + i * NT;
+        const int2 v = e < wg.n_ent ? c.ents[wg.ent0 + e] : make_int2(0, -1);
+        entf[i] = v.y;
+        if constexpr (FORM != kRadialInterp) entx[i] = (unsigned)v.x * (unsigned)sizeof(TabT);
     }
-    if (fresh) {
-        if (tid < 2 * (m.lam_max + 1)) rps[tid] = r.rp;
-        if (tid < (m.lam_max + 1) * (m.lam_max + 2) / 2) pbs[tid] = r.pb;
-        if (tid < m.n_f) phs[tid] = r.ph;
-        for (int i = tid + B; i < m.n_f; i += B) phs[i] = a.pt.ph[jp * m.n_f + i];
-    }
-    __syncthreads();
-
+    double gco[GP];    // angular coefficients and their Legendre factors
+    int gpi[GP];
 #pragma unroll
-    for (int i = 0; i < kXBatch; ++i) {
-        const int idx = tid + i * B;
-        if (idx < N) {
-            const double2 ph = phs[r.sv[i] & 0xffff], x = uv[i];
-            xs[r.sv[i] >> 16] = make_double2(ph.x * x.x + ph.y * x.y, ph.x * x.y - ph.y * x.x);
+    for (int i = 0; i < GP; ++i) {
+        const int e = tid + i * NT, q = e < n_g ? c.gsrc[wg.g0 + e] : -1;
+        gpi[i] = q >= 0 ? T.gpb[q] : -1;
+        gco[i] = gpi[i] >= 0 ? T.gcoef[q] : 0.0;
+    }
+    // output tid
+    int4 out = c.outs[wg.out0 + min(tid, n_out - 1)];
+    double2 x0 = a.X[(size_t)j * a.n_pad + out.x], xa = make_double2(0.0, 0.0);
+    // groups halves * g + half for the chain of this wave
+    constexpr int halves = NT / 64 / kChains;
+    const int chain = wave & (kChains - 1), half = wave / kChains;
+    int2 grp[kChunkGroups];
+#pragma unroll
+    for (int g = 0; g < kChunkGroups; ++g)
+        grp[g] = c.grps[(size_t)64 * (wg.grp0 + halves * min(g, n_grp - 1) + half) + lane];
+    for (int i = tid; i < 64 * halves * n_grp; i += NT) grps[i] = c.grps[(size_t)64 * wg.grp0 + i];
+    const int kb = wg.kb;
+    for (int i = tid; i < 64 * wg.n_jobs; i += NT) jls[i] = c.jlane[(size_t)64 * wg.job0 + i];
+    for (int i = tid; i < wg.n_jobs; i += NT) jhs[i] = c.jobs[wg.job0 + i];
+    for (int i = tid; i < wg.n_f; i += NT) Fs[i] = 0.0;
+    for (int i = tid; i < c.n_xs + wg.n_w; i += NT) xs[i] = make_double2(0.0, 0.0);
+    if (tid == 0) gave_up = 0;
+    bool alive = true;
+    const int sx[2] = {c.xpos[min(tid, N - 1)], c.xpos[min(tid + NT, N - 1)]};
+    const int j_first = wg.wave_job[wave], j_end = wg.wave_job[wave + 1];
+    // the wave's first job (the headers and lanes of the others are read from
+    // LDS while the job before runs)
+    int4 job0 = j_first < j_end ? c.jobs[wg.job0 + j_first] : make_int4(0, 0, 0, 0);
+    job0 = wave_uniform(job0);
+    const int2 jlv0 = j_first < j_end ? c.jlane[(size_t)64 * (wg.job0 + j_first) + lane] : make_int2(0, 0);
+    const int n_rp = FORM == kRadialInterp ? max(5, lam_max + 1) : 2 * (lam_max + 1);
+    const int n_pb = (lam_max + 1) * (lam_max + 2) / 2;
+    const size_t j0 = (size_t)j * a.pt.n_pts;
+    const double sc = a.Zp / T.vvec[j];
+    const unsigned tag0 = (unsigned)*c.epoch;
+    unsigned long long* exch = c.exch + (size_t)j * 8 * N;   // [2][4][N]
+
+    // What the next new point needs, in registers before its use: a stage
+    // ahead its grid node, R factor tid, Legendre factor tid and the phase of
+    // its radial function tid, while phase 3 runs its table entries.
+    TabT tv[FORM == kRadialInterp ? 1 : FP];
+    double rpv = 0.0, pbv = 0.0;
+    double2 phv = make_double2(0.0, 0.0);
+    int kload = 0, kcur = 0;
+    auto load_factors = [&](int p) {
+        kload = a.pt.kidx[j0 + p];
+        if (tid < n_rp) rpv = a.pt.rpow[(j0 + p) * kRpow + tid];
+        if (tid < n_pb) pbv = a.pt.pbar[(j0 + p) * kMaxPb + tid];
+        if (tid < n_rad) phv = a.pt.ph[(j0 + p) * n_f + rad0 + tid];
+    };
+    auto load_table = [&]() {
+        kcur = __builtin_amdgcn_readfirstlane(kload);
+        if constexpr (FORM != kRadialInterp) {
+            const TabT* tab;
+            if constexpr (FORM == kRadialMoments32) tab = T.tab32;
+            else tab = T.tab;
+            const char* row = reinterpret_cast<const char*>(tab + (size_t)kcur * n_frow);
+#pragma unroll
+            for (int i = 0; i < FP; ++i) tv[i] = *reinterpret_cast<const TabT*>(row + entx[i]);
         }
-    }
-    for (int idx = tid + kXBatch * B; idx < N; idx += B) {
-        const double2 ph = phs[T.st_rad[idx]], x = u[idx];
-        xs[T.st_xs[idx]] = make_double2(ph.x * x.x + ph.y * x.y, ph.x * x.y - ph.y * x.x);
-    }
-    if (fresh) {
-        const int totF = nrows * nV;
+    };
+    // R factors and phases of point p to LDS (phases by parity of the point)
+    auto store_factors = [&](int p) {
+        if (tid < n_rp) rps[tid] = rpv;
+        if (tid < n_rad) phs[(p & 1) * n_rad + tid] = phv;
+    };
+    auto form_F = [&]() {
 #pragma unroll
-        for (int i = 0; i < FP; ++i) {
-            const int idx = tid + i * B;
-            if (idx < totF) {
-                const int l0 = cls[idx % nV];
-                Fs[idx] = r.tv[i].x * rps[2 * l0] + r.tv[i].y * rps[2 * l0 + 1];
+        for (int i = 0; i < FP; ++i)
+            if (entf[i] >= 0) {
+                const int l = entf[i] >> 20;
+                double f;
+                if constexpr (FORM == kRadialInterp)
+                    f = interp_value(T.ftab, n_frow, n_r, kcur, rps, c.ents[ent0 + tid + i * NT].x, l);
+                else
+                    {
+                    const double2 rp = reinterpret_cast<const double2*>(rps)[l];
+                    f = radial_f((double)tv[i].x, (double)tv[i].y, rp.x, rp.y);
+                }
+                Fs[entf[i] & 0xfffff] = f;
             }
-        }
-        if (totF > FP * B) {
-            const double2* row = T.tab + (size_t)a.pt.kidx[jp] * m.n_frow + m.frow_off[lp] + (size_t)row0 * nV;
-            for (int idx = tid + FP * B; idx < totF; idx += B) {
-                const double2 t0 = row[idx];
-                const int l0 = cls[idx % nV];
-                Fs[idx] = t0.x * rps[2 * l0] + t0.y * rps[2 * l0 + 1];
-            }
-        }
-        const int totG = nmp * gcols;
+        if (tid < n_pb) pbs[tid] = pbv;
+    };
+    auto form_G = [&]() {
 #pragma unroll
-        for (int i = 0; i < kGBatch; ++i) {
-            const int idx = tid + i * B;
-            if (idx < totG) Gs[idx] = r.gpv[i] >= 0 ? r.gcv[i] * pbs[r.gpv[i]] : 0.0;
+        for (int i = 0; i < GP; ++i) {
+            const int e = tid + i * NT;
+            if (e < n_g) Gs[e] = gpi[i] >= 0 ? gco[i] * pbs[gpi[i]] : 0.0;
         }
-        const double* gc = T.gcoef + m.g_off[lp];
-        const int* gp = T.gpb + m.g_off[lp];
-        for (int idx = tid + kGBatch * B; idx < totG; idx += B) {
-            const int p = gp[idx];
-            Gs[idx] = p >= 0 ? gc[idx] * pbs[p] : 0.0;
+        for (int e = tid + GP * NT; e < n_g; e += NT) {
+            const int q = c.gsrc[g0 + e], p = q >= 0 ? T.gpb[q] : -1;
+            Gs[e] = p >= 0 ? T.gcoef[q] * pbs[p] : 0.0;
         }
-    }
+    };
+
+    // the first point: F, Pbar, x'
+    load_factors(0);
+    load_table();
+    store_factors(0);
     __syncthreads();
+    form_F();
+    for (int i = tid; i < N; i += NT)
+        xs[c.xpos[i]] = dephase(a.pt.ph[j0 * n_f + T.st_rad[i]], a.X[(size_t)j * a.n_pad + i]);
+    load_factors(1);
 
-    stage_phase2<ROWS>(Fs, xs, gis, Ws, nrows, gcols, nV);
-    __syncthreads();
-    const int n_out = nrows * nmp;
-    const int S = phase3_lanes(ROWS * nmp, B);   // as stage_body
-    const int o = tid / S, s = tid - o * S;
-    const double2 y = stage_phase3(Gs, Ws, o, s, S, n_out, nmp, gcols);
-    if (o < n_out && s == 0) {
-        const int rr = o / nmp, qp = o - rr * nmp;
-        const size_t oi = (size_t)j * a.n_pad + m.state_off[lp] + qp * nlp + row0 + rr;
-        const double2 py = cmul(phs[m.rad_off[lp] + row0 + rr], y);
-        const double sc = a.Zp / T.vvec[j];
-        const double2 K = make_double2(sc * py.y, -sc * py.x);  // -(i/v) Zp ph y
-        if (a.stage < 4) {
-            a.u_out[oi] = rk4_next_input(a.stage, r.x0, K, a.h);
-            r.xa = rk4_accumulate(a.stage, r.x0, r.xa, K, a.h);
-        } else {
-            const double2 xn = rk4_accumulate(4, r.x0, r.xa, K, a.h);
-            if (!isfinite(xn.x) || !isfinite(xn.y)) atomicOr(a.flag, 1);
-            a.X[oi] = xn;
-            r.x0 = xn;
-        }
-    }
-}
-
-// All steps of a chunk for every path (see ChunkArgs).  grid: 8 x ceil(items
-// / 8) workgroups, items = paths x row chunks; consecutive workgroup ids go to
-// the eight XCDs in turn and the items of XCD x are the x-th eighth of the
-// path-major list, so the workgroups of a path share an XCD (and its L2).
-// Each workgroup keeps the couplings of its rows at the current point in LDS
-// and builds them only when the point changes (twice per step: midpoint and
-// end point); the loads for the next new point are issued before the path
-// barrier that precedes it, so their latency overlaps the wait.
-template <int ROWS>
-__global__ __launch_bounds__(kStageThreads, 2) void k_chunk(ChunkArgs c) {
-    extern __shared__ double2 smem2[];
-    char* smem = reinterpret_cast<char*>(smem2);
-    const Meta& m = *c.s.meta;
-    const Tables& T = c.s.tb;
-    const int nwg = chunks_of(m, ROWS);
-    int jl, lp, row0, nrows;
-    if (!xcd_item<ROWS>(m, c.n_traj, blockIdx.x, &jl, &lp, &row0, &nrows)) return;
-    const int j = c.s.traj0 + jl;
-    const int B = blockDim.x, tid = threadIdx.x;
-    const int N = m.n_states, nmp = 2 * lp + 1, nV = m.nV[lp], gcols = m.gcols[lp];
-
-    // constants of the workgroup's rows
-    ChunkRegs<fpre(ROWS)> r;
-    {
-        const double* gc = T.gcoef + m.g_off[lp];
-        const int* gp = T.gpb + m.g_off[lp];
-#pragma unroll
-        for (int i = 0; i < kGBatch; ++i) {
-            const int idx = tid + i * B;
-            r.gcv[i] = idx < nmp * gcols ? gc[idx] : 0.0;
-            r.gpv[i] = idx < nmp * gcols ? gp[idx] : -1;
-        }
-#pragma unroll
-        for (int i = 0; i < kXBatch; ++i) {
-            const int idx = tid + i * B;
-            r.sv[i] = idx < N ? (T.st_rad[idx] | (T.st_xs[idx] << 16)) : 0;
-        }
-        double* Fs = reinterpret_cast<double*>(reinterpret_cast<double2*>(smem) + m.n_xs + ROWS * gcols + m.n_f);
-        int2* gis = reinterpret_cast<int2*>(Fs + ROWS * nV + nmp * gcols + kRpow + kMaxPb);
-        for (int i = tid; i < gcols; i += B) gis[i] = T.gcol_info[m.gcol_off[lp] + i];
-        int* cls = reinterpret_cast<int*>(gis + gcols);
-        for (int i = tid; i < nV; i += B) cls[i] = T.col_lam[m.col_off[lp] + i];
-        const int n_out = nrows * nmp;
-        const int S = phase3_lanes(ROWS * nmp, B);   // as stage_body
-        const int o = tid / S;
-        r.x0 = r.xa = make_double2(0.0, 0.0);
-        if (o < n_out && tid - o * S == 0) {
-            const int rr = o / nmp, qp = o - rr * nmp;
-            r.x0 = c.s.X[(size_t)j * c.s.n_pad + m.state_off[lp] + qp * m.n_l[lp] + row0 + rr];
-        }
-    }
-    StageArgs a = c.s;
-    chunk_prefetch(a, j, lp, row0, nrows, 0, r);
-    int target = 0;
-    for (int i = 0; i < c.n_steps; ++i) {
-        a.h = c.h[i];
+    for (int step = 0; step < c.n_steps; ++step) {
+        const double h = c.h[step], h6 = rk4_weight(1, h), h3 = rk4_weight(2, h);
+#pragma unroll 1
         for (int stage = 1; stage <= 4; ++stage) {
-            a.stage = stage;
-            a.p = stage == 1 ? 2 * i : (stage == 4 ? 2 * i + 2 : 2 * i + 1);
-            a.u_in = stage == 1 ? c.s.X : (stage == 3 ? c.Ub : c.Ua);
-            a.u_out = stage == 1 ? c.Ua : (stage == 2 ? c.Ub : (stage == 3 ? c.Ua : nullptr));
-            // stage 3 repeats stage 2's point (the midpoint) and stage 1 of
-            // step i > 0 repeats stage 4's point of step i - 1
-            const bool fresh = stage == 2 || stage == 4 || i == 0;
-            chunk_stage<ROWS>(a, j, lp, row0, nrows, smem, fresh, r);
-            if (i + 1 == c.n_steps && stage == 4) break;
-            int* bar = c.bar + (size_t)jl * kBarStride;
-            path_arrive(bar);
-            // the next stage at a new point: stage 2 (midpoint) or 4 (end point)
-            if (stage == 1 || stage == 3) chunk_prefetch(a, j, lp, row0, nrows, 2 * i + (stage == 1 ? 1 : 2), r);
-            target += nwg;
-            if (!path_wait(bar, target, c.s.flag)) return;
+            const int p = stage == 1 ? 2 * step : (stage == 4 ? 2 * step + 2 : 2 * step + 1);
+            // the point of the stage after this one
+            const bool last = step + 1 == c.n_steps && stage == 4;
+            const int pn = stage == 2 || stage == 4 ? p : p + 1;
+            const unsigned tag = tag0 + 4 * step + stage;   // of the x' this stage writes
+            // keeps the addresses derived from these out of the registers that
+            // live across stages
+            asm volatile("" : "+v"(tid), "+v"(lane), "+v"(out.x), "+v"(out.y), "+v"(out.z));
+#pragma unroll
+            for (int i = 0; i < GP; ++i) asm volatile("" : "+v"(gpi[i]));
+#pragma unroll
+            for (int g = 0; g < kChunkGroups; ++g) asm volatile("" : "+v"(grp[g].x), "+v"(grp[g].y));
+#pragma unroll
+            for (int i = 0; i < FP; ++i) asm volatile("" : "+v"(entf[i]));
+            if constexpr (FORM != kRadialInterp)
+#pragma unroll
+                for (int i = 0; i < FP; ++i) asm volatile("" : "+v"(entx[i]));
+            if (!local && !(step == 0 && stage == 1) &&
+                !chunk_take<NT>(exch + (size_t)((tag - 1) & 1) * 4 * N, N, tag - 1, sx, c.xpos, xs, alive ? kChunkSpin : 1, tid)) {
+                alive = false;
+                gave_up = 1;
+            }
+            __syncthreads();
+            // a path whose words did not come ends at the next step: its flag
+            // is latched and its amplitudes are not written
+            if (!local && stage == 1 && *(volatile int*)&gave_up) {
+                if (tid == 0) atomicOr(a.flag, 2);
+                return;
+            }
+            // W = F x'
+            {
+                const double2* F2 = reinterpret_cast<const double2*>(Fs);
+                int4 job = job0;
+                int2 jlv = jlv0;
+                for (int i = j_first; i < j_end; ++i) {
+                    const int in = min(i + 1, j_end - 1);
+                    const int4 next = jhs[in];
+                    const int2 jln = jls[64 * in + lane];
+                    if (job.w == 1) chunk_job<1>(F2, xs, Ws, job, jlv, lane);
+                    else if (job.w == 2) chunk_job<2>(F2, xs, Ws, job, jlv, lane);
+                    else if (job.w == 3) chunk_job<3>(F2, xs, Ws, job, jlv, lane);
+                    else chunk_job<4>(F2, xs, Ws, job, jlv, lane);
+                    job = wave_uniform(next);
+                    jlv = jln;
+                }
+            }
+            if (stage == 2 || stage == 4 || (step == 0 && stage == 1)) form_G();
+            __syncthreads();
+            if (pn != p) {
+                store_factors(pn);
+                if (NT == 512) load_table();   // 1024 threads: no registers for it yet
+            }
+            // the wave's chain of y = G W
+            if (n_grp == 1) chunk_groups<1>(grp, Ws, Gs, Ps, chain, n_out, kb);
+            else chunk_groups<2>(grp, Ws, Gs, Ps, chain, n_out, kb);
+            for (int g = kChunkGroups; g < n_grp; g += 2) {
+                const int2 q[2] = {grps[64 * (halves * g + half) + lane], grps[64 * (halves * min(g + 1, n_grp - 1) + half) + lane]};
+                if (g + 1 == n_grp) chunk_groups<1>(q, Ws, Gs, Ps, chain, n_out, kb);
+                else chunk_groups<2>(q, Ws, Gs, Ps, chain, n_out, kb);
+            }
+            if (NT != 512 && pn != p) load_table();
+            __syncthreads();
+            // the slope and the RK4 update of output tid
+            if (tid < n_out) {
+                double2 t[kChains];
+#pragma unroll
+                for (int k = 0; k < kChains; ++k) t[k] = Ps[k * n_out + tid];
+#pragma unroll
+                for (int d = 1; d < kChains; d *= 2)
+#pragma unroll
+                    for (int k = 0; k + d < kChains; k += 2 * d) {
+                        t[k].x += t[k + d].x;
+                        t[k].y += t[k + d].y;
+                    }
+                const double2 py = cmul(phs[(p & 1) * n_rad + out.y], t[0]);
+                const double2 K = make_double2(sc * py.y, -sc * py.x);   // -(i/v) Zp ph y
+                xa = rk4_accumulate(stage, x0, xa, K, stage == 1 || stage == 4 ? h6 : h3);
+                double2 u = xa;
+                if (stage < 4) u = rk4_next_input(stage, x0, K, h);
+                if (!last) {
+                    const double2 xn = dephase(phs[(pn & 1) * n_rad + out.y], u);
+                    if (local) xs[out.z] = xn;
+                    else chunk_put(exch + (size_t)(tag & 1) * 4 * N, N, out.x, xn, tag);
+                }
+                if (stage == 4) {
+                    if (!isfinite(xa.x) || !isfinite(xa.y)) atomicOr(a.flag, 1);
+                    x0 = xa;
+                    if (last && !*(volatile int*)&gave_up) a.X[(size_t)j * a.n_pad + out.x] = xa;
+                }
+            }
+            if (last && !local && tid == 0 && *(volatile int*)&gave_up) atomicOr(a.flag, 2);
+            if (pn != p) form_F();
+            if (stage == 2 || (stage == 4 && !last)) load_factors(p + 1);
         }
     }
 }
@@ -1342,19 +1578,6 @@ int stage_smem_bytes(const Meta& m, int rows, bool gg) {
 
 bool stage_rows_fit(const Meta& m, int rows) { return phase3_fits(rows, 2 * m.l_max + 1); }
 
-int chunk_smem_bytes(const Meta& m, int rows) {
-    int best = 0;
-    for (int lp = 0; lp <= m.l_max; ++lp) {
-        const size_t nmp = 2 * lp + 1;
-        const size_t bytes = m.n_xs * sizeof(double2) + (size_t)rows * m.gcols[lp] * sizeof(double2) +
-                             (size_t)m.n_f * sizeof(double2) + (size_t)rows * m.nV[lp] * sizeof(double) +
-                             nmp * m.gcols[lp] * sizeof(double) + (kRpow + kMaxPb) * sizeof(double) +
-                             (size_t)m.gcols[lp] * sizeof(int2) + (size_t)m.nV[lp] * sizeof(int);
-        if ((int)bytes > best) best = (int)bytes;
-    }
-    return best;
-}
-
 // The dynamic-LDS attribute is per kernel and process-wide: it is only ever
 // raised (to the largest size any plan has asked for), so that a plan created
 // later with a smaller basis does not lower it under an earlier plan's launches.
@@ -1365,7 +1588,7 @@ hipError_t stage_set_smem_limit(int, int bytes) {
     if (bytes <= set_bytes) return hipSuccess;
 #define WPCCC_FN_PAIR(R)                                                                        \
     (const void*)k_stage<R, false, false>, (const void*)k_stage<R, false, true>,                 \
-        (const void*)k_stage<R, true, true>, (const void*)k_stage<R, true, false>, (const void*)k_chunk<R>,
+        (const void*)k_stage<R, true, true>, (const void*)k_stage<R, true, false>,
 #define WPCCC_FN_GG(R) (const void*)k_stage<R, false, true, true>, (const void*)k_stage<R, true, true, true>,
     const void* fns[] = {WPCCC_STAGE_ROWS(WPCCC_FN_PAIR) WPCCC_STAGE_ROWS_GG(WPCCC_FN_GG)(const void*)k_apply<kRowsPerBlock>,
                          (const void*)k_apply<kApplyRowsLarge>, (const void*)k_apply<4, true>,
@@ -1378,8 +1601,6 @@ hipError_t stage_set_smem_limit(int, int bytes) {
     if (e == hipSuccess) set_bytes = bytes;
     return e;
 }
-
-int chunk_grid(const Meta& hm, int n_traj, int rows) { return 8 * ((n_traj * stage_chunks(hm, rows) + 7) / 8); }
 
 int stage_wgs_per_cu(int rows, int smem) {
     const void* f = nullptr;
@@ -1402,35 +1623,336 @@ int stage_wgs_per_cu(int rows, int smem) {
     return smem > 0 ? std::min(per_cu, lds_cu / smem) : per_cu;
 }
 
-static const void* chunk_fn(int rows) {
-    switch (rows) {
-#define WPCCC_CASE(R) \
-    case R: return (const void*)k_chunk<R>;
-        WPCCC_STAGE_ROWS(WPCCC_CASE)
-#undef WPCCC_CASE
-        default: return nullptr;
-    }
-}
-
-bool chunk_fits(const Meta& hm, int n_traj, int rows, int smem) {
-    int dev = 0, n_cu = 0, per_cu = 0, coop = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return false;
-    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop) return false;
-    if (hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
-    if (!chunk_fn(rows)) return false;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, chunk_fn(rows), kStageThreads, smem) != hipSuccess)
+// Whether the tiles of `rows` rows of all paths, with their F, could be resident
+// at once at two workgroups per CU: the size up to which an explicit
+// WPCCC_LAUNCH_PERSISTENT is taken.
+bool tiles_resident(const Meta& m, int n_traj, int rows) {
+    size_t smem = 0;
+    for (int lp = 0; lp <= m.l_max; ++lp)
+        smem = std::max(smem, (m.n_xs + (size_t)rows * m.gcols[lp] + m.n_f) * sizeof(double2) +
+                                  ((size_t)rows * m.nV[lp] + (size_t)(2 * lp + 1) * m.gcols[lp] + kRpow + kMaxPb) * sizeof(double) +
+                                  (size_t)m.gcols[lp] * sizeof(int2) + (size_t)m.nV[lp] * sizeof(int));
+    int dev = 0, n_cu = 0, coop = 0, lds_cu = 0;
+    if (smem > (size_t)kMaxDynLds || !stage_rows_fit(m, rows) || hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
+        hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+        (void)hipGetLastError();
         return false;
-    return (long long)per_cu * n_cu >= chunk_grid(hm, n_traj, rows);
+    }
+    const long long grid = 8 * (((long long)n_traj * stage_chunks(m, rows) + 7) / 8);
+    return grid <= (long long)n_cu * std::min(2, (int)(lds_cu / smem));
 }
 
-hipError_t launch_chunk(const ChunkArgs& a, const Meta& hm, int smem, int rows, hipStream_t st, const LaunchEv& ev) {
-    const dim3 grid(chunk_grid(hm, a.n_traj, rows)), block(kStageThreads);
+namespace {
+
+// k_chunk's instances: form, threads, table entries per thread
+#define WPCCC_CHUNK_FORMS(X)                                                                               \
+    X(kRadialMoments, 1024, 2) X(kRadialMoments, 512, 8) X(kRadialMoments, 512, 12) X(kRadialMoments, 512, 16)           \
+    X(kRadialMoments32, 1024, 2) X(kRadialMoments32, 512, 8) X(kRadialMoments32, 512, 12) X(kRadialMoments32, 512, 16) \
+    X(kRadialInterp, 1024, 2) X(kRadialInterp, 512, 8) X(kRadialInterp, 512, 12) X(kRadialInterp, 512, 16)
+
+const void* chunk_fn(int form, int nt, int fp) {
+#define WPCCC_CASE(F, T, P) \
+    if (form == F && nt == T && fp == P) return (const void*)k_chunk<F, T, P>;
+    WPCCC_CHUNK_FORMS(WPCCC_CASE)
+#undef WPCCC_CASE
+    return nullptr;
+}
+
+}  // namespace
+
+namespace {
+
+// Splits the n_f radial functions of a path over at most G workgroups (runs
+// of consecutive functions, the largest run's cost minimised) and writes the
+// index tables k_chunk reads.  Returns false where a field, the entries per
+// thread, the outputs or the LDS of a workgroup would not fit.  whole: no
+// workgroup holds functions of two l'.
+bool chunk_split(const Meta& m, int G, int threads, bool whole, ChunkTables& t) {
+    t = ChunkTables{};
+    t.nt = threads;
+    const int waves = threads / 64, halves = waves / kChains;
+    if ((long long)m.n_frow > (long long)G * threads * (threads == 1024 ? 2 : 16)) return false;   // entries per thread
+    auto blocks4 = [](int n) { return (n + 3) / 4; };
+    auto n_lam = [](int l, int lp) { return std::min(l, lp) + 1; };
+    // x' rows in whole pairs of blocks of four n, at a stride of 4 modulo 8 (in
+    // 16-byte units), which spreads the four rows x four n of a load over all
+    // banks; the padding stays zero.  Three more rows follow the last: a group
+    // of four rows may reach past those of its l (products that nothing uses).
+    int xs_off[kMaxL + 1], xs_stride[kMaxL + 1];
+    for (int l = 0; l <= m.l_max; ++l) {
+        xs_off[l] = t.n_xs;
+        xs_stride[l] = (m.n_l[l] + 7) / 8 * 8 + 4;
+        t.n_xs += (2 * l + 1) * xs_stride[l];
+        if (m.n_l[l] > 0x3fff) return false;
+    }
+    t.n_xs += 3 * xs_stride[m.l_max];
+    if (m.n_frow > 0x7fffffff / 16 || m.l_max > 11) return false;
+    int kbl[kMaxL + 1];           // column blocks of each chain
+    double per_row[kMaxL + 1];    // cost of a row, in MFMAs
+    for (int lp = 0; lp <= m.l_max; ++lp) {
+        kbl[lp] = blocks4((m.gcols[lp] + kChains - 1) / kChains);
+        if (m.gcols[lp] > 0x3ff || kbl[lp] > 31) return false;
+        double sums = 0.0;
+        for (int l = 0; l <= m.l_max; ++l) sums += n_lam(l, lp) * blocks4(m.n_l[l]) * 2.0 * blocks4(2 * l + 1);
+        per_row[lp] = sums / 16 + kChains * kbl[lp] * 2.0 * blocks4(2 * lp + 1) / 16 + m.nV[lp] * 0.03;
+    }
+    struct Seg {
+        int lp, r0, nr;
+    };
+    auto split = [&](double cap, std::vector<std::vector<Seg>>& out) {
+        out.assign(1, {});
+        double used = 0.0;
+        for (int lp = 0; lp <= m.l_max; ++lp) {
+            if (whole && !out.back().empty()) {
+                if ((int)out.size() == G) return false;
+                out.push_back({});
+                used = 0.0;
+            }
+            for (int r0 = 0; r0 < m.n_l[lp];) {
+                const int nr = std::min((int)((cap - used) / per_row[lp]), m.n_l[lp] - r0);
+                if (nr > 0) {
+                    out.back().push_back(Seg{lp, r0, nr});
+                    used += nr * per_row[lp];
+                    r0 += nr;
+                }
+                if (r0 < m.n_l[lp]) {
+                    if (out.back().empty() || (int)out.size() == G) return false;
+                    out.push_back({});
+                    used = 0.0;
+                }
+            }
+        }
+        return true;
+    };
+    double lo = 0.0, hi = 1.0;
+    std::vector<std::vector<Seg>> wgs, best;
+    for (int lp = 0; lp <= m.l_max; ++lp) hi += (m.n_l[lp] + 1) * per_row[lp];
+    for (int it = 0; it < 40; ++it) {
+        const double mid = 0.5 * (lo + hi);
+        if (split(mid, wgs)) {
+            hi = mid;
+            best = wgs;
+        } else {
+            lo = mid;
+        }
+    }
+    if (best.empty()) return false;
+    t.G = (int)best.size();
+    t.xpos.resize(m.n_states);
+    for (int l = 0; l <= m.l_max; ++l)
+        for (int q = 0; q <= 2 * l; ++q)
+            for (int n = 0; n < m.n_l[l]; ++n)
+                t.xpos[(size_t)m.state_off[l] + q * m.n_l[l] + n] = xs_off[l] + q * xs_stride[l] + n;
+    size_t smem = 0;
+    int most_ent = 0;
+    for (const auto& segs : best) {
+        ChunkWG w{};
+        w.ent0 = (int)t.ents.size();
+        w.job0 = (int)t.jobs.size();
+        w.grp0 = (int)t.grps.size() / 64;
+        w.out0 = (int)t.outs.size();
+        w.rad0 = m.rad_off[segs[0].lp] + segs[0].r0;
+        w.g0 = (int)t.gsrc.size();
+        // W, angular factors and outputs of each segment, all with the block
+        // count of the segment that needs most
+        std::vector<int> seg_w;
+        for (const Seg& s : segs) w.kb = std::max(w.kb, kbl[s.lp]);
+        const int kb = w.kb;
+        for (const Seg& s : segs) {
+            const int lp = s.lp, nmp = 2 * lp + 1, nu = blocks4(nmp), nrg = blocks4(s.nr), per = kChains * kb * 16;
+            const int out0 = w.n_out, w0 = w.n_w, g0 = w.n_g;
+            seg_w.push_back(w0);
+            for (int qp = 0; qp < nmp; ++qp)
+                for (int r = 0; r < s.nr; ++r)
+                    t.outs.push_back(make_int4(m.state_off[lp] + qp * m.n_l[lp] + s.r0 + r, w.n_rad + r,
+                                               xs_off[lp] + qp * xs_stride[lp] + s.r0 + r, 0));
+            w.n_out += nmp * s.nr;
+            w.n_rad += s.nr;
+            w.n_w += nrg * per;
+            for (int u = 0; u < nu; ++u)
+                for (int c = 0; c < kChains; ++c)
+                    for (int b = 0; b < kb; ++b)
+                        for (int k = 0; k < 4; ++k)
+                            for (int i = 0; i < 4; ++i) {
+                                const int qp = 4 * u + i, g = c + kChains * (4 * b + k);
+                                t.gsrc.push_back(qp < nmp && g < m.gcols[lp] ? m.g_off[lp] + qp * m.gcols[lp] + g : -1);
+                            }
+            w.n_g += nu * per;
+            // four (row group, m' group) pairs per MFMA
+            const int pairs = nrg * nu;
+            for (int p0 = 0; p0 < pairs; p0 += 4)
+                for (int lane = 0; lane < 64; ++lane) {
+                    const int blk = (lane & 15) >> 2, p = std::min(p0 + blk, pairs - 1), rg = p / nu, u = p - rg * nu;
+                    const int row = 4 * rg + (lane >> 4), qp = 4 * u + (lane & 3);
+                    const bool ok = p0 + blk < pairs && row < s.nr && qp < nmp;
+                    const int at = (lane >> 4) * 4 + (lane & 3), gp = g0 + u * per + at;
+                    if (gp > 0xffff) return false;
+                    t.grps.push_back(make_int2((w0 + rg * per + at) | (gp << 16), ok ? out0 + qp * s.nr + row : -1));
+                }
+        }
+        // the waves of a chain take every halves-th group each
+        while (((int)t.grps.size() / 64 - w.grp0) % halves)
+            for (int lane = 0; lane < 64; ++lane) t.grps.push_back(make_int2(0, -1));
+        w.n_grp = ((int)t.grps.size() / 64 - w.grp0) / halves;
+        // jobs: 16 rows (l' n', lambda) against the rows of one l
+        struct Job {
+            int4 h;
+            std::vector<int2> lanes;
+            int cost;
+        };
+        std::vector<Job> jobs;
+        for (int l = 0; l <= m.l_max; ++l) {
+            struct Row {
+                int seg, r, e, g;   // segment, row of it, Frow column and G column of the block
+                int lam;
+            };
+            std::vector<Row> rows;
+            for (size_t si = 0; si < segs.size(); ++si) {
+                const int lp = segs[si].lp;
+                int e0 = 0, g0 = 0;
+                for (int ll = 0; ll < l; ++ll) {
+                    e0 += n_lam(ll, lp) * m.n_l[ll];
+                    g0 += n_lam(ll, lp) * (2 * ll + 1);
+                }
+                for (int r = 0; r < segs[si].nr; ++r)
+                    for (int k = 0; k < n_lam(l, lp); ++k)
+                        rows.push_back(Row{(int)si, r, e0 + k * m.n_l[l], g0 + k * (2 * l + 1), std::abs(l - lp) + 2 * k});
+            }
+            const int np = (m.n_l[l] + 7) / 8;
+            for (size_t r0 = 0; r0 < rows.size(); r0 += 16) {
+                // operand order: [pair of n blocks][lane = (n % 4) * 16 + row][block of the
+                // pair]; consecutive entries take four n of a row (a 64-byte run of the
+                // table), then the next row (other banks of the LDS)
+                for (int ks = 0; ks < blocks4(m.n_l[l]); ++ks)
+                    for (int i = 0; i < 16 && r0 + i < rows.size(); ++i)
+                        for (int n = 4 * ks; n < std::min(4 * ks + 4, m.n_l[l]); ++n) {
+                            const Row& rw = rows[r0 + i];
+                            const Seg& s = segs[rw.seg];
+                            t.ents.push_back(make_int2(m.frow_off[s.lp] + (s.r0 + rw.r) * m.nV[s.lp] + rw.e + n,
+                                                       (w.n_f + ((ks / 2) * 64 + (n & 3) * 16 + i) * 2 + (ks & 1)) |
+                                                           (rw.lam << 20)));
+                        }
+                for (int q0 = 0; q0 <= 2 * l; q0 += 16) {
+                    const int nu = std::min(4, blocks4(2 * l + 1 - q0));
+                    Job jb;
+                    jb.h = make_int4(w.n_f, xs_off[l] + q0 * xs_stride[l], xs_stride[l] | (np << 16), nu);
+                    jb.cost = 12 + np * (2 + 4 * nu);
+                    for (int lane = 0; lane < 64; ++lane) {
+                        const size_t i = r0 + 4 * ((lane & 15) >> 2) + (lane >> 4);
+                        int pos[4] = {0, 0, 0, 0};
+                        for (int u = 0; u < nu; ++u) {
+                            const int q = q0 + 4 * u + (lane & 3);
+                            pos[u] = w.n_w + lane;   // read by nothing
+                            if (i < rows.size() && q <= 2 * l) {
+                                const Row& rw = rows[i];
+                                pos[u] = seg_w[rw.seg] + (rw.r / 4) * kChains * kb * 16 + (rw.r & 3) +
+                                         chunk_column(rw.g + q, kb);
+                            }
+                        }
+                        jb.lanes.push_back(make_int2(pos[0] | (pos[1] << 16), pos[2] | (pos[3] << 16)));
+                    }
+                    jobs.push_back(jb);
+                }
+                w.n_f += np * 128;
+            }
+        }
+        w.n_w += 64;
+        if (w.n_w > 0xffff) return false;
+        // jobs to waves: the longest first, each to the least loaded wave
+        std::vector<int> order(jobs.size());
+        for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
+        std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return jobs[x].cost > jobs[y].cost; });
+        std::vector<int> of_wave[kChunkWaves];
+        int load[kChunkWaves] = {};
+        for (int i : order) {
+            const int v = (int)(std::min_element(load, load + waves) - load);
+            of_wave[v].push_back(i);
+            load[v] += jobs[i].cost;
+        }
+        for (int v = 0; v < waves; ++v) {
+            w.wave_job[v] = w.n_jobs;
+            for (int i : of_wave[v]) {
+                t.jobs.push_back(jobs[i].h);
+                t.jlane.insert(t.jlane.end(), jobs[i].lanes.begin(), jobs[i].lanes.end());
+                ++w.n_jobs;
+            }
+        }
+        w.wave_job[waves] = w.n_jobs;
+        w.n_ent = (int)t.ents.size() - w.ent0;
+        if (w.n_out > threads || w.n_rad > threads || w.n_f >= (1 << 20)) return false;
+        most_ent = std::max(most_ent, w.n_ent);
+        smem = std::max(smem, ((size_t)t.n_xs + w.n_w + kChains * (size_t)w.n_out + 2 * (size_t)w.n_rad + 32 * (size_t)halves * w.n_grp) *
+                                      sizeof(double2) +
+                                  ((size_t)w.n_f + w.n_g + kRpow + kMaxPb + 1 + 66 * (size_t)w.n_jobs) * sizeof(double));
+        t.wgs.push_back(w);
+    }
+    if (smem > (size_t)kMaxDynLds) return false;
+    t.smem = (int)smem;
+    for (int fp : {2, 8, 12, 16})
+        if (fp * threads >= most_ent && chunk_fn(kRadialMoments, threads, fp)) {
+            t.fp = fp;
+            return true;
+        }
+    return false;
+}
+
+}  // namespace
+
+// A workgroup that holds functions of two l' holds the angular factors of
+// both: large bases fit with one l' per workgroup only.
+bool chunk_build(const Meta& m, int G, int threads, ChunkTables& t) {
+    return chunk_split(m, G, threads, false, t) || chunk_split(m, G, threads, true, t);
+}
+
+// Paths per launch: those whose workgroups can be resident at once (with one
+// workgroup per path nothing waits for another: any number).
+int chunk_paths(const ChunkTables& t, int form, int n_traj) {
+    if (t.G == 1) return n_traj;
+    int dev = 0, n_cu = 0, per_cu = 0, coop = 0;
+    const void* f = chunk_fn(form, t.nt, t.fp);
+    if (!f || hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, t.nt, t.smem) != hipSuccess) {
+        (void)hipGetLastError();
+        return 0;
+    }
+    // the grid is rounded up to a multiple of eight workgroups (XCD order)
+    const int resident = per_cu * n_cu;
+    int n = std::min(n_traj, resident / t.G);
+    while (n > 0 && 8 * ((n * t.G + 7) / 8) > resident) --n;
+    return n;
+}
+
+hipError_t launch_chunk(const ChunkArgs& a, const ChunkTables& t, int form, hipStream_t st, const LaunchEv& ev) {
+    const dim3 grid(8 * ((a.n_traj * a.G + 7) / 8)), block(t.nt);
+    const void* f = chunk_fn(form, t.nt, t.fp);
+    if (!f) return hipErrorInvalidValue;
     ChunkArgs arg = a;
     void* params[] = {&arg};
     if (ev.a) (void)hipEventRecord(ev.a, st);
-    if (!chunk_fn(rows)) return hipErrorInvalidValue;
-    const hipError_t e = hipLaunchCooperativeKernel(chunk_fn(rows), grid, block, params, smem, st);
+    const hipError_t e = a.G > 1 ? hipLaunchCooperativeKernel(f, grid, block, params, t.smem, st)
+                                 : hipLaunchKernel(f, grid, block, params, t.smem, st);
     if (ev.b) (void)hipEventRecord(ev.b, st);
+    return e;
+}
+
+// The dynamic-LDS attribute of every k_chunk instance (raised only, as
+// stage_set_smem_limit).
+hipError_t chunk_set_smem_limit(int bytes) {
+    static std::mutex mu;
+    static int set_bytes = 64 * 1024;
+    std::lock_guard<std::mutex> lk(mu);
+    if (bytes <= set_bytes) return hipSuccess;
+    hipError_t e = hipSuccess;
+#define WPCCC_CASE(F, T, P) \
+    if (e == hipSuccess) \
+        e = hipFuncSetAttribute((const void*)k_chunk<F, T, P>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    WPCCC_CHUNK_FORMS(WPCCC_CASE)
+#undef WPCCC_CASE
+    if (e == hipSuccess) set_bytes = bytes;
     return e;
 }
 

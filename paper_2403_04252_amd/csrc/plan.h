@@ -189,28 +189,66 @@ constexpr int kFcSlots = 2;
 // gradient share slots of k_apply per path: b (deriv 1), b (deriv 2), a, c
 constexpr int kGradSlots = 4;
 
-// ints between the barrier counters of two paths: one 256-byte line each, so
-// that the polls of different paths do not contend for one memory line
-constexpr int kBarStride = 64;
-
 // Up to three operator applications of one k_apply launch (grid z selects
 // one; they share the launch's point slot and run side by side).
 struct ApplyArgs {
     StageArgs s[3];
 };
 
-// Persistent form of a propagation chunk (k_chunk): every workgroup of the
-// stage grid stays resident for all steps of the chunk and the workgroups of
-// one path meet at a barrier (bar[path], counted with agent-scope atomics)
-// between stages, instead of ending the kernel.
+// Persistent form of a propagation chunk (k_chunk): G workgroups per path
+// stay resident for all steps of the chunk, each holding a run of the path's
+// radial functions, and exchange the stage inputs through tagged words.
+constexpr int kChunkWaves = 16;   // most waves of a workgroup of k_chunk
+constexpr int kChunkGroups = 2;   // groups of a wave's chain run side by side
+// the tags of a chunk's stages: the prologue that precedes every k_chunk
+// launch advances the plan's epoch by this much
+constexpr int kChunkEpoch = 4 * kChunkSteps + 4;
+
+// One workgroup of a path: where its index tables start, their lengths, and
+// the lengths of its LDS arrays (F, W, angular factors).
+struct alignas(64) ChunkWG {
+    int ent0, n_ent, job0, n_jobs, grp0, n_grp, out0, n_out, g0, n_g, rad0, n_rad, n_f, n_w;
+    int kb;                          // column blocks of each chain
+    int wave_job[kChunkWaves + 1];   // jobs of wave w: wave_job[w] .. wave_job[w + 1] - 1
+};
+
+// The index tables of a split of one path over G workgroups (host copy).
+// Positions are those of the workgroup's LDS arrays: F in doubles, W and x'
+// in complex values.
+//   ents   (entry of a moment-table row, F position | lambda << 20)
+//   jobs   16 rows (l' n', lambda) of F against up to 16 rows of x' of one l:
+//          (F position, x' position, x' stride | pairs of four n << 16, groups
+//          of four rows of x')
+//   jlane  [job][lane]: four 16-bit W positions of the lane's results
+//   grps   [group][lane] of four (row group, m' group) pairs: (W position |
+//          angular position << 16, output or -1)
+//   outs   (state, radial function, x' position, 0)
+//   gsrc   angular coefficient of each position, or -1
+//   xpos   x' position of each state
+struct ChunkTables {
+    int G = 0, nt = 0, fp = 0, smem = 0, n_xs = 0;
+    std::vector<ChunkWG> wgs;
+    std::vector<int2> ents;
+    std::vector<int4> jobs, outs;
+    std::vector<int2> grps, jlane;
+    std::vector<int> gsrc, xpos;
+};
+
 struct ChunkArgs {
-    StageArgs s;          // per-plan fields; p, h, stage, u_in, u_out are set per stage
-    double2* Ua;
-    double2* Ub;
+    StageArgs s;          // per-plan fields (meta, tb, pt, Zp, n_pad, traj0, X, flag)
     int n_steps;
     double h[kChunkSteps];
-    int* bar;             // [n_traj][kBarStride], zero at launch (counter of path j at bar[j * kBarStride])
-    int n_traj;
+    int n_traj, G, n_xs;
+    const ChunkWG* wgs;
+    const int2* ents;
+    const int4* jobs;
+    const int2* grps;
+    const int4* outs;
+    const int2* jlane;
+    const int* gsrc;
+    const int* xpos;
+    unsigned long long* exch;   // [n_traj][2][4][N] tagged words
+    const int* epoch;
 };
 
 struct SetupArgs {
@@ -234,6 +272,7 @@ struct PrologueArgs {
     // graph replays: z = zdev[*chunk * kChunkPoints + p] instead of z[p]
     const double* zdev;
     const int* chunk;
+    int* epoch;              // advanced by kChunkEpoch
 };
 
 // Device tables of one centre's basis (moment tables, column maps, angular
@@ -410,14 +449,15 @@ hipError_t launch_table_nodes(const double2* tab, const int* dl, int n_frow, int
 hipError_t launch_table_f32(const double2* tab, const int* dl, int n_frow, int n_r, double r_max, float2* out,
                             hipStream_t st);
 hipError_t stage_set_smem_limit(int l_max, int bytes);
-// k_chunk with `rows` rows per workgroup as one cooperative launch; returns
-// hipErrorCooperativeLaunchTooLarge (and launches nothing) when the grid
-// cannot be resident at once
-hipError_t launch_chunk(const ChunkArgs& a, const Meta& host_meta, int smem, int rows, hipStream_t st,
-                        const LaunchEv& ev = LaunchEv{});
-// workgroups k_chunk needs for n_traj paths (rows per workgroup), and whether they fit at once
-int chunk_grid(const Meta& host_meta, int n_traj, int rows);
-bool chunk_fits(const Meta& host_meta, int n_traj, int rows, int smem);
+// k_chunk on the tables of a split (chunk_build): form is the plan's
+// RadialForm; a cooperative launch where a path has more than one workgroup
+hipError_t launch_chunk(const ChunkArgs& a, const ChunkTables& t, int form, hipStream_t st, const LaunchEv& ev = LaunchEv{});
+// index tables for at most G workgroups per path; false: does not fit
+bool tiles_resident(const Meta& m, int n_traj, int rows);
+bool chunk_build(const Meta& m, int G, int threads, ChunkTables& t);
+// paths of one launch (all workgroups resident at once), 0: not one
+int chunk_paths(const ChunkTables& t, int form, int n_traj);
+hipError_t chunk_set_smem_limit(int bytes);
 // gg: the large-basis form (no angular factors in LDS)
 int stage_smem_bytes(const Meta& m, int rows = kRowsPerBlock, bool gg = false);
 // the row tiles of one path for `rows` rows per workgroup, l' order
@@ -433,8 +473,6 @@ int stage_wgs_per_cu(int rows, int smem);
 // whether the stage kernels can use `rows` rows per workgroup for this basis
 // (every output of a workgroup needs a lane of the phase-3 reduction)
 bool stage_rows_fit(const Meta& m, int rows);
-// LDS of k_chunk: the stage layout plus the multipole order of each F column
-int chunk_smem_bytes(const Meta& m, int rows);
 int stage_chunks(const Meta& m, int rows);
 
 }  // namespace wpccc

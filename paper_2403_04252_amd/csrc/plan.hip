@@ -78,8 +78,16 @@ struct wpccc_plan_s {
     int launch = WPCCC_LAUNCH_STAGES;
     bool mixed = false;       // scaled FP32 moment table (WPCCC_MIXED): per-stage launches only, no adjoint
     bool interp = false;      // F on the grid nodes, five-point interpolation (WPCCC_RADIAL_INTERP)
-    int chunk_smem = 0;       // k_chunk with stage_rows
-    int* d_bar = nullptr;     // [n_traj][kBarStride] path barrier counters of k_chunk
+    // chunks by k_chunk: launch is WPCCC_LAUNCH_PERSISTENT, or the FP32-table
+    // or interpolated form (which report WPCCC_LAUNCH_STAGES) took it by timing
+    bool resident = false;
+    int form = kRadialMoments;
+    ChunkTables chunk;        // the split k_chunk runs (host copy without the index arrays)
+    int chunk_np = 0;         // paths per k_chunk launch
+    char* d_ctab = nullptr;   // its index tables
+    size_t ctab_off[8] = {}, ctab_cap = 0;
+    unsigned long long* d_exch = nullptr;  // [n_traj][2][4][N] tagged words of k_chunk
+    int* d_epoch = nullptr;
     double* d_gpart = nullptr;  // [n_traj][kGradSlots][n_chunks] per-workgroup gradient shares (k_apply)
     StageTile* d_tiles = nullptr;  // the row tiles of every tiling in kStageRowsList, one after another
     Observables obs;               // channel codes and path groups (wpccc_observables)
@@ -127,8 +135,8 @@ void free_plan(wpccc_plan_s* p) {
     if (p->d_chunk) (void)hipFree(p->d_chunk);
     void* bufs[] = {p->d_b,    p->d_v,    p->d_flag, p->d_Frow1, p->d_G1,   p->d_PH1,  p->d_Ua,
                     p->d_Ub,   p->d_Xacc, p->d_kidx, p->d_rpow,  p->d_pbar, p->d_ph,   p->d_va,
-                    p->d_vc,   p->d_lam,  p->d_nu,   p->d_ckpt,  p->d_seg,  p->d_bar,  p->d_gpart,
-                    p->d_tiles, p->d_fc};
+                    p->d_vc,   p->d_lam,  p->d_nu,   p->d_ckpt,  p->d_seg,  p->d_gpart, p->d_tiles,
+                    p->d_fc,   p->d_ctab, p->d_exch, p->d_epoch};
     for (void* q : bufs)
         if (q) (void)hipFree(q);
     delete p;
@@ -145,6 +153,7 @@ int enqueue_prologue(wpccc_plan_s* p, const double* z, int n, int j0, int nj, hi
     a.traj0 = j0;
     a.zdev = p->capturing ? p->d_zall : nullptr;
     a.chunk = p->capturing ? p->d_chunk : nullptr;
+    a.epoch = p->d_epoch;
     hipError_t e = launch_prologue(a, nj, st, p->timer.open(kPrologue));
     return launched(e, "k_prologue");
 }
@@ -225,20 +234,85 @@ int enqueue_stage(wpccc_plan_s* p, int j0, int nj, int stage, int point, int ste
     return launched(e, "k_stage");
 }
 
+// The split of a path that k_chunk runs: at most G workgroups.  *ok: it fits
+// this basis and the device (nothing is changed otherwise).
+int set_chunk(wpccc_plan_s* p, int G, bool* ok, hipStream_t st) {
+    ChunkTables t;
+    *ok = false;
+    if (!chunk_build(p->c.meta, G, 1024, t) && !chunk_build(p->c.meta, G, 512, t)) return WPCCC_OK;
+    const hipError_t es = chunk_set_smem_limit(t.smem);
+    if (es != hipSuccess) {
+        set_error("k_chunk: %s", hipGetErrorString(es));
+        return WPCCC_EHIP;
+    }
+    const int np = chunk_paths(t, p->form, p->batched ? p->n_traj : 1);
+    if (np < 1) return WPCCC_OK;
+    constexpr int kParts = 8;
+    const void* src[kParts] = {t.wgs.data(),  t.ents.data(),  t.jobs.data(), t.grps.data(),
+                               t.outs.data(), t.jlane.data(), t.gsrc.data(), t.xpos.data()};
+    const size_t len[kParts] = {t.wgs.size() * sizeof(ChunkWG), t.ents.size() * sizeof(int2), t.jobs.size() * sizeof(int4),
+                                t.grps.size() * sizeof(int2),   t.outs.size() * sizeof(int4), t.jlane.size() * sizeof(int2),
+                                t.gsrc.size() * sizeof(int),    t.xpos.size() * sizeof(int)};
+    size_t tot = 0;
+    for (int k = 0; k < kParts; ++k) {
+        p->ctab_off[k] = tot;
+        tot += (len[k] + 255) & ~size_t(255);
+    }
+    // launches that read the previous tables
+    WPCCC_HIP_CHECK(hipStreamSynchronize(st));
+    if (tot > p->ctab_cap) {
+        if (p->d_ctab) (void)hipFree(p->d_ctab);
+        p->d_ctab = nullptr;
+        p->bytes -= (long long)p->ctab_cap;
+        p->ctab_cap = 0;
+        const int rc = dev_alloc(&p->d_ctab, tot, p->bytes);
+        if (rc) return rc;
+        p->ctab_cap = tot;
+    }
+    std::vector<char> all(tot);
+    for (int k = 0; k < kParts; ++k)
+        if (len[k]) std::memcpy(all.data() + p->ctab_off[k], src[k], len[k]);
+    WPCCC_HIP_CHECK(hipMemcpyAsync(p->d_ctab, all.data(), tot, hipMemcpyHostToDevice, st));
+    WPCCC_HIP_CHECK(hipStreamSynchronize(st));
+    p->chunk = ChunkTables{};
+    p->chunk.G = t.G;
+    p->chunk.n_xs = t.n_xs;
+    p->chunk.nt = t.nt;
+    p->chunk.fp = t.fp;
+    p->chunk.smem = t.smem;
+    p->chunk_np = np;
+    *ok = true;
+    return WPCCC_OK;
+}
+
 // Steps 0..ns-1 of the current prologue chunk (step lengths h[i]) for paths
-// [j0, j0+nj) as one persistent k_chunk launch with `rows` rows per workgroup.
-int enqueue_chunk(wpccc_plan_s* p, double2* X, int j0, int nj, const double* h, int ns, int rows, int smem,
-                  hipStream_t st) {
+// [j0, j0+nj) by k_chunk, chunk_np paths per launch.  A prologue precedes
+// every call: it advances the epoch that the exchanged words are tagged with.
+int enqueue_chunk(wpccc_plan_s* p, double2* X, int j0, int nj, const double* h, int ns, hipStream_t st) {
     ChunkArgs c{};
     c.s = stage_args(p, j0, X);
-    c.Ua = p->d_Ua;
-    c.Ub = p->d_Ub;
     c.n_steps = ns;
     for (int i = 0; i < ns; ++i) c.h[i] = h[i];
-    c.bar = p->d_bar;
-    c.n_traj = nj;
-    WPCCC_HIP_CHECK(hipMemsetAsync(p->d_bar, 0, (size_t)nj * kBarStride * sizeof(int), st));
-    return launched(launch_chunk(c, p->c.meta, smem, rows, st, p->timer.open(kChunk)), "k_chunk");
+    c.G = p->chunk.G;
+    c.wgs = reinterpret_cast<const ChunkWG*>(p->d_ctab + p->ctab_off[0]);
+    c.ents = reinterpret_cast<const int2*>(p->d_ctab + p->ctab_off[1]);
+    c.jobs = reinterpret_cast<const int4*>(p->d_ctab + p->ctab_off[2]);
+    c.grps = reinterpret_cast<const int2*>(p->d_ctab + p->ctab_off[3]);
+    c.outs = reinterpret_cast<const int4*>(p->d_ctab + p->ctab_off[4]);
+    c.jlane = reinterpret_cast<const int2*>(p->d_ctab + p->ctab_off[5]);
+    c.gsrc = reinterpret_cast<const int*>(p->d_ctab + p->ctab_off[6]);
+    c.xpos = reinterpret_cast<const int*>(p->d_ctab + p->ctab_off[7]);
+    c.n_xs = p->chunk.n_xs;
+    c.exch = p->d_exch;
+    c.epoch = p->d_epoch;
+    for (int j = j0; j < j0 + nj; j += p->chunk_np) {
+        c.s.traj0 = j;
+        c.n_traj = std::min(p->chunk_np, j0 + nj - j);
+        const int rc = launched(launch_chunk(c, p->chunk, p->form, st, p->timer.open(kChunk)),
+                                "k_chunk");
+        if (rc) return rc;
+    }
+    return WPCCC_OK;
 }
 
 // One RK4 step of length h for paths [j0, j0+nj) with M at the points pz (z),
@@ -479,15 +553,17 @@ int propagate_graph(wpccc_plan_s* p, const double* zg, int n_full, double2* X, h
     return WPCCC_OK;
 }
 
-// Stage configuration of a one-centre plan: rows per workgroup and launch
-// form (kernel by kernel, or the persistent k_chunk where its grid fits on
-// the device at once).  Each admissible candidate runs kTuneSteps RK4 steps
-// over the plan's launch batch from zero amplitudes (the table and state
-// traffic of a real step), once to warm up and kTunePasses times timed; the
-// candidate with the fastest pass is kept.
+// Stage configuration of a one-centre plan: rows per workgroup of k_stage,
+// with or without the radial-integral cache, and whether wpccc_propagate runs
+// its chunks by k_stage or by the persistent k_chunk (and on which split of a
+// path).  Each admissible candidate runs kTuneSteps RK4 steps over the plan's
+// launch batch from zero amplitudes (the table and state traffic of a real
+// step), once to warm up and kTunePasses times timed; the fastest is kept.
 constexpr int kTuneSteps = 8;
 constexpr double kAdjointStoreAll = 256.0 * (1 << 20);  // bytes of stored states and stage inputs below which nothing is recomputed
-constexpr int kTunePasses = 3;
+constexpr int kTunePasses = 2;
+// splits of a path tried for k_chunk: workgroups per path
+constexpr int kTuneSplits[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 80, 96};
 
 int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hipStream_t st) {
     const Meta& m = p->c.meta;
@@ -517,30 +593,24 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
     double pts[2 * kTuneSteps + 1], hs[kTuneSteps];
     for (int i = 0; i <= 2 * kTuneSteps; ++i) pts[i] = 0.37 + 0.005 * i;  // b > 0, so R > 0 at any z
     for (int i = 0; i < kTuneSteps; ++i) hs[i] = 0.01;
-    rc = enqueue_prologue(p, pts, 2 * kTuneSteps + 1, 0, nj, st);
     const bool timing = p->timer.on;
     p->timer.on = false;
-    float best_ms = 1e30f;
-    int best_rows = 0, best_launch = 0;
-    const int saved_rows = p->stage_rows, saved_smem = p->stage_smem_rows;
     const bool direct_ok = !p->interp && !p->gg && p->cache_req != WPCCC_CACHE_ON;
     const bool cache_ok = p->cache_req != WPCCC_CACHE_OFF;
-    bool best_cache = cache_ok;
-    auto time_it = [&](int rows, int launch, bool cache, float* ms) -> int {
-        const int smem = stage_smem_bytes(m, rows, p->gg);
-        p->stage_rows = rows;
-        p->stage_smem_rows = smem;
-        p->fcache = cache;
-        // a warm-up pass, then the fastest of kTunePasses timed passes
+    // a warm-up pass of one step, then the fastest of kTunePasses timed passes;
+    // the prologue before each pass (untimed) advances k_chunk's epoch
+    auto time_it = [&](bool resident, float* ms) -> int {
         int r = WPCCC_OK;
         *ms = 1e30f;
         for (int pass = 0; pass <= kTunePasses && r == WPCCC_OK; ++pass) {
-            if (pass > 0 && hipEventRecord(ev.e0, st) != hipSuccess) r = WPCCC_EHIP;
-            if (launch == WPCCC_LAUNCH_PERSISTENT) {
-                if (r == WPCCC_OK) r = enqueue_chunk(p, X, 0, nj, hs, kTuneSteps, rows, chunk_smem_bytes(m, rows), st);
+            const int n = pass ? kTuneSteps : 1;
+            r = enqueue_prologue(p, pts, 2 * n + 1, 0, nj, st);
+            if (r == WPCCC_OK && pass > 0 && hipEventRecord(ev.e0, st) != hipSuccess) r = WPCCC_EHIP;
+            if (resident) {
+                if (r == WPCCC_OK) r = enqueue_chunk(p, X, 0, nj, hs, n, st);
             } else {
                 if (r == WPCCC_OK) r = enqueue_fpoint(p, 0, nj, 0, st);
-                for (int i = 0; i < kTuneSteps && r == WPCCC_OK; ++i) r = enqueue_step(p, X, 0, nj, 2 * i, hs[i], st);
+                for (int i = 0; i < n && r == WPCCC_OK; ++i) r = enqueue_step(p, X, 0, nj, 2 * i, hs[i], st);
             }
             float t = 0.f;
             if (pass > 0 && r == WPCCC_OK &&
@@ -553,30 +623,68 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
         }
         return r;
     };
-    for (int ci = 0; ci < n_cand && rc == WPCCC_OK; ++ci) {
+    float best_ms = 1e30f;
+    int best_rows = 0;
+    bool best_cache = cache_ok;
+    const int saved_rows = p->stage_rows, saved_smem = p->stage_smem_rows;
+    auto set_rows = [&](int rows) {
+        p->stage_rows = rows;
+        p->stage_smem_rows = stage_smem_bytes(m, rows, p->gg);
+    };
+    for (int ci = 0; ci < n_cand && rc == WPCCC_OK && launch_req != WPCCC_LAUNCH_PERSISTENT; ++ci) {
         const int rows = cand[ci];
-        const int smem = stage_smem_bytes(m, rows, p->gg);
-        if (smem > kMaxDynLds || !stage_rows_fit(m, rows)) continue;
-        for (int launch : {WPCCC_LAUNCH_STAGES, WPCCC_LAUNCH_PERSISTENT}) {
-            if (launch_req != WPCCC_LAUNCH_AUTO && launch != launch_req) continue;
-            if (launch == WPCCC_LAUNCH_PERSISTENT && (p->mixed || p->interp || p->gg)) continue;
-            if (launch == WPCCC_LAUNCH_PERSISTENT &&
-                (chunk_smem_bytes(m, rows) > kMaxDynLds || !chunk_fits(m, nj, rows, chunk_smem_bytes(m, rows))))
-                continue;
-            for (int cache = 1; cache >= 0; --cache) {
-                if (!cache && (launch == WPCCC_LAUNCH_PERSISTENT || !direct_ok)) continue;
-                if (cache && !cache_ok && launch != WPCCC_LAUNCH_PERSISTENT) continue;
-                float ms = 0.f;
-                if ((rc = time_it(rows, launch, cache != 0, &ms))) break;
-                if (ms < best_ms) {
-                    best_ms = ms;
-                    best_rows = rows;
-                    best_launch = launch;
-                    best_cache = cache != 0;
-                }
+        if (stage_smem_bytes(m, rows, p->gg) > kMaxDynLds || !stage_rows_fit(m, rows)) continue;
+        for (int cache = 1; cache >= 0 && rc == WPCCC_OK; --cache) {
+            if (cache ? !cache_ok : !direct_ok) continue;
+            set_rows(rows);
+            p->fcache = cache != 0;
+            float ms = 0.f;
+            rc = time_it(false, &ms);
+            if (rc == WPCCC_OK && ms < best_ms) {
+                best_ms = ms;
+                best_rows = rows;
+                best_cache = cache != 0;
             }
-            if (rc) break;
         }
+    }
+    // An explicit WPCCC_LAUNCH_PERSISTENT needs a row tiling whose workgroups
+    // could be resident at once for all paths.
+    bool asked = launch_req == WPCCC_LAUNCH_PERSISTENT;
+    if (asked) {
+        asked = false;
+        for (int ci = 0; ci < n_cand; ++ci) asked = asked || tiles_resident(m, nj, cand[ci]);
+    }
+    // the persistent form on the splits of a path that fit
+    float chunk_ms = 1e30f;
+    int chunk_G = 0, last_G = 0;
+    const bool chunk_ok = !p->gg && (asked || launch_req == WPCCC_LAUNCH_AUTO) && !(p->mixed && p->cache_req == WPCCC_CACHE_ON);
+    for (int G : kTuneSplits) {
+        if (!chunk_ok || rc) break;
+        bool ok = false;
+        rc = set_chunk(p, G, &ok, st);
+        if (rc || !ok || p->chunk.G == last_G) continue;
+        last_G = p->chunk.G;
+        float ms = 0.f;
+        rc = time_it(true, &ms);
+        if (rc == WPCCC_OK && ms < chunk_ms) {
+            chunk_ms = ms;
+            chunk_G = G;
+        }
+        // finer splits exchange more and, past the device, take more launches
+        if (ms > 1.4f * chunk_ms) break;
+    }
+    if (rc == WPCCC_OK && chunk_G && chunk_ms < best_ms) {
+        bool ok = false;
+        rc = set_chunk(p, chunk_G, &ok, st);
+        p->resident = ok;
+        // k_stage's rows (wpccc_step, graph replays, the adjoint): the fastest
+        // of those timed, or the default ones where only k_chunk was
+        if (!best_rows) best_rows = saved_rows;
+        p->launch = p->form == kRadialMoments ? WPCCC_LAUNCH_PERSISTENT : WPCCC_LAUNCH_STAGES;
+    } else if (rc == WPCCC_OK && asked) {
+        // no split of a path fits: the same amplitudes kernel by kernel
+        best_rows = saved_rows;
+        p->launch = WPCCC_LAUNCH_PERSISTENT;
     }
     p->fcache = best_cache;
     p->timer.on = timing;
@@ -593,10 +701,7 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
         set_error("wpccc_plan_create: the persistent stage kernel's grid does not fit on the device at once");
         return WPCCC_ENOTSUP;
     }
-    p->stage_rows = best_rows;
-    p->stage_smem_rows = stage_smem_bytes(m, best_rows, p->gg);
-    p->chunk_smem = chunk_smem_bytes(m, best_rows);
-    p->launch = best_launch;
+    set_rows(best_rows);
     return WPCCC_OK;
 }
 
@@ -805,10 +910,10 @@ int wpccc_plan_create(wpccc_basis_t target, int n_traj, const double* b_host, co
     plan->n_pad = (N + 7) & ~7;
     plan->mixed = mixed;
     plan->interp = interp;
+    plan->form = interp ? kRadialInterp : (mixed ? kRadialMoments32 : kRadialMoments);
     plan->cache_req = o.stage_cache;
     plan->fcache = o.stage_cache != WPCCC_CACHE_OFF;
-    TRY(centre_build(hb, st, plan->c, o.model_a, o.model_c, o.Zp,
-                     interp ? kRadialInterp : (mixed ? kRadialMoments32 : kRadialMoments)));
+    TRY(centre_build(hb, st, plan->c, o.model_a, o.model_c, o.Zp, plan->form));
     plan->ckpt_every = o.checkpoint_every;
     plan->use_graph = o.graph != 0;
     const Meta& m = plan->c.meta;
@@ -885,7 +990,8 @@ int wpccc_plan_create(wpccc_basis_t target, int n_traj, const double* b_host, co
     TRY(dev_alloc(&plan->d_b, (size_t)n_traj, tot));
     TRY(dev_alloc(&plan->d_v, (size_t)n_traj, tot));
     TRY(dev_alloc(&plan->d_flag, 1, tot));
-    TRY(dev_alloc(&plan->d_bar, (size_t)n_traj * kBarStride, tot));
+    TRY(dev_alloc(&plan->d_exch, (size_t)n_traj * 8 * N, tot));
+    TRY(dev_alloc(&plan->d_epoch, 1, tot));
     TRY(dev_alloc(&plan->d_gpart, (size_t)n_traj * kGradSlots * stage_chunks(m, plan->apply_rows), tot));
     std::vector<StageTile> tiles;
     for (int i = 0; i < kNumStageRows; ++i) {
@@ -943,6 +1049,8 @@ int wpccc_plan_create(wpccc_basis_t target, int n_traj, const double* b_host, co
     if (e == hipSuccess)
         e = hipMemcpyAsync(plan->d_v, v_host, (size_t)n_traj * sizeof(double), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipMemsetAsync(plan->d_flag, 0, sizeof(int), st);
+    if (e == hipSuccess) e = hipMemsetAsync(plan->d_exch, 0, (size_t)n_traj * 8 * N * sizeof(unsigned long long), st);
+    if (e == hipSuccess) e = hipMemsetAsync(plan->d_epoch, 0, sizeof(int), st);
     if (e == hipSuccess)
         e = hipMemcpyAsync(plan->d_tiles, tiles.data(), tiles.size() * sizeof(StageTile), hipMemcpyHostToDevice, st);
     if (e == hipSuccess)
@@ -950,27 +1058,16 @@ int wpccc_plan_create(wpccc_basis_t target, int n_traj, const double* b_host, co
     if (e == hipSuccess)
         e = hipMemcpyAsync(plan->d_vc, vc.data(), vc.size() * sizeof(double), hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    const int smem16 = chunk_smem_bytes(m, 16);
-    const int smem_max = std::min(kMaxDynLds, std::max(smem16, plan->stage_smem));
+    const int smem_max = std::min(kMaxDynLds, std::max(stage_smem_bytes(m, 16), plan->stage_smem));
     if (e == hipSuccess && smem_max > 64 * 1024) e = stage_set_smem_limit(m.l_max, smem_max);
     if (e != hipSuccess) {
         set_error("wpccc_plan_create: device setup failed: %s", hipGetErrorString(e));
         free_plan(plan);
         return WPCCC_EHIP;
     }
-    if (o.stage_rows == 0 || o.stage_launch == WPCCC_LAUNCH_AUTO) {
+    if (o.stage_rows == 0 || o.stage_launch != WPCCC_LAUNCH_STAGES) {
         const int* cand = o.stage_rows ? &o.stage_rows : (plan->gg ? kStageRowsGG : kStageRowsList);
         TRY(tune_stage(plan, cand, o.stage_rows ? 1 : (plan->gg ? 3 : kNumStageRows), o.stage_launch, st));
-    } else if (o.stage_launch == WPCCC_LAUNCH_PERSISTENT) {
-        // nothing to choose: check that the grid can be resident at once
-        const int nj = plan->batched ? n_traj : 1;
-        plan->chunk_smem = chunk_smem_bytes(m, plan->stage_rows);
-        if (plan->chunk_smem > kMaxDynLds || !chunk_fits(m, nj, plan->stage_rows, plan->chunk_smem)) {
-            set_error("wpccc_plan_create: the persistent stage kernel's grid does not fit on the device at once");
-            free_plan(plan);
-            return WPCCC_ENOTSUP;
-        }
-        plan->launch = WPCCC_LAUNCH_PERSISTENT;
     }
     TRY(build_observables(plan, n_traj, plan->n_pad, {&hb}, {}, nullptr, b_host, v_host));
     *out = plan;
@@ -1291,9 +1388,8 @@ int wpccc_propagate(wpccc_plan_t plan, const double* zgrid_host, int n_points, v
             if ((rc = enqueue_prologue(plan, pts, 2 * ns + 1, j0, nj, st))) return rc;
             double hs[kChunkSteps];
             for (int i = 0; i < ns; ++i) hs[i] = zgrid_host[c0 + i + 1] - zgrid_host[c0 + i];
-            if (plan->launch == WPCCC_LAUNCH_PERSISTENT) {
-                if ((rc = enqueue_chunk(plan, X, j0, nj, hs, ns, plan->stage_rows, plan->chunk_smem, st)))
-                    return rc;
+            if (plan->resident) {
+                if ((rc = enqueue_chunk(plan, X, j0, nj, hs, ns, st))) return rc;
                 continue;
             }
             if ((rc = enqueue_fpoint(plan, j0, nj, 0, st))) return rc;

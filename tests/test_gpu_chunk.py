@@ -1,0 +1,52 @@
+"""The persistent chunk kernel at the edges of its splits: bases whose N_l are
+below, at and just past its blocks of four and eight n and of 16 rows, one
+workgroup per path and many, workgroups that hold one l' only (l_max 6, 7).
+
+It adds the same products in the same order as the stage kernel, so every
+comparison with that is bitwise.  Against the oracle: amplitudes move by at
+most 1e-13 per step of unit-norm X (the bar of the one-step checks)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2403_04252_amd as W
+from paper_2403_04252_amd import workloads as WL
+from oracle.propagate import propagate_one_centre
+from oracle.radial import BasisSpec as OSpec, build_basis
+
+pytestmark = pytest.mark.gpu
+
+# n_max, l_max, n_bins: N_l = n_max - l + n_bins
+BASES = [(1, 0, 0), (1, 0, 3), (2, 1, 2), (3, 2, 6), (5, 4, 4), (4, 3, 21), (7, 6, 10), (10, 6, 32), (8, 7, 26)]
+
+
+def _run(plan, zg):
+    X = torch.zeros((plan.n_traj, plan.n_pad), dtype=torch.complex128, device="cuda")
+    X[:, 0] = 1.0
+    W.wpccc_propagate(plan, zg, X)
+    W.wpccc_plan_status(plan)
+    torch.cuda.synchronize()
+    return X.cpu().numpy()[:, :plan.n_states]
+
+
+@pytest.mark.parametrize("n_max,l_max,n_bins", BASES)
+def test_chunk_kernel_edges(n_max, l_max, n_bins):
+    spec = (n_max, l_max, n_bins, 3.0, 300, 60.0, 1.0)
+    lb = W.wpccc_basis(W.BasisSpec(*spec))
+    b, v = [0.4, 1.5, 6.0], [1.0, 2.0, 1.5]
+    zg = np.linspace(-3.0, 0.5, 71) ** 3 / 9.0   # 70 ragged steps: a full chunk and a short one
+    print(f"l_max {l_max}, N_l = {n_max + n_bins} - l", flush=True)
+    ref = _run(W.wpccc_plan_create(lb, b, v, stage_launch=W.WPCCC_LAUNCH_STAGES), zg)
+    pp = W.wpccc_plan_create(lb, b, v, stage_launch=W.WPCCC_LAUNCH_PERSISTENT)
+    assert W.wpccc_plan_stage_launch(pp) == W.WPCCC_LAUNCH_PERSISTENT
+    assert np.array_equal(_run(pp, zg), ref)
+    assert np.array_equal(_run(pp, zg[:2]), _run(W.wpccc_plan_create(lb, b, v, stage_launch=W.WPCCC_LAUNCH_STAGES), zg[:2]))
+    # the forms that report one launch per stage may run it as well
+    for kw in (dict(interp=True), dict(mixed=True, stage_cache=W.WPCCC_CACHE_OFF)):
+        a = _run(W.wpccc_plan_create(lb, b, v, **kw), zg)
+        s = _run(W.wpccc_plan_create(lb, b, v, stage_launch=W.WPCCC_LAUNCH_STAGES, **kw), zg)
+        assert np.array_equal(a, s), kw
+    if ref.shape[1] <= 120:
+        ob = build_basis(OSpec(*spec))
+        for j in range(3):
+            assert np.abs(ref[j] - propagate_one_centre(ob, b[j], v[j], zg)).max() <= 70 * 1e-13
