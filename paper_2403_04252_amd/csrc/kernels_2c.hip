@@ -232,9 +232,7 @@ __global__ __launch_bounds__(256) void k_2c_interp(InterpArgs a) {
 typedef float flt4 __attribute__((ext_vector_type(4)));
 
 // Output row of register r in lane l of a 16 x 16 MFMA tile (column l % 16),
-// measured on gfx950: 4 r + l / 16 for the FP64 instruction, 4 (l / 16) + r
-// for the FP32 one.
-__device__ inline int mfma_row_f64(int r, int l) { return 4 * r + (l >> 4); }
+// measured on gfx950: 4 (l / 16) + r for the FP32 instruction.
 __device__ inline int mfma_row_f32(int r, int l) { return kF32RowByLaneGroup ? 4 * (l >> 4) + r : 4 * r + (l >> 4); }
 
 constexpr int kWFields = 7;  // cos, sin, W_0..W_2, J_|s-t|, J_(s+t)
@@ -246,35 +244,35 @@ constexpr int kStageThreads2C = 256;  // threads of a contraction workgroup
 // covers the two subtiles of row half mt = wave / 2 and kk0 = (wave % 2) KPW
 // (nk = 2 KPW).  One LDS read of an A value then serves 2 KPW products, one
 // of a B value KPW * SPW / 2, and one of a weight SPW.
+// Nodes per chunk of the FP32 products, whose MFMA is twice as fast: the
+// per-chunk staging and the FP64 accumulation of the chunk sums are spread
+// over more products.
+constexpr int kNodeChunk32 = 2 * kNodeChunk;
+
 // LDS of a contraction workgroup.  As[node][row] and Bs[node][col] hold one
 // chunk of operands at a row pitch of kPitch elements with the row index
 // XOR-ed by 4 (node / 4): the MFMA reads (16 rows of 4 nodes per wave) and the
 // staging writes (8 rows of 8 node quads per wave) then spread over the 64
 // LDS banks with the fewest passes (pitch 40 for FP64, 48 for FP32).
-template <typename T, int NC>
 struct ContractLds {
-    static constexpr int kPitch = sizeof(T) == 8 ? 40 : 48;
-    T As[NC][kPitch], Bs[NC][kPitch];
+    static constexpr int kPitch = 48, NC = kNodeChunk32;
+    float As[NC][kPitch], Bs[NC][kPitch];
     double fl[kWFields][NC];
-    T wk[NC][kMaxK];   // weights w_k(p), formed in FP64 and stored in the product precision
+    float wk[NC][kMaxK];   // weights w_k(p), formed in FP64 and stored in the product precision
 };
 
-// Nodes per chunk: kNodeChunk for FP64; twice that for the FP32 products,
-// whose MFMA is three times faster, so that the per-chunk staging and the
-// FP64 accumulation of the chunk sums are spread over more products.
-template <bool MIXED>
-constexpr int contract_chunk() { return MIXED ? 2 * kNodeChunk : kNodeChunk; }
 __device__ inline int lds_swz(int node) { return 4 * ((node >> 2) & 7); }
 
 // The MFMAs of one chunk for the wave's active subtiles: row halves
 // mt0 .. mt0 + NA - 1 and column halves 0 .. NV - 1 (subtiles wholly outside
 // the block are left out at compile time, so the k-step loop has no
-// branches), KPW weights from kk0.  MIXED: FP32 products summed over the
-// chunk in FP32 MFMA accumulators, then added to the FP64 ones.
-template <bool MIXED, int KPW, int NMT, int NA, int NV, typename T, int NC>
-__device__ __forceinline__ void chunk_mfma(const ContractLds<T, NC>& L, int mt0, int kk0, int li, int lk,
-                                           bool r2, bool c2, dbl4 (&acc)[KPW][NMT][2]) {
-    constexpr int NKS = NC / 4;
+// branches), KPW weights from kk0: FP32 products summed over the chunk in
+// FP32 MFMA accumulators, then added to the FP64 ones.
+template <int KPW, int NMT, int NA, int NV>
+__device__ __forceinline__ void chunk_mfma(const ContractLds& L, int mt0, int kk0, int li, int lk,
+                                           dbl4 (&acc)[KPW][NMT][2]) {
+    typedef float T;
+    constexpr int NKS = ContractLds::NC / 4;
     T av[2][NA], bv[2][NV], w[2][KPW];
     auto load = [&](int ks, int b) {
         const int kr = ks * 4 + lk;
@@ -286,28 +284,7 @@ __device__ __forceinline__ void chunk_mfma(const ContractLds<T, NC>& L, int mt0,
 #pragma unroll
         for (int i = 0; i < KPW; ++i) w[b][i] = L.wk[kr][kk0 + i];
     };
-    if (!MIXED) {
-        // FP64: one variant per weight split (NA = NMT, NV = 2) that skips
-        // the second row half (!r2) and column half (!c2) at run time; an
-        // FP64 MFMA is long enough that the branches cost little, and one
-        // variant instead of four keeps the kernel's code in the instruction
-        // cache
-#pragma unroll
-        for (int ks = 0; ks < NKS; ++ks) {
-            load(ks, 0);
-#pragma unroll
-            for (int i = 0; i < KPW; ++i)
-#pragma unroll
-                for (int u = 0; u < NA; ++u) {
-                    if (u > 0 && !r2) continue;
-                    const double aw = (double)av[0][u] * (double)w[0][i];
-                    acc[i][u][0] = __builtin_amdgcn_mfma_f64_16x16x4f64(aw, (double)bv[0][0], acc[i][u][0], 0, 0, 0);
-                    if (NV > 1 && c2)
-                        acc[i][u][NV - 1] =
-                            __builtin_amdgcn_mfma_f64_16x16x4f64(aw, (double)bv[0][NV - 1], acc[i][u][NV - 1], 0, 0, 0);
-                }
-        }
-    } else {
+    {
         // FP32: k-steps in pairs, buffer 0 holding the even step and buffer 1
         // the odd one (NKS is even), the next step's operands read while the
         // current step's MFMAs issue
@@ -354,12 +331,11 @@ __device__ __forceinline__ void chunk_mfma(const ContractLds<T, NC>& L, int mt0,
 // tile, fixed per workgroup: subtiles wholly outside the block are left out
 // at compile time.  SPW = 2: NA = 1 for every wave, and a wave whose row
 // half lies outside the block skips its MFMAs (one branch per chunk).
-template <bool MIXED, int KPW, int SPW, int NA, int NV>
-__device__ void contract_tile(const ContractArgs& a, int y, int piece, int s, int t, int a0, int b0, bool r2, bool c2,
-                              bool upper, ContractLds<typename std::conditional<MIXED, float, double>::type,
-                                                      contract_chunk<MIXED>()>& L) {
-    typedef typename std::conditional<MIXED, float, double>::type T;
-    constexpr int NC = contract_chunk<MIXED>();   // nodes per chunk
+template <int KPW, int SPW, int NA, int NV>
+__device__ void contract_tile(const ContractArgs& a, int y, int piece, int s, int t, int a0, int b0, bool upper,
+                              ContractLds& L) {
+    typedef float T;
+    constexpr int NC = kNodeChunk32;              // nodes per chunk
     constexpr int NPT = NC / 8;                   // nodes per loader thread and row
     auto& As = L.As;
     auto& Bs = L.Bs;
@@ -455,7 +431,7 @@ __device__ void contract_tile(const ContractArgs& a, int y, int piece, int s, in
         __syncthreads();
         // next chunk's operands in flight during this chunk's MFMA
         if (base + NC < nact) fetch(base + NC);
-        if (rows_in) chunk_mfma<MIXED, KPW, NMT, NA, NV>(L, mt0, kk0, li, lk, r2, c2, acc);
+        if (rows_in) chunk_mfma<KPW, NMT, NA, NV>(L, mt0, kk0, li, lk, acc);
         __syncthreads();
     }
     double* out = a.tmol + ((size_t)y * m.n_split + piece) * m.n_tmol + m.st_off[s][t];
@@ -473,9 +449,252 @@ __device__ void contract_tile(const ContractArgs& a, int y, int piece, int s, in
                 const int jj = b0 + v * 16 + li;
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int ii = a0 + (mt0 + u) * 16 + (MIXED ? mfma_row_f32(r, lane) : mfma_row_f64(r, lane));
+                    const int ii = a0 + (mt0 + u) * 16 + mfma_row_f32(r, lane);
                     if (kk < nk && ii < nA && jj < nB) out[((size_t)ko * nA + ii) * nB + jj] = acc[i][u][v][r];
                 }
+            }
+    }
+}
+
+// ---- FP64 contraction -------------------------------------------------
+//
+// A tile of at most 32 x 32 of a block, all its nk weights, in one workgroup
+// of 2 x 2 waves (row half, column half).  The products run on
+// v_mfma_f64_4x4x4: four 4 x 4 products of four nodes each, the same rate as
+// the 16 x 16 form, whose four blocks here are four weights of one group of
+// four rows (nk = 4, 8, 12), or two weights of two row groups (nk = 2, 6).
+// Edge tiles are then padded to 8 rows and columns instead of 16, and each
+// wave holds nk * 4 QR * 4 CB sums of its QR row sets and CB column groups.
+// The MFMA adds its four terms one after another, so a sum over nodes is the
+// same chain whatever the tile.
+//
+// What bounds it is the FP64 unit: products and the weighting A w share it (48
+// products and 12 weightings of a full tile's k-step reach 67 TF/s of 74 by
+// themselves, with its LDS reads 55-60).  Measured on the three launches of a
+// step of the N = 764 batch, alone: 20.5 -> 19.7 ms (66% of the cycles in
+// MFMA) against 16 x 16 products with the chunk staged between barriers;
+// the pass 241 -> 232 ms; unequal bases, N = 115: 8.1 -> 7.8.
+//
+// LDS, double buffered: per pair of k-steps (eight nodes) [k][row] of the
+// values at nodes k and 4 + k, so one 16-byte read per lane serves two
+// k-steps, at a row pitch that spreads the 4 k x 4 rows of a read over all
+// banks.
+struct Contract64Lds {
+    static constexpr int kPairs = kNodeChunk / 8, kPitch = 36, kWPitch = kMaxK + 1;
+    struct Buf {
+        double2 A[kPairs * 4 * kPitch], B[kPairs * 4 * kPitch], W[kPairs * 4 * kWPitch];
+        double fl[kWFields][kNodeChunk];
+    } buf[2];
+};
+
+// The MFMAs of one chunk: QW weight sets, QR row sets, CB column groups.
+// ao, bo, wo: the lane's places in a k row of A, B and W; rs, ws: rows and
+// weights of a set.  Operands of pair h (eight nodes) are read while the
+// products of the pair before run.
+template <int QW, int QR, int CB>
+struct Chunk64 {
+    double2 av[QR], bv[CB], w[QW];
+    double acc[QW][QR][CB];
+    int ao, bo, wo, rs, ws;
+
+    __device__ __forceinline__ void load_aw(const Contract64Lds::Buf& L, int h) {
+#pragma unroll
+        for (int r = 0; r < QR; ++r) av[r] = L.A[h * 4 * Contract64Lds::kPitch + ao + r * rs];
+#pragma unroll
+        for (int q = 0; q < QW; ++q) w[q] = L.W[h * 4 * Contract64Lds::kWPitch + wo + q * ws];
+    }
+    __device__ __forceinline__ void load_b(const Contract64Lds::Buf& L, int h) {
+#pragma unroll
+        for (int c = 0; c < CB; ++c) bv[c] = L.B[h * 4 * Contract64Lds::kPitch + bo + 4 * c];
+    }
+    // one k-step of four nodes (half 0 or 1 of a pair)
+    __device__ __forceinline__ void products(const double (&aw)[QW][QR], const double (&b)[CB]) {
+#pragma unroll
+        for (int q = 0; q < QW; ++q)
+#pragma unroll
+            for (int r = 0; r < QR; ++r)
+#pragma unroll
+                for (int c = 0; c < CB; ++c)
+                    acc[q][r][c] = __builtin_amdgcn_mfma_f64_4x4x4f64(aw[q][r], b[c], acc[q][r][c], 0, 0, 0);
+    }
+    // the pair whose operands are loaded; then those of pair `next`
+    __device__ __forceinline__ void pair(const Contract64Lds::Buf& L, int next) {
+        double aw[QW][QR], b[CB];
+#pragma unroll
+        for (int q = 0; q < QW; ++q)
+#pragma unroll
+            for (int r = 0; r < QR; ++r) aw[q][r] = av[r].x * w[q].x;
+#pragma unroll
+        for (int c = 0; c < CB; ++c) b[c] = bv[c].x;
+        products(aw, b);
+#pragma unroll
+        for (int q = 0; q < QW; ++q)
+#pragma unroll
+            for (int r = 0; r < QR; ++r) aw[q][r] = av[r].y * w[q].y;
+#pragma unroll
+        for (int c = 0; c < CB; ++c) b[c] = bv[c].y;
+        if (next >= 0) {
+            load_aw(L, next);
+            load_b(L, next);
+        }
+        products(aw, b);
+    }
+};
+
+// PAIR: the blocks of an MFMA are two weights of two row groups.
+template <int QW, bool PAIR, int QR, int CB>
+__device__ __forceinline__ void contract_tile64(const ContractArgs& a, int y, int piece, int s, int t, int a0, int b0, bool upper,
+                                Contract64Lds& L) {
+    constexpr int NC = kNodeChunk, RP = Contract64Lds::kPitch, WP = Contract64Lds::kWPitch;
+    constexpr int rs = PAIR ? 8 : 4, ws = PAIR ? 2 : 4;
+    const Meta2C& m = *a.m;
+    // weights of this block (st_nw) and of this tile: all of them, or the
+    // target potential alone (weight 1) above the diagonal of a block (s, s)
+    // whose overlap follows from the transposed tile (overlap_mirrored)
+    const int n_w = upper ? 1 : st_nw(m.same, m.n_w, s, t), w0 = upper ? 1 : 0;
+    const int nk = st_nk(s, t, n_w);
+    const int o1 = abs(s - t), o2 = s + t;
+    const int nA = m.nA[s], nB = m.nB[t];
+    const size_t nn = m.n_nodes;
+    const double* nd = a.nodes + (size_t)y * m.n_fields * nn;
+    // this work item's node range [p_begin, nact) (whole chunks)
+    const int nact_all = a.n_act[y];
+    const int span = ((nact_all + m.n_split - 1) / m.n_split + NC - 1) / NC * NC;
+    const int p_begin = piece * span;
+    const int nact = min(nact_all, p_begin + span);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    // loader roles: row (column) lr of A (B), four consecutive nodes from kq
+    // (rows past the tile repeat its last: nothing reads their sums); up to
+    // one node field of the weights per thread
+    const int lr = tid >> 3, kq = (tid & 7) * 4;
+    const double* arow = static_cast<const double*>(a.AT) + ((size_t)y * m.rowsT + m.rowT_off[s] + min(a0 + min(lr, 2 * QR * rs - 1), nA - 1)) * nn;
+    const double* brow = static_cast<const double*>(a.BT) + ((size_t)y * m.rowsP + m.rowP_off[t] + min(b0 + min(lr, 8 * CB - 1), nB - 1)) * nn;
+    const bool vec = (nn & 1) == 0;   // 16-byte aligned rows
+    const int ffi = tid / NC, fk = tid % NC;
+    constexpr int kFStep = kStageThreads2C / NC;
+    static_assert(kWFields <= kFStep && NC == 32 && kStageThreads2C == 256, "loader roles");
+    const int field = ffi == 0 ? kFCos : ffi == 1 ? kFSin : ffi < 5 ? kFW + ffi - 2 : ffi == 5 ? kFJ + o1 : kFJ + o2;
+    // weight roles: node fk, weights kk = ffi + q * kFStep as the fl rows of
+    // their three factors (Bessel order, cos/sin, quadrature weight) packed
+    // in 4-bit fields, -1 past nk
+    constexpr int kWIt = (NC * kMaxK + kStageThreads2C - 1) / kStageThreads2C;
+    int wsel[kWIt];
+#pragma unroll
+    for (int q = 0; q < kWIt; ++q) {
+        const int kk = ffi + q * kFStep;
+        const int order = kk / (2 * n_w), trig = (kk / n_w) & 1, w = kk % n_w;
+        wsel[q] = kk < nk ? (5 + order) | (trig << 4) | ((2 + w0 + w) << 8) : -1;
+    }
+    // the wave's share: QR row sets from row 4 QR (or 8 QR) * row half, CB
+    // column groups from 4 CB * column half
+    const int r0 = (wave & 1) * QR * rs, c0 = (wave >> 1) * CB * 4;
+    const int blk = (lane >> 2) & 3, lk = lane >> 4;
+    const int ao = lk * RP + r0 + (lane & 3) + (PAIR ? 4 * (blk >> 1) : 0);
+    const int bo = lk * RP + c0 + (lane & 3);
+    const int wo = lk * WP + (PAIR ? (blk & 1) : blk);
+
+    double2 ra[2], rb[2];
+    double rf = 0.0;
+    auto fetch = [&](int base) {
+        if (vec && base + NC <= nact) {
+            const double2* pa = reinterpret_cast<const double2*>(arow + base + kq);
+            const double2* pb = reinterpret_cast<const double2*>(brow + base + kq);
+            ra[0] = pa[0];
+            ra[1] = pa[1];
+            rb[0] = pb[0];
+            rb[1] = pb[1];
+            if (ffi < kWFields) rf = nd[(size_t)field * nn + base + fk];
+        } else {
+            const int p = base + kq;
+            auto at = [&](const double* row, int e) { return p + e < nact ? row[p + e] : 0.0; };
+            ra[0] = make_double2(at(arow, 0), at(arow, 1));
+            ra[1] = make_double2(at(arow, 2), at(arow, 3));
+            rb[0] = make_double2(at(brow, 0), at(brow, 1));
+            rb[1] = make_double2(at(brow, 2), at(brow, 3));
+            rf = ffi < kWFields && base + fk < nact ? nd[(size_t)field * nn + base + fk] : 0.0;
+        }
+    };
+
+    auto store = [&](Contract64Lds::Buf& B) {
+        // nodes kq .. kq + 3: k rows 0 .. 3 of pair kq / 8, half kq / 4 % 2
+        const int o = 2 * (((kq >> 3) * 4) * RP + lr) + ((kq >> 2) & 1);
+        double* A = reinterpret_cast<double*>(B.A) + o;
+        double* C = reinterpret_cast<double*>(B.B) + o;
+        A[0] = ra[0].x;
+        A[2 * RP] = ra[0].y;
+        A[4 * RP] = ra[1].x;
+        A[6 * RP] = ra[1].y;
+        C[0] = rb[0].x;
+        C[2 * RP] = rb[0].y;
+        C[4 * RP] = rb[1].x;
+        C[6 * RP] = rb[1].y;
+        if (ffi < kWFields) B.fl[ffi][fk] = rf;
+    };
+    auto weights = [&](Contract64Lds::Buf& B) {
+#pragma unroll
+        for (int q = 0; q < kWIt; ++q)
+            if (wsel[q] >= 0)
+                reinterpret_cast<double*>(B.W)[2 * (((fk >> 3) * 4 + (fk & 3)) * WP + ffi + q * kFStep) + ((fk >> 2) & 1)] =
+                    B.fl[wsel[q] & 15][fk] * B.fl[(wsel[q] >> 4) & 15][fk] * B.fl[wsel[q] >> 8][fk];
+    };
+
+    Chunk64<QW, QR, CB> C;
+    C.ao = ao;
+    C.bo = bo;
+    C.wo = wo;
+    C.rs = rs;
+    C.ws = ws;
+#pragma unroll
+    for (int q = 0; q < QW; ++q)
+#pragma unroll
+        for (int r = 0; r < QR; ++r)
+#pragma unroll
+            for (int c = 0; c < CB; ++c) C.acc[q][r][c] = 0.0;
+
+    // While the products of a chunk run, the next one is staged in the other
+    // buffer (operands and fields before the middle barrier, its weights
+    // after it) and the one after that is in flight.
+    static_assert(Contract64Lds::kPairs == 4, "two pairs on either side of the middle barrier");
+    if (p_begin < nact) {
+        fetch(p_begin);
+        store(L.buf[0]);
+        if (p_begin + NC < nact) fetch(p_begin + NC);
+        __syncthreads();
+        weights(L.buf[0]);
+        __syncthreads();
+    }
+    int b = 0;
+    for (int base = p_begin; base < nact; base += NC, b ^= 1) {
+        const Contract64Lds::Buf& B = L.buf[b];
+        const bool more = base + NC < nact;
+        C.load_aw(B, 0);
+        C.load_b(B, 0);
+        if (more) {
+            store(L.buf[b ^ 1]);
+            if (base + 2 * NC < nact) fetch(base + 2 * NC);
+        }
+        C.pair(B, 1);
+        C.pair(B, 2);
+        __syncthreads();
+        if (more) weights(L.buf[b ^ 1]);
+        C.pair(B, 3);
+        C.pair(B, -1);
+        __syncthreads();
+    }
+    double* out = a.tmol + ((size_t)y * m.n_split + piece) * m.n_tmol + m.st_off[s][t];
+#pragma unroll
+    for (int q = 0; q < QW; ++q) {
+        const int kk = ws * q + (PAIR ? (blk & 1) : blk);
+        // position of weight kk of the tile in the block's (order, trig, weight)
+        // layout: an upper tile's weight kk is the target potential (weight 1
+        // of the block's two) of (order, trig) = kk
+        const int ko = upper ? 2 * kk + 1 : kk;
+#pragma unroll
+        for (int r = 0; r < QR; ++r)
+#pragma unroll
+            for (int c = 0; c < CB; ++c) {
+                const int ii = a0 + r0 + r * rs + (PAIR ? 4 * (blk >> 1) : 0) + lk, jj = b0 + c0 + 4 * c + (lane & 3);
+                if (ii < nA && jj < nB) out[((size_t)ko * nA + ii) * nB + jj] = C.acc[q][r][c];
             }
     }
 }
@@ -484,18 +703,17 @@ __device__ void contract_tile(const ContractArgs& a, int y, int piece, int s, in
 // workgroup ids go to the eight XCDs in turn, and the work items of XCD x are
 // the x-th eighth of the job-major list, so the tiles of one job (which
 // stream the same operand rows) share an L2.  Per chunk of nodes (32, or 64
-// for the FP32 products) the 32 rows of A, the 32 columns of B and the node
-// fields of the weights are loaded into registers one chunk ahead (their latency overlaps the MFMA
-// of the current chunk), then staged in LDS; the waves split the nk weights
-// and the four 16 x 16 subtiles as contract_tile describes and feed the MFMA
-// with (A w_k) and B.
+// for the FP32 products) the rows of A, the columns of B and the node fields
+// of the weights are loaded into registers a chunk ahead, then staged in LDS;
+// the waves split the sums as contract_tile64 and contract_tile describe and
+// feed the MFMA with (A w_k) and B.
 //
 // MIXED: the products run on v_mfma_f32_16x16x4f32 (operands in FP32,
 // accumulated in FP32 over the 64 nodes of a chunk) and each chunk's partial
 // sums are added to FP64 accumulators, so the FP32 accumulation error stays
 // that of a 64-term sum whatever the number of nodes.
 template <bool MIXED>
-__global__ __launch_bounds__(kStageThreads2C, MIXED ? 2 : 3) void k_2c_contract(ContractArgs a) {
+__global__ __launch_bounds__(kStageThreads2C, 2) void k_2c_contract(ContractArgs a) {
     const Meta2C& m = *a.m;
     const int per_job = m.n_tiles * m.n_split;
     const int total = per_job * a.n_jobs;
@@ -508,28 +726,54 @@ __global__ __launch_bounds__(kStageThreads2C, MIXED ? 2 : 3) void k_2c_contract(
     const int2 tl = a.tiles[rem - piece * m.n_tiles];
     const int s = tl.x & 0xff, t = (tl.x >> 8) & 0xff, a0 = tl.y & 0xffff, b0 = tl.y >> 16;
     const bool upper = (tl.x & kTileUpper) != 0;
-    __shared__ ContractLds<typename std::conditional<MIXED, float, double>::type, contract_chunk<MIXED>()> L;
-    // second row / column half of the 32 x 32 tile inside the block
-    const bool r2 = a0 + 16 < m.nA[s], c2 = b0 + 16 < m.nB[t];
-    // FP32 products: one compiled variant per set of active subtiles; FP64:
-    // one variant that tests r2 and c2 at run time
-#define WPCCC_TILE4(KPW)                                                                          \
-    if (!MIXED || (r2 && c2)) contract_tile<MIXED, KPW, 4, 2, 2>(a, y, piece, s, t, a0, b0, r2, c2, upper, L); \
-    else if (r2) contract_tile<MIXED, KPW, 4, 2, 1>(a, y, piece, s, t, a0, b0, r2, c2, upper, L);              \
-    else if (c2) contract_tile<MIXED, KPW, 4, 1, 2>(a, y, piece, s, t, a0, b0, r2, c2, upper, L);              \
-    else contract_tile<MIXED, KPW, 4, 1, 1>(a, y, piece, s, t, a0, b0, r2, c2, upper, L);
-#define WPCCC_TILE2(KPW)                                                                          \
-    if (!MIXED || c2) contract_tile<MIXED, KPW, 2, 1, 2>(a, y, piece, s, t, a0, b0, r2, c2, upper, L);         \
-    else contract_tile<MIXED, KPW, 2, 1, 1>(a, y, piece, s, t, a0, b0, r2, c2, upper, L);
-    switch (st_nk(s, t, upper ? 1 : st_nw(m.same, m.n_w, s, t))) {
-        case 2: WPCCC_TILE2(1) break;
-        case 4: WPCCC_TILE4(1) break;
-        case 6: WPCCC_TILE2(3) break;
-        case 8: WPCCC_TILE4(2) break;
-        default: WPCCC_TILE4(3) break;
-    }
+    const int nk = st_nk(s, t, upper ? 1 : st_nw(m.same, m.n_w, s, t));
+    if constexpr (!MIXED) {
+        __shared__ Contract64Lds L;
+        // row sets and column groups of a wave
+        const int r8 = ((tl.x >> 17) & 3) + 1, cb = ((tl.x >> 19) & 3) + 1;
+#define WPCCC_COLS(QW, PAIR, QR)                                                                       \
+    if (cb == 4) contract_tile64<QW, PAIR, QR, 4>(a, y, piece, s, t, a0, b0, upper, L);                \
+    else if (cb == 3) contract_tile64<QW, PAIR, QR, 3>(a, y, piece, s, t, a0, b0, upper, L);           \
+    else if (cb == 2) contract_tile64<QW, PAIR, QR, 2>(a, y, piece, s, t, a0, b0, upper, L);           \
+    else contract_tile64<QW, PAIR, QR, 1>(a, y, piece, s, t, a0, b0, upper, L);
+#define WPCCC_PAIRS(QW)                                                                                \
+    if (r8 > 2) { WPCCC_COLS(QW, true, 2) } else { WPCCC_COLS(QW, true, 1) }
+#define WPCCC_QUADS(QW)                                                                                \
+    if (r8 == 4) { WPCCC_COLS(QW, false, 4) } else if (r8 == 3) { WPCCC_COLS(QW, false, 3) }           \
+    else if (r8 == 2) { WPCCC_COLS(QW, false, 2) } else { WPCCC_COLS(QW, false, 1) }
+        switch (nk) {
+            case 2: WPCCC_PAIRS(1) break;
+            case 4: WPCCC_QUADS(1) break;
+            case 6: WPCCC_PAIRS(3) break;
+            case 8: WPCCC_QUADS(2) break;
+            default: WPCCC_QUADS(3) break;
+        }
+#undef WPCCC_QUADS
+#undef WPCCC_PAIRS
+#undef WPCCC_COLS
+    } else {
+        __shared__ ContractLds L;
+        // second row / column half of the 32 x 32 tile inside the block: one
+        // compiled variant per set of active subtiles
+        const bool r2 = a0 + 16 < m.nA[s], c2 = b0 + 16 < m.nB[t];
+#define WPCCC_TILE4(KPW)                                                                    \
+    if (r2 && c2) contract_tile<KPW, 4, 2, 2>(a, y, piece, s, t, a0, b0, upper, L);         \
+    else if (r2) contract_tile<KPW, 4, 2, 1>(a, y, piece, s, t, a0, b0, upper, L);          \
+    else if (c2) contract_tile<KPW, 4, 1, 2>(a, y, piece, s, t, a0, b0, upper, L);          \
+    else contract_tile<KPW, 4, 1, 1>(a, y, piece, s, t, a0, b0, upper, L);
+#define WPCCC_TILE2(KPW)                                                                    \
+    if (c2) contract_tile<KPW, 2, 1, 2>(a, y, piece, s, t, a0, b0, upper, L);               \
+    else contract_tile<KPW, 2, 1, 1>(a, y, piece, s, t, a0, b0, upper, L);
+        switch (nk) {
+            case 2: WPCCC_TILE2(1) break;
+            case 4: WPCCC_TILE4(1) break;
+            case 6: WPCCC_TILE2(3) break;
+            case 8: WPCCC_TILE4(2) break;
+            default: WPCCC_TILE4(3) break;
+        }
 #undef WPCCC_TILE4
 #undef WPCCC_TILE2
+    }
 }
 
 // Sum of the node-range partial sums of the contraction into range 0, in
@@ -649,7 +893,7 @@ __global__ __launch_bounds__(256) void k_2c_assemble(AssembleArgs a) {
                 const double* base = tm + m.st_off[s][t] + (size_t)is * nBt + jt;
                 // above the diagonal of a block (s, s) the overlap is that of
                 // (b, a) under the same exchange map (overlap_mirrored)
-                const bool ovl_t = overlap_mirrored(m.same, s, t, is, jt);
+                const bool ovl_t = overlap_mirrored(m.same, m.fine, s, t, m.nA[s], is, jt);
                 const double* bt = tm + m.st_off[s][t] + (size_t)jt * nBt + is;
                 const double sgt = ((la + lb) & 1) ? -1.0 : 1.0;
                 for (int w = 0; w < n_w; ++w) {

@@ -68,6 +68,7 @@ struct Meta2C {
     int stT_off[kMaxL + 2], stP_off[kMaxL + 2];  // state offsets per l
     int n_lT[kMaxL + 1], n_lP[kMaxL + 1];
     int n_tiles;
+    int fine;                // tiles in groups of eight rows and columns (tile_of)
     int n_split;             // node ranges per contraction tile; tmol holds one partial sum per range
     // interpolated operands: row r of side T is (s, i) with s = block, i < nA[s]
     int rowsT, rowsP;                  // sum_s nA[s], sum_t nB[t]
@@ -90,11 +91,26 @@ __host__ __device__ inline int st_nw(int same, int n_w, int s, int t) {
 // The same map takes the overlap of a diagonal block (s, s) at (a, b) to the
 // overlap at (b, a), so a tile of such a block above its diagonal (a0 < b0)
 // forms the target potential only; k_2c_assemble reads the overlap there
-// from the transposed tile.  Contraction tiles: x = s | t << 8 | upper << 16,
-// y = a0 | b0 << 16.
+// from the transposed tile.  Contraction tiles: x = s | t << 8 | upper << 16
+// | (row groups - 1) << 17 | (column groups - 1) << 19, y = a0 | b0 << 16.
 constexpr int kTileUpper = 1 << 16;
-__host__ __device__ inline bool overlap_mirrored(int same, int s, int t, int a, int b) {
-    return same && s == t && a / kTile < b / kTile;
+
+// The n rows (columns) of a block in as few tiles of at most kTile as there
+// can be.  fine (the FP64 products, padded to groups of eight): the groups of
+// eight are spread evenly over them, so no tile is a sliver that stages whole
+// chunks for a few products; else whole tiles and a remainder.
+__host__ __device__ inline int tile_of(int fine, int n, int a) {
+    if (!fine) return a / kTile;
+    const int g8 = (n + 7) / 8, nt = (n + kTile - 1) / kTile, q = g8 / nt, r = g8 - q * nt, g = a / 8;
+    return g < r * (q + 1) ? g / (q + 1) : r + (g - r * (q + 1)) / q;
+}
+__host__ __device__ inline int tile_start(int fine, int n, int i) {
+    if (!fine) return i * kTile < n ? i * kTile : n;
+    const int g8 = (n + 7) / 8, nt = (n + kTile - 1) / kTile, q = g8 / nt, r = g8 - q * nt;
+    return 8 * (i * q + (i < r ? i : r));
+}
+__host__ __device__ inline bool overlap_mirrored(int same, int fine, int s, int t, int n, int a, int b) {
+    return same && s == t && tile_of(fine, n, a) < tile_of(fine, n, b);
 }
 
 struct Jobs {

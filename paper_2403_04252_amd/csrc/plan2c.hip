@@ -260,6 +260,7 @@ void fill_meta(const HostBasis& tb, const HostBasis& pb, int n_eta, int n_tau, i
     m.f_pb = m.f_pa + (m.LT + 1) * (m.LT + 2) / 2;
     m.n_fields = m.f_pb + (m.LP + 1) * (m.LP + 2) / 2;
     m.same = same;
+    m.fine = !mixed;
     m.mirror = q_prior && same;
     m.n_w = (q_prior && !m.mirror) ? 3 : 2;
     m.q_prior = q_prior;
@@ -284,18 +285,24 @@ void fill_meta(const HostBasis& tb, const HostBasis& pb, int n_eta, int n_tau, i
             const int nw = st_nw(m.same, m.n_w, s, t);
             if (!nw) continue;   // formed from block (t, s)
             off += st_nk(s, t, nw) * m.nA[s] * m.nB[t];
-            for (int a0 = 0; a0 < m.nA[s]; a0 += kTile)
-                for (int b0 = 0; b0 < m.nB[t]; b0 += kTile)
-                    tiles.push_back(make_int2(s | (t << 8) | (overlap_mirrored(m.same, s, t, a0, b0) ? kTileUpper : 0),
+            const int nta = (m.nA[s] + kTile - 1) / kTile, ntb = (m.nB[t] + kTile - 1) / kTile;
+            for (int ia = 0; ia < nta; ++ia)
+                for (int ib = 0; ib < ntb; ++ib) {
+                    const int a0 = tile_start(m.fine, m.nA[s], ia), b0 = tile_start(m.fine, m.nB[t], ib);
+                    const int r8 = (std::min(tile_start(m.fine, m.nA[s], ia + 1), m.nA[s]) - a0 + 7) / 8;
+                    const int c8 = (std::min(tile_start(m.fine, m.nB[t], ib + 1), m.nB[t]) - b0 + 7) / 8;
+                    const bool upper = overlap_mirrored(m.same, m.fine, s, t, m.nA[s], a0, b0);
+                    tiles.push_back(make_int2(s | (t << 8) | (upper ? kTileUpper : 0) | ((r8 - 1) << 17) | ((c8 - 1) << 19),
                                               a0 | (b0 << 16)));
+                }
         }
-    // heaviest tiles first (weights formed x active 16 x 16 subtiles): the
+    // heaviest tiles first (weights formed x padded rows x columns): the
     // dispatcher takes each XCD's work items in order, so the last ones it
     // hands out are the short ones; the order changes no sum
     auto tile_cost = [&](const int2& q) {
-        const int s = q.x & 0xff, t = (q.x >> 8) & 0xff, a0 = q.y & 0xffff, b0 = q.y >> 16;
+        const int s = q.x & 0xff, t = (q.x >> 8) & 0xff, r8 = ((q.x >> 17) & 3) + 1, c8 = ((q.x >> 19) & 3) + 1;
         const int nk = (q.x & kTileUpper) ? st_nk(s, t, 1) : st_nk(s, t, st_nw(m.same, m.n_w, s, t));
-        return nk * (a0 + 16 < m.nA[s] ? 2 : 1) * (b0 + 16 < m.nB[t] ? 2 : 1);
+        return m.fine ? nk * r8 * c8 : nk * 4 * ((r8 + 1) / 2) * ((c8 + 1) / 2);
     };
     std::stable_sort(tiles.begin(), tiles.end(),
                      [&](const int2& x, const int2& y) { return tile_cost(x) > tile_cost(y); });
