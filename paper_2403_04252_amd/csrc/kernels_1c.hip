@@ -811,11 +811,11 @@ __device__ void stage_body(const StageArgs& a, int j, const StageTile& t, char* 
                 sa += red[1][w];
                 sc += red[2][w];
             }
-            double* g = a.grad + (size_t)j * kGradSlots * gridDim.x + blockIdx.x;
-            g[a.gslot * gridDim.x] += sb;
+            double* g = a.grad + (size_t)j * kGradSlots * a.gn + blockIdx.x;
+            g[a.gslot * a.gn] += sb;
             if (a.model) {
-                g[2 * gridDim.x] += sa;
-                g[3 * gridDim.x] += sc;
+                g[2 * a.gn] += sa;
+                g[3 * a.gn] += sc;
             }
         }
     }
@@ -1091,8 +1091,9 @@ __device__ inline void chunk_groups(const int2* q, const double2* Ws, const doub
 
 // FORM: kRadialMoments (FP64 table), kRadialMoments32 (scaled FP32 table) or
 // kRadialInterp (F interpolated from the node table where it is needed).
-// NT: threads.  FP: table entries per thread.
-template <int FORM, int NT, int FP>
+// NT: threads.  FP: table entries per thread.  ADJ: the adjoint's forms
+// (ChunkArgs::adjoint).
+template <int FORM, int NT, int FP, bool ADJ>
 __global__ __launch_bounds__(NT) void k_chunk(ChunkArgs c) {
     extern __shared__ double2 smem2[];
     __shared__ int gave_up;
@@ -1240,8 +1241,17 @@ __global__ __launch_bounds__(NT) void k_chunk(ChunkArgs c) {
     store_factors(0);
     __syncthreads();
     form_F();
-    for (int i = tid; i < N; i += NT)
-        xs[c.xpos[i]] = dephase(a.pt.ph[j0 * n_f + T.st_rad[i]], a.X[(size_t)j * a.n_pad + i]);
+    const bool rev = ADJ && c.adjoint == kChunkReverse;
+    double2* const mu = rev ? c.mu + (size_t)j * a.n_pad : nullptr;
+    {
+        const double w = rev ? rk4_weight(1, c.h[0]) : 1.0;   // reverse: the first input is h/6 lambda
+        for (int i = tid; i < N; i += NT) {
+            double2 x = a.X[(size_t)j * a.n_pad + i];
+            if (rev) x = make_double2(w * x.x, w * x.y);
+            xs[c.xpos[i]] = dephase(a.pt.ph[j0 * n_f + T.st_rad[i]], x);
+        }
+        if (rev && tid < n_out) mu[out.x] = make_double2(w * x0.x, w * x0.y);
+    }
     load_factors(1);
 
     for (int step = 0; step < c.n_steps; ++step) {
@@ -1324,18 +1334,38 @@ __global__ __launch_bounds__(NT) void k_chunk(ChunkArgs c) {
                     }
                 const double2 py = cmul(phs[(p & 1) * n_rad + out.y], t[0]);
                 const double2 K = make_double2(sc * py.y, -sc * py.x);   // -(i/v) Zp ph y
-                xa = rk4_accumulate(stage, x0, xa, K, stage == 1 || stage == 4 ? h6 : h3);
-                double2 u = xa;
-                if (stage < 4) u = rk4_next_input(stage, x0, K, h);
+                double2 u;
+                if (!rev) {
+                    xa = rk4_accumulate(stage, x0, xa, K, stage == 1 || stage == 4 ? h6 : h3);
+                    u = xa;
+                    if (stage < 4) u = rk4_next_input(stage, x0, K, h);
+                } else {
+                    // nu = M^H mu = -K; lambda of the step before is lambda + the
+                    // four nu; next mu = h/3 lambda + h nu, h/3 lambda + h/2 nu,
+                    // h/6 lambda + h/2 nu, then h'/6 of the new lambda
+                    xa = stage == 1 ? x0 : xa;
+                    xa = make_double2(xa.x - K.x, xa.y - K.y);
+                    const double wn = stage == 1 ? h : 0.5 * h, wl = stage < 3 ? h3 : h6;
+                    u = make_double2(wl * x0.x - wn * K.x, wl * x0.y - wn * K.y);
+                    if (stage == 4 && !last) {
+                        const double w = rk4_weight(1, c.h[step + 1]);
+                        u = make_double2(w * xa.x, w * xa.y);
+                    }
+                    if (!last) mu[(size_t)(4 * step + stage) * c.v + out.x] = u;
+                }
+                if (ADJ && !rev) {
+                    double2* keep = stage < 4 ? c.us + (size_t)(3 * step + stage - 1) * c.v : c.xs + (size_t)(step + 1) * c.v;
+                    keep[(size_t)j * a.n_pad + out.x] = u;
+                }
                 if (!last) {
                     const double2 xn = dephase(phs[(pn & 1) * n_rad + out.y], u);
                     if (local) xs[out.z] = xn;
                     else chunk_put(exch + (size_t)(tag & 1) * 4 * N, N, out.x, xn, tag);
                 }
                 if (stage == 4) {
-                    if (!isfinite(xa.x) || !isfinite(xa.y)) atomicOr(a.flag, 1);
+                    if (!rev && (!isfinite(xa.x) || !isfinite(xa.y))) atomicOr(a.flag, 1);
                     x0 = xa;
-                    if (last && !*(volatile int*)&gave_up) a.X[(size_t)j * a.n_pad + out.x] = xa;
+                    if (last && (!ADJ || rev) && !*(volatile int*)&gave_up) a.X[(size_t)j * a.n_pad + out.x] = xa;
                 }
             }
             if (last && !local && tid == 0 && *(volatile int*)&gave_up) atomicOr(a.flag, 2);
@@ -1358,18 +1388,35 @@ __global__ __launch_bounds__(kStageThreads) void k_apply(ApplyArgs a) {
 // grad[j] = (dL/da, dL/dc, dL/db): the k_apply shares of path j (slots 2, 3
 // and 0 + 1 of gpart[j][kGradSlots][n_part]) summed in a fixed order, so that
 // the result does not depend on the order in which workgroups ran.
-__global__ __launch_bounds__(64) void k_grad_sum(const double* __restrict__ gpart, int n_part,
-                                                 double* __restrict__ grad) {
-    const int j = blockIdx.x, t = threadIdx.x;
-    if (t >= 3) return;
-    const double* g = gpart + (size_t)j * kGradSlots * n_part;
+__global__ __launch_bounds__(192) void k_grad_sum(const double* __restrict__ gpart, int n_part,
+                                                  double* __restrict__ grad) {
+    // wave t: derivative by a, c, b (its two shares)
+    const int j = blockIdx.x, t = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const double* g = gpart + (size_t)j * kGradSlots * n_part + (t < 2 ? (size_t)(2 + t) * n_part : 0);
     double s = 0.0;
-    if (t < 2) {
-        for (int i = 0; i < n_part; ++i) s += g[(2 + t) * n_part + i];
-    } else {
-        for (int i = 0; i < 2 * n_part; ++i) s += g[i];
-    }
-    grad[(size_t)j * 3 + t] = s;
+    for (int i = lane; i < (t < 2 ? n_part : 2 * n_part); i += 64) s += g[i];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (lane == 0) grad[(size_t)j * 3 + t] = s;
+}
+
+// The gradient shares of a run of reverse steps (GradArgs): grid x = row
+// tiles, y = paths, z = 2 (4 s + r) + (first or second b term).  They feed
+// nothing back, so the chain of stages (k_chunk in its reverse form) keeps
+// its adjoint inputs and these launches fill the chip afterwards.
+template <int ROWS>
+__global__ __launch_bounds__(kStageThreads) void k_grad(GradArgs g) {
+    extern __shared__ double2 smem2[];
+    const int d = blockIdx.z & 1, r = (blockIdx.z >> 1) & 3, s = blockIdx.z >> 3;
+    StageArgs a = g.s;
+    a.p = 2 * s + (r == 0 ? 0 : (r == 3 ? 2 : 1));
+    a.z = g.z[a.p];
+    a.deriv = d + 1;
+    a.gslot = d;
+    a.model = d == 0;
+    a.u_in = g.us[r] - (size_t)s * g.ustep[r];
+    a.dv = g.mu + (size_t)(4 * s + r) * g.v;
+    a.grad += (size_t)(g.q0 - 4 * s + r) * gridDim.x;
+    stage_entry<1, ROWS, false>(a, reinterpret_cast<char*>(smem2));
 }
 
 __global__ void k_chunk_counter(int* chunk, int reset) {
@@ -1591,7 +1638,8 @@ hipError_t stage_set_smem_limit(int, int bytes) {
         (const void*)k_stage<R, true, true>, (const void*)k_stage<R, true, false>,
 #define WPCCC_FN_GG(R) (const void*)k_stage<R, false, true, true>, (const void*)k_stage<R, true, true, true>,
     const void* fns[] = {WPCCC_STAGE_ROWS(WPCCC_FN_PAIR) WPCCC_STAGE_ROWS_GG(WPCCC_FN_GG)(const void*)k_apply<kRowsPerBlock>,
-                         (const void*)k_apply<kApplyRowsLarge>, (const void*)k_apply<4, true>,
+                         (const void*)k_apply<kApplyRowsLarge>, (const void*)k_grad<kRowsPerBlock>,
+                         (const void*)k_grad<kApplyRowsLarge>, (const void*)k_apply<4, true>,
                          (const void*)k_apply<2, true>, (const void*)k_apply<1, true>};
 #undef WPCCC_FN_PAIR
 #undef WPCCC_FN_GG
@@ -1652,9 +1700,9 @@ namespace {
     X(kRadialMoments32, 1024, 2) X(kRadialMoments32, 512, 8) X(kRadialMoments32, 512, 12) X(kRadialMoments32, 512, 16) \
     X(kRadialInterp, 1024, 2) X(kRadialInterp, 512, 8) X(kRadialInterp, 512, 12) X(kRadialInterp, 512, 16)
 
-const void* chunk_fn(int form, int nt, int fp) {
+const void* chunk_fn(int form, int nt, int fp, bool adjoint = false) {
 #define WPCCC_CASE(F, T, P) \
-    if (form == F && nt == T && fp == P) return (const void*)k_chunk<F, T, P>;
+    if (form == F && nt == T && fp == P) return adjoint ? (const void*)k_chunk<F, T, P, F == kRadialMoments> : (const void*)k_chunk<F, T, P, false>;
     WPCCC_CHUNK_FORMS(WPCCC_CASE)
 #undef WPCCC_CASE
     return nullptr;
@@ -1908,10 +1956,10 @@ bool chunk_build(const Meta& m, int G, int threads, ChunkTables& t) {
 
 // Paths per launch: those whose workgroups can be resident at once (with one
 // workgroup per path nothing waits for another: any number).
-int chunk_paths(const ChunkTables& t, int form, int n_traj) {
+int chunk_paths(const ChunkTables& t, int form, int n_traj, bool adjoint) {
     if (t.G == 1) return n_traj;
     int dev = 0, n_cu = 0, per_cu = 0, coop = 0;
-    const void* f = chunk_fn(form, t.nt, t.fp);
+    const void* f = chunk_fn(form, t.nt, t.fp, adjoint);
     if (!f || hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess || !coop ||
         hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -1928,7 +1976,7 @@ int chunk_paths(const ChunkTables& t, int form, int n_traj) {
 
 hipError_t launch_chunk(const ChunkArgs& a, const ChunkTables& t, int form, hipStream_t st, const LaunchEv& ev) {
     const dim3 grid(8 * ((a.n_traj * a.G + 7) / 8)), block(t.nt);
-    const void* f = chunk_fn(form, t.nt, t.fp);
+    const void* f = chunk_fn(form, t.nt, t.fp, a.adjoint != 0);
     if (!f) return hipErrorInvalidValue;
     ChunkArgs arg = a;
     void* params[] = {&arg};
@@ -1949,11 +1997,22 @@ hipError_t chunk_set_smem_limit(int bytes) {
     hipError_t e = hipSuccess;
 #define WPCCC_CASE(F, T, P) \
     if (e == hipSuccess) \
-        e = hipFuncSetAttribute((const void*)k_chunk<F, T, P>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        e = hipFuncSetAttribute((const void*)k_chunk<F, T, P, false>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); \
+    if (e == hipSuccess && F == kRadialMoments) \
+        e = hipFuncSetAttribute((const void*)k_chunk<F, T, P, F == kRadialMoments>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     WPCCC_CHUNK_FORMS(WPCCC_CASE)
 #undef WPCCC_CASE
     if (e == hipSuccess) set_bytes = bytes;
     return e;
+}
+
+hipError_t launch_grad(const GradArgs& a, const Meta& hm, int n_traj, int n_steps, int smem, int rows, hipStream_t st,
+                       const LaunchEv& ev) {
+    const dim3 grid(stage_chunks(hm, rows), n_traj, 8 * n_steps);
+    if (rows == kRowsPerBlock) WPCCC_LAUNCH(ev, k_grad<kRowsPerBlock>, grid, dim3(kStageThreads), smem, st, a);
+    else if (rows == kApplyRowsLarge) WPCCC_LAUNCH(ev, k_grad<kApplyRowsLarge>, grid, dim3(kStageThreads), smem, st, a);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 hipError_t launch_apply(const ApplyArgs& a, int n_ops, const Meta& hm, int n_traj_launch, int smem, int rows,
@@ -1981,7 +2040,7 @@ hipError_t launch_chunk_counter(int* chunk, int reset, hipStream_t st) {
 }
 
 hipError_t launch_grad_sum(const double* gpart, int n_part, double* grad, int n_traj, hipStream_t st) {
-    hipLaunchKernelGGL(k_grad_sum, dim3(n_traj), dim3(64), 0, st, gpart, n_part, grad);
+    hipLaunchKernelGGL(k_grad_sum, dim3(n_traj), dim3(192), 0, st, gpart, n_part, grad);
     return hipGetLastError();
 }
 

@@ -169,8 +169,8 @@ struct StageArgs {
     const double2* dv;
     const double2* dv2;
     double cd1, cd2;
-    double* grad;         // [n_traj][kGradSlots][grid x] shares
-    int gslot;
+    double* grad;         // [n_traj][kGradSlots][gn] shares, at this launch's first
+    int gslot, gn;
     int model;
     const double* va;
     const double* vc;
@@ -249,6 +249,30 @@ struct ChunkArgs {
     const int* xpos;
     unsigned long long* exch;   // [n_traj][2][4][N] tagged words
     const int* epoch;
+    // the adjoint's forms (launch_chunk with adjoint set), vectors of v amplitudes:
+    //   kChunkStore    keeps state s + 1 at xs + (s + 1) v and the inputs of
+    //                  stages 2, 3, 4 of step s at us + (3 s + 0, 1, 2) v; X is
+    //                  only read
+    //   kChunkReverse  X is lambda; the points and h are those of the steps in
+    //                  reverse order; keeps the adjoint input of reverse stage
+    //                  r of step s at mu + (4 s + r - 1) v
+    int adjoint;
+    double2 *xs, *us, *mu;
+    size_t v;
+};
+constexpr int kChunkStore = 1, kChunkReverse = 2;
+
+// Gradient shares of a run of n_steps reverse steps in one launch: reverse
+// stage r of step s at point slot 2 s + (0, 1, 1, 2), with the adjoint input
+// mu + (4 s + r) v and the forward input us[r] - s ustep.
+struct GradArgs {
+    StageArgs s;
+    const double2* us[4];
+    size_t ustep[4];      // forward inputs of one step earlier lie this far before
+    const double2* mu;
+    size_t v;
+    int q0;               // share index of the run's first stage; later steps lie before it
+    double z[kChunkPoints];
 };
 
 struct SetupArgs {
@@ -455,8 +479,10 @@ hipError_t launch_chunk(const ChunkArgs& a, const ChunkTables& t, int form, hipS
 // index tables for at most G workgroups per path; false: does not fit
 bool tiles_resident(const Meta& m, int n_traj, int rows);
 bool chunk_build(const Meta& m, int G, int threads, ChunkTables& t);
+hipError_t launch_grad(const GradArgs& a, const Meta& host_meta, int n_traj, int n_steps, int smem, int rows, hipStream_t st,
+                       const LaunchEv& ev = LaunchEv{});
 // paths of one launch (all workgroups resident at once), 0: not one
-int chunk_paths(const ChunkTables& t, int form, int n_traj);
+int chunk_paths(const ChunkTables& t, int form, int n_traj, bool adjoint = false);
 hipError_t chunk_set_smem_limit(int bytes);
 // gg: the large-basis form (no angular factors in LDS)
 int stage_smem_bytes(const Meta& m, int rows = kRowsPerBlock, bool gg = false);

@@ -89,6 +89,8 @@ struct wpccc_plan_s {
     unsigned long long* d_exch = nullptr;  // [n_traj][2][4][N] tagged words of k_chunk
     int* d_epoch = nullptr;
     double* d_gpart = nullptr;  // [n_traj][kGradSlots][n_chunks] per-workgroup gradient shares (k_apply)
+    double2* d_mu = nullptr;    // adjoint by k_chunk: adjoint inputs of a run, [4 kChunkSteps][n_traj][n_pad]
+    double* d_gshare = nullptr; // and its shares, [n_traj][kGradSlots][4 kChunkSteps][n_chunks]
     StageTile* d_tiles = nullptr;  // the row tiles of every tiling in kStageRowsList, one after another
     Observables obs;               // channel codes and path groups (wpccc_observables)
     int tile_off[kNumStageRows] = {}, tile_n[kNumStageRows] = {};
@@ -135,7 +137,7 @@ void free_plan(wpccc_plan_s* p) {
     if (p->d_chunk) (void)hipFree(p->d_chunk);
     void* bufs[] = {p->d_b,    p->d_v,    p->d_flag, p->d_Frow1, p->d_G1,   p->d_PH1,  p->d_Ua,
                     p->d_Ub,   p->d_Xacc, p->d_kidx, p->d_rpow,  p->d_pbar, p->d_ph,   p->d_va,
-                    p->d_vc,   p->d_lam,  p->d_nu,   p->d_ckpt,  p->d_seg,  p->d_gpart, p->d_tiles,
+                    p->d_vc,   p->d_mu,   p->d_gshare, p->d_lam,  p->d_nu,   p->d_ckpt,  p->d_seg,  p->d_gpart, p->d_tiles,
                     p->d_fc,   p->d_ctab, p->d_exch, p->d_epoch};
     for (void* q : bufs)
         if (q) (void)hipFree(q);
@@ -288,8 +290,10 @@ int set_chunk(wpccc_plan_s* p, int G, bool* ok, hipStream_t st) {
 // Steps 0..ns-1 of the current prologue chunk (step lengths h[i]) for paths
 // [j0, j0+nj) by k_chunk, chunk_np paths per launch.  A prologue precedes
 // every call: it advances the epoch that the exchanged words are tagged with.
-int enqueue_chunk(wpccc_plan_s* p, double2* X, int j0, int nj, const double* h, int ns, hipStream_t st) {
-    ChunkArgs c{};
+int enqueue_chunk(wpccc_plan_s* p, double2* X, int j0, int nj, const double* h, int ns, hipStream_t st,
+                  const ChunkArgs* adjoint = nullptr, int np = 0) {
+    ChunkArgs c = adjoint ? *adjoint : ChunkArgs{};
+    if (!np) np = p->chunk_np;
     c.s = stage_args(p, j0, X);
     c.n_steps = ns;
     for (int i = 0; i < ns; ++i) c.h[i] = h[i];
@@ -305,9 +309,9 @@ int enqueue_chunk(wpccc_plan_s* p, double2* X, int j0, int nj, const double* h, 
     c.n_xs = p->chunk.n_xs;
     c.exch = p->d_exch;
     c.epoch = p->d_epoch;
-    for (int j = j0; j < j0 + nj; j += p->chunk_np) {
+    for (int j = j0; j < j0 + nj; j += np) {
         c.s.traj0 = j;
-        c.n_traj = std::min(p->chunk_np, j0 + nj - j);
+        c.n_traj = std::min(np, j0 + nj - j);
         const int rc = launched(launch_chunk(c, p->chunk, p->form, st, p->timer.open(kChunk)),
                                 "k_chunk");
         if (rc) return rc;
@@ -453,6 +457,7 @@ int enqueue_reverse_stage(wpccc_plan_s* p, int pt, double z, const double2* v1, 
         g.dv2 = v2;
         g.cd2 = c2;
         g.grad = p->d_gpart;
+        g.gn = stage_chunks(p->c.meta, p->apply_rows);
         g.gslot = d - 1;
         if (d == 1) {
             g.model = 1;
@@ -461,6 +466,45 @@ int enqueue_reverse_stage(wpccc_plan_s* p, int pt, double z, const double2* v1, 
         }
     }
     return launched(launch_apply(a, 3, p->c.meta, p->n_traj, p->stage_smem, p->apply_rows, p->gg, st), "k_apply");
+}
+
+// The adjoint's steps [na, nb) of zg by k_chunk in the form of `c` (or, with
+// c.adjoint 0, forward on X in place), one launch per 64-step chunk of the grid
+// they touch, backwards for kChunkReverse.  c's vectors are those of step na.
+// With `grad` (reverse) the gradient shares of each run follow; its vectors
+// are those of step na too.
+int adjoint_steps(wpccc_plan_s* p, double2* X, const double* zg, int na, int nb, ChunkArgs c, const GradArgs* grad, int np,
+                  hipStream_t st) {
+    const bool rev = c.adjoint == kChunkReverse;
+    const int c0 = na / kChunkSteps, c1 = (nb - 1) / kChunkSteps;
+    for (int k = 0; k <= c1 - c0; ++k) {
+        const int ck = rev ? c1 - k : c0 + k;
+        const int a = std::max(na, ck * kChunkSteps), b = std::min(nb, (ck + 1) * kChunkSteps), ns = b - a;
+        double pts[kChunkPoints], hs[kChunkSteps];
+        for (int i = 0; i <= ns; ++i) {
+            const int n = rev ? b - i : a + i, m = rev ? n - 1 : n;   // point i and the step after it
+            pts[2 * i] = zg[n];
+            if (i == ns) break;
+            pts[2 * i + 1] = 0.5 * (zg[m] + zg[m + 1]);
+            hs[i] = zg[m + 1] - zg[m];
+        }
+        int rc = enqueue_prologue(p, pts, 2 * ns + 1, 0, p->n_traj, st);
+        if (rc) return rc;
+        ChunkArgs r = c;
+        double2* x = X;
+        if (c.adjoint == kChunkStore) {
+            x = r.xs = c.xs + (size_t)(a - na) * c.v;
+            r.us = c.us + (size_t)3 * (a - na) * c.v;
+        }
+        if ((rc = enqueue_chunk(p, x, 0, p->n_traj, hs, ns, st, &r, np))) return rc;
+        if (!grad) continue;
+        GradArgs g = *grad;
+        for (int q = 0; q < 4; ++q) g.us[q] += (size_t)(b - 1 - na) * g.ustep[q];
+        g.q0 = 4 * (b - 1 - ck * kChunkSteps);
+        for (int i = 0; i <= 2 * ns; ++i) g.z[i] = pts[i];
+        if ((rc = launched(launch_grad(g, p->c.meta, p->n_traj, ns, p->stage_smem, p->apply_rows, st), "k_grad"))) return rc;
+    }
+    return WPCCC_OK;
 }
 
 // Capture one chunk of kChunkSteps steps for all paths on X into plan->gexec:
@@ -1470,11 +1514,38 @@ int wpccc_adjoint(wpccc_plan_t plan, const double* zgrid_host, int n_points, con
     auto xs_of = [&](int i) { return seg + (size_t)i * V; };
     auto us_of = [&](int i, int k) { return seg + (size_t)(K + 1 + 3 * i + k) * V; };
     AdjointPoints pts{zgrid_host, n_steps};
+    // Where wpccc_propagate runs k_chunk, so do both sweeps: only the chain of
+    // adjoint inputs is sequential, the gradient shares of a run of up to 64
+    // steps follow it in one launch (16 paths, N = 86, 800 steps: 49.7 ms with
+    // four launches per step and sweep, 23.7 this way).
+    const int np = plan->resident && plan->form == kRadialMoments ? chunk_paths(plan->chunk, plan->form, plan->n_traj, true) : 0;
+    const int n_share = 4 * kChunkSteps * stage_chunks(plan->c.meta, plan->apply_rows);
+    if (np > 0 && !plan->d_mu &&
+        ((rc = dev_alloc(&plan->d_mu, 4 * kChunkSteps * V, plan->bytes)) ||
+         (rc = dev_alloc(&plan->d_gshare, (size_t)plan->n_traj * kGradSlots * n_share, plan->bytes))))
+        return rc;
+    ChunkArgs keep{};
+    keep.v = V;
+    GradArgs grad{};
+    if (np > 0) {
+        grad.s = apply_args(plan, 0, 0.0, 1);
+        grad.s.grad = plan->d_gshare;
+        grad.s.gn = n_share;
+        grad.s.va = plan->d_va;
+        grad.s.vc = plan->d_vc;
+        grad.mu = plan->d_mu;
+        grad.v = V;
+    }
     // forward sweep with a checkpoint every K steps (not needed for one segment)
     if (n_ck > 1) {
         double2* xw = xs_of(0);
         WPCCC_HIP_CHECK(hipMemcpyAsync(xw, X0_dev, VB, hipMemcpyDeviceToDevice, st));
-        for (int n = 0; n < n_steps; ++n) {
+        for (int s = 0; s < n_ck && np > 0; ++s) {
+            WPCCC_HIP_CHECK(hipMemcpyAsync(plan->d_ckpt + (size_t)s * V, xw, VB, hipMemcpyDeviceToDevice, st));
+            if ((rc = adjoint_steps(plan, xw, zgrid_host, s * K, std::min((s + 1) * K, n_steps), ChunkArgs{}, nullptr, 0, st)))
+                return rc;
+        }
+        for (int n = 0; n < n_steps && np < 1; ++n) {
             if (n % K == 0)
                 WPCCC_HIP_CHECK(hipMemcpyAsync(plan->d_ckpt + (size_t)(n / K) * V, xw, VB, hipMemcpyDeviceToDevice, st));
             const int pz = pts.slot(plan, n, st, &rc);
@@ -1494,13 +1565,29 @@ int wpccc_adjoint(wpccc_plan_t plan, const double* zgrid_host, int n_points, con
     double2* nu3 = plan->d_nu + V;
     double2* nu2 = plan->d_nu + 2 * V;
     WPCCC_HIP_CHECK(hipMemcpyAsync(lam, gX_dev, VB, hipMemcpyDeviceToDevice, st));
-    WPCCC_HIP_CHECK(hipMemsetAsync(plan->d_gpart, 0,
-                                   (size_t)plan->n_traj * kGradSlots * stage_chunks(plan->c.meta, plan->apply_rows) *
-                                       sizeof(double), st));
+    double* shares = np > 0 ? plan->d_gshare : plan->d_gpart;
+    const int n_part = np > 0 ? n_share : stage_chunks(plan->c.meta, plan->apply_rows);
+    WPCCC_HIP_CHECK(hipMemsetAsync(shares, 0, (size_t)plan->n_traj * kGradSlots * n_part * sizeof(double), st));
     for (int s = n_ck - 1; s >= 0; --s) {
         const int n0 = s * K, n1 = std::min(n0 + K, n_steps);
         const void* x0 = n_ck > 1 ? (const void*)(plan->d_ckpt + (size_t)s * V) : X0_dev;
         WPCCC_HIP_CHECK(hipMemcpyAsync(xs_of(0), x0, VB, hipMemcpyDeviceToDevice, st));
+        if (np > 0) {
+            keep.adjoint = kChunkStore;
+            keep.xs = xs_of(0);
+            keep.us = us_of(0, 0);
+            if ((rc = adjoint_steps(plan, nullptr, zgrid_host, n0, n1, keep, nullptr, np, st))) return rc;
+            if (n_ck == 1 && X_dev)
+                WPCCC_HIP_CHECK(hipMemcpyAsync(X_dev, xs_of(n1 - n0), VB, hipMemcpyDeviceToDevice, st));
+            keep.adjoint = kChunkReverse;
+            keep.mu = plan->d_mu;
+            for (int r = 0; r < 4; ++r) {
+                grad.us[r] = r < 3 ? us_of(0, 2 - r) : xs_of(0);
+                grad.ustep[r] = (r < 3 ? 3 : 1) * V;
+            }
+            if ((rc = adjoint_steps(plan, lam, zgrid_host, n0, n1, keep, &grad, np, st))) return rc;
+            continue;
+        }
         for (int n = n0; n < n1; ++n) {
             const int i = n - n0;
             const int pz = pts.slot(plan, n, st, &rc);
@@ -1532,9 +1619,7 @@ int wpccc_adjoint(wpccc_plan_t plan, const double* zgrid_host, int n_points, con
             std::swap(lam, lam_next);
         }
     }
-    return launched(launch_grad_sum(plan->d_gpart, stage_chunks(plan->c.meta, plan->apply_rows), (double*)grad_dev,
-                                    plan->n_traj, st),
-                    "k_grad_sum");
+    return launched(launch_grad_sum(shares, n_part, (double*)grad_dev, plan->n_traj, st), "k_grad_sum");
 }
 
 int wpccc_plan_timing(wpccc_plan_t plan, int enable) {

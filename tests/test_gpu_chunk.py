@@ -50,3 +50,33 @@ def test_chunk_kernel_edges(n_max, l_max, n_bins):
         ob = build_basis(OSpec(*spec))
         for j in range(3):
             assert np.abs(ref[j] - propagate_one_centre(ob, b[j], v[j], zg)).max() <= 70 * 1e-13
+
+
+@pytest.mark.parametrize("n_max,l_max,n_bins,n_paths,every", [(1, 0, 2, 1, 0), (3, 2, 6, 3, 0), (3, 2, 6, 3, 7), (5, 4, 21, 2, 50),
+                                                              (10, 6, 20, 2, 0)])
+def test_adjoint_by_chunk_kernel(n_max, l_max, n_bins, n_paths, every):
+    """Both sweeps of the adjoint by the persistent kernel against one launch
+    per stage, over 130 steps (runs that end inside and at the 64-step chunks,
+    segments across them): the forward states are the same bitwise, the
+    gradients are the same sums in another order (each of their 4 x 130 x rows
+    terms rounds once: 1e-12 of the largest)."""
+    lb = W.wpccc_basis(W.BasisSpec(n_max, l_max, n_bins, 3.0, 300, 60.0, 1.0))
+    b, v = np.linspace(0.6, 4.0, n_paths), np.full(n_paths, 1.5)
+    zg = np.linspace(-4.0, 3.0, 131)
+    out = []
+    for launch in (W.WPCCC_LAUNCH_STAGES, W.WPCCC_LAUNCH_PERSISTENT):
+        plan = W.wpccc_plan_create(lb, b, v, model_a=0.5, model_c=1.2, checkpoint_every=every, stage_launch=launch)
+        X0 = torch.zeros((n_paths, plan.n_pad), dtype=torch.complex128, device="cuda")
+        X0[:, 0] = 1.0
+        gX = torch.zeros_like(X0)
+        gX[:, :plan.n_states] = torch.exp(1j * torch.arange(plan.n_states, device="cuda", dtype=torch.float64))
+        X = torch.empty_like(X0)
+        grad = torch.empty((n_paths, 3), dtype=torch.float64, device="cuda")
+        W.wpccc_adjoint(plan, zg, X0, gX, grad, X)
+        W.wpccc_adjoint(plan, zg, X0, gX, grad, X)   # a second call starts from cleared shares
+        W.wpccc_plan_status(plan)
+        torch.cuda.synchronize()
+        out.append((X.cpu().numpy(), grad.cpu().numpy()))
+    print(f"N = {plan.n_states}: {np.abs(out[0][1] - out[1][1]).max():.1e} of {np.abs(out[0][1]).max():.1e}", flush=True)
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.abs(out[0][1] - out[1][1]).max() <= 1e-12 * np.abs(out[0][1]).max()
