@@ -346,141 +346,178 @@ __global__ __launch_bounds__(1024) void k_lu_check(LUStepArgs a) {
 
 
 // M = S^{-1} H = U^{-1} L^{-1} (P H) for every matrix of the launch from the
-// factors above: the explicit form of Eq. INV, N right-hand sides.  One
-// workgroup per (matrix, block of 32 columns of H).  Column blocks are
-// independent, so a block's forward and backward substitutions run back to
-// back in one workgroup, left-looking by blocks of 32 rows: a row block
-// first subtracts its products with the finished blocks (32 x 32 tiles of
-// the factor and of the solution staged in LDS; each thread holds one row
-// and four columns), then solves its triangular diagonal block with
-// shuffles across the 32 lanes that hold the block's rows.  The solution is
-// written to M and read back by the later row blocks of the same workgroup.
-constexpr int kRhsB = 32;
+// factors above: the explicit form of Eq. INV, N right-hand sides.
+//
+// A workgroup of eight waves takes 16 columns of one matrix through both
+// substitutions, right-looking by blocks of 32 rows: solve the diagonal block,
+// then subtract its products from the rows still to come, 16 rows x 16 columns
+// per wave at a time on v_mfma_f64_16x16x4.  The factor is the A operand as it
+// lies in memory (16 consecutive rows of a column), read straight into
+// registers a tile ahead; the 16 columns stay in LDS (ONCHIP, up to kRhsRows
+// rows; beyond that in M), where one 16-byte read gives the real and imaginary
+// B operand.  In the diagonal block a lane holds one element (32 rows x two
+// columns per wave) and the solved row is broadcast by lane reads.
+//
+// The chain of 2 N such rows bounds small batches, the products large ones.
+// Column blocks of 32 staged in LDS and solved with vector FMAs, one launch
+// -> this one: N = 442, 16 matrices: 1.86 -> 0.62 ms; N = 115, ten matrices:
+// 223 -> 58 us.
+constexpr int kRhsB = 32;          // rows of a block
+constexpr int kRhsC = 16;          // columns of a workgroup
+constexpr int kRhsThreads = 512;
+constexpr int kRhsRows = 544;      // 16 columns of as many rows fit the LDS beside the diagonal block
 
-__global__ __launch_bounds__(256) void k_lu_rhs(RhsArgs a) {
-    __shared__ double2 ft[kRhsB][kRhsB + 1];  // factor tile [row][k]
-    __shared__ double2 yt[kRhsB][kRhsB + 1];  // right-hand-side / solution tile [row][column]
-    const int N = a.N, t = threadIdx.x, r = t & 31, cq = (t >> 5) * 4;
+__device__ inline double lane_read(double x, int lane) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                            __builtin_amdgcn_readlane(__double2loint(x), lane));
+}
+
+template <bool ONCHIP>
+__global__ __launch_bounds__(kRhsThreads) void k_lu_rhs(RhsArgs a, int n_jobs) {
+    extern __shared__ double2 rhs_lds[];
+    double2* ft = rhs_lds;                    // [k][row] diagonal block of the factors
+    double2* Y = rhs_lds + kRhsB * kRhsB;     // ONCHIP: [row][column]
+    const int N = a.N, t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    // the column blocks of a matrix on one XCD, whose L2 then holds its factors
+    const int n_cb = (N + kRhsC - 1) / kRhsC, total = n_cb * n_jobs, per = (total + 7) / 8;
+    const int W = (blockIdx.x % 8) * per + blockIdx.x / 8;
+    if (W >= total) return;
+    const int job = W / n_cb;
     int pl, slot;
-    job_of(a.jobs, blockIdx.y, pl, slot);
+    job_of(a.jobs, job, pl, slot);
     const size_t ms = (size_t)pl * kSlots2C + slot, NN = (size_t)N * N;
     const double2* LU = a.LU + ms * NN;
+    const double2* H = a.H + ms * NN;
     const int* perm = a.perm + ms * N;
     double2* M = a.M + ms * NN;
-    const int c0 = blockIdx.x * kRhsB, nc = min(kRhsB, N - c0), nb = (N + kRhsB - 1) / kRhsB;
-    const double2 zero = make_double2(0.0, 0.0);
-    double2 acc[4];
-    // rows [rb0, rb0 + 32) x columns [c0, c0 + 32) of a row-major matrix (row
-    // i of the tile taken from row rows[rb0 + i] when rows is given), zero-padded
-    auto load_rows = [&](const double2* src, const int* rows, int rb0) {
-        for (int e = t; e < kRhsB * kRhsB; e += 256) {
-            const int i = e >> 5, c = e & 31, row = rb0 + i;
-            double2 v = zero;
-            if (row < N && c < nc) v = src[(size_t)(rows ? rows[row] : row) * N + c0 + c];
-            yt[i][c] = v;
-        }
+    const int c0 = (W - job * n_cb) * kRhsC, nc = min(kRhsC, N - c0), nb = (N + kRhsB - 1) / kRhsB;
+    auto get = [&](int row, int col) {
+        if (ONCHIP) return Y[row * kRhsC + col];
+        return row < N && col < nc ? M[(size_t)row * N + c0 + col] : make_double2(0.0, 0.0);
     };
-    // rows [rb0, rb0 + 32) x columns [kb0, kb0 + 32) of the column-major factors, zero-padded
-    auto load_factor = [&](int rb0, int kb0) {
-        for (int e = t; e < kRhsB * kRhsB; e += 256) {
-            const int i = e & 31, k = e >> 5, row = rb0 + i, col = kb0 + k;
-            ft[i][k] = (row < N && col < N) ? LU[row + (size_t)col * N] : zero;
-        }
+    auto put = [&](int row, int col, double2 v) {
+        if (ONCHIP) Y[row * kRhsC + col] = v;
+        else if (row < N && col < nc) M[(size_t)row * N + c0 + col] = v;
     };
-    auto subtract_products = [&]() {
-#pragma unroll 8
-        for (int k = 0; k < kRhsB; ++k) {
-            const double2 f = ft[r][k];
+    for (int e = t; e < nb * kRhsB * kRhsC; e += kRhsThreads) {
+        const int row = e / kRhsC, col = e % kRhsC;
+        put(row, col, row < N && col < nc ? H[(size_t)perm[row] * N + c0 + col] : make_double2(0.0, 0.0));
+    }
+    const int li = lane & 15, lk = lane >> 4;
+    // rows [row0, row0 + 16) x columns [kb0, kb0 + 32) of the factors as A operands
+    auto load_tile = [&](int row0, int kb0, double2 (&f)[8]) {
+        const int row = row0 + li;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const double2 y = yt[k][cq + q];
-                acc[q].x -= f.x * y.x - f.y * y.y;
-                acc[q].y -= f.x * y.y + f.y * y.x;
+        for (int s = 0; s < 8; ++s) {
+            const int col = kb0 + 4 * s + lk;
+            f[s] = LU[min(row, N - 1) + (size_t)min(col, N - 1) * N];
+            if (row >= N || col >= N) f[s] = make_double2(0.0, 0.0);
+        }
+    };
+    // Y[rows of tiles] -= factors x Y[block kb0], the tiles q = q0, q0 + 8, .. < q1 of 16 rows
+    auto update = [&](int q0, int q1, int kb0) {
+        int q = q0 + wave;
+        if (q >= q1) return;
+        double2 y[8];
+#pragma unroll
+        for (int s = 0; s < 8; ++s) y[s] = get(kb0 + 4 * s + lk, li);
+        double2 f[8];
+        load_tile(16 * q, kb0, f);
+        for (; q < q1; q += kRhsThreads / 64) {
+            double2 fn[8];
+            load_tile(16 * min(q + kRhsThreads / 64, q1 - 1), kb0, fn);
+            dbl4 re, im;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double2 v = get(16 * q + 4 * r + lk, li);
+                re[r] = v.x;
+                im[r] = v.y;
             }
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                re = __builtin_amdgcn_mfma_f64_16x16x4f64(-f[s].x, y[s].x, re, 0, 0, 0);
+                im = __builtin_amdgcn_mfma_f64_16x16x4f64(-f[s].x, y[s].y, im, 0, 0, 0);
+                re = __builtin_amdgcn_mfma_f64_16x16x4f64(f[s].y, y[s].y, re, 0, 0, 0);
+                im = __builtin_amdgcn_mfma_f64_16x16x4f64(-f[s].y, y[s].x, im, 0, 0, 0);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) put(16 * q + 4 * r + lk, li, make_double2(re[r], im[r]));
+#pragma unroll
+            for (int s = 0; s < 8; ++s) f[s] = fn[s];
         }
     };
-    auto take_rows = [&]() {
+    // the diagonal block's factors: two elements per thread
+    double2 dg[2];
+    auto load_diag = [&](int rb0) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q] = yt[r][cq + q];
-    };
-    auto store_rows = [&](int rb0) {
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 4; ++q) yt[r][cq + q] = acc[q];
-        __syncthreads();
-        for (int e = t; e < kRhsB * kRhsB; e += 256) {
-            const int i = e >> 5, c = e & 31, row = rb0 + i;
-            if (row < N && c < nc) M[(size_t)row * N + c0 + c] = yt[i][c];
+        for (int i = 0; i < 2; ++i) {
+            const int e = t + i * kRhsThreads, row = rb0 + e % kRhsB, col = rb0 + e / kRhsB;
+            dg[i] = row < N && col < N ? LU[row + (size_t)col * N] : make_double2(0.0, 0.0);
         }
     };
+    auto store_diag = [&]() {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) ft[t + i * kRhsThreads] = dg[i];
+    };
+    // this lane's element of a diagonal block
+    const int r = lane & 31, col = 2 * wave + (lane >> 5);
+    auto solved_row = [&](double2 v, int k) {
+        const double ax = lane_read(v.x, k), ay = lane_read(v.y, k), bx = lane_read(v.x, k + 32), by = lane_read(v.y, k + 32);
+        return lane < 32 ? make_double2(ax, ay) : make_double2(bx, by);
+    };
+    load_diag(0);
+    __syncthreads();
     // forward: L (unit diagonal) Y = P H
     for (int rb = 0; rb < nb; ++rb) {
         const int rb0 = rb * kRhsB;
+        store_diag();
         __syncthreads();
-        load_rows(a.H + ms * NN, perm, rb0);
-        __syncthreads();
-        take_rows();
-        for (int cb = 0; cb < rb; ++cb) {
-            __syncthreads();
-            load_factor(rb0, cb * kRhsB);
-            load_rows(M, nullptr, cb * kRhsB);
-            __syncthreads();
-            subtract_products();
-        }
-        __syncthreads();
-        load_factor(rb0, rb0);
-        __syncthreads();
+        if (rb + 1 < nb) load_diag(rb0 + kRhsB);
+        double2 v = get(rb0 + r, col);
+#pragma unroll 4
         for (int k = 0; k + 1 < kRhsB; ++k) {
-            const double2 f = ft[r][k];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const double yr = __shfl(acc[q].x, k, 32), yi = __shfl(acc[q].y, k, 32);
-                if (r > k) {
-                    acc[q].x -= f.x * yr - f.y * yi;
-                    acc[q].y -= f.x * yi + f.y * yr;
-                }
+            const double2 f = ft[k * kRhsB + r], y = solved_row(v, k);
+            if (r > k) {
+                v.x -= f.x * y.x - f.y * y.y;
+                v.y -= f.x * y.y + f.y * y.x;
             }
         }
-        store_rows(rb0);
+        put(rb0 + r, col, v);
+        __syncthreads();
+        update(2 * (rb + 1), 2 * nb, rb0);
+        __syncthreads();
     }
     // backward: U M = Y
+    load_diag((nb - 1) * kRhsB);
     for (int rb = nb - 1; rb >= 0; --rb) {
         const int rb0 = rb * kRhsB;
+        store_diag();
         __syncthreads();
-        load_rows(M, nullptr, rb0);
-        __syncthreads();
-        take_rows();
-        for (int cb = rb + 1; cb < nb; ++cb) {
-            __syncthreads();
-            load_factor(rb0, cb * kRhsB);
-            load_rows(M, nullptr, cb * kRhsB);
-            __syncthreads();
-            subtract_products();
-        }
-        __syncthreads();
-        load_factor(rb0, rb0);
-        __syncthreads();
-        for (int k = kRhsB - 1; k >= 0; --k) {
-            if (r == k && rb0 + k < N) {
-                const double2 d = ft[k][k];
-                const double dn = d.x * d.x + d.y * d.y;
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    acc[q] = make_double2((acc[q].x * d.x + acc[q].y * d.y) / dn,
-                                          (acc[q].y * d.x - acc[q].x * d.y) / dn);
-            }
-            const double2 f = ft[r][k];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const double yr = __shfl(acc[q].x, k, 32), yi = __shfl(acc[q].y, k, 32);
-                if (r < k) {
-                    acc[q].x -= f.x * yr - f.y * yi;
-                    acc[q].y -= f.x * yi + f.y * yr;
-                }
+        if (rb > 0) load_diag(rb0 - kRhsB);
+        double2 v = get(rb0 + r, col);
+        const double2 d = ft[r * kRhsB + r];
+        const double rdn = rb0 + r < N ? 1.0 / (d.x * d.x + d.y * d.y) : 0.0;
+        const double2 id = make_double2(d.x * rdn, -d.y * rdn);   // 1 / d
+#pragma unroll 4
+        for (int k = min(kRhsB, N - rb0) - 1; k >= 0; --k) {
+            const double2 f = ft[k * kRhsB + r];
+            if (r == k) v = cmul(v, id);
+            const double2 y = solved_row(v, k);
+            if (r < k) {
+                v.x -= f.x * y.x - f.y * y.y;
+                v.y -= f.x * y.y + f.y * y.x;
             }
         }
-        store_rows(rb0);
+        put(rb0 + r, col, v);
+        __syncthreads();
+        update(0, 2 * rb, rb0);
+        __syncthreads();
     }
+    if (ONCHIP)
+        for (int e = t; e < N * kRhsC; e += kRhsThreads) {
+            const int row = e / kRhsC, c = e % kRhsC;
+            if (c < nc) M[(size_t)row * N + c0 + c] = Y[e];
+        }
 }
 
 }  // namespace
@@ -525,7 +562,18 @@ hipError_t launch_lu_update(const LUStepArgs& a, int n_jobs, hipStream_t st, con
 }
 
 hipError_t launch_lu_rhs(const RhsArgs& a, int n_jobs, hipStream_t st, const LaunchEv& ev) {
-    WPCCC_LAUNCH(ev, k_lu_rhs, dim3((a.N + kRhsB - 1) / kRhsB, n_jobs), dim3(256), 0, st, a);
+    const int n = (a.N + kRhsC - 1) / kRhsC * n_jobs;
+    const dim3 grid(8 * ((n + 7) / 8)), block(kRhsThreads);
+    const int rows = (a.N + kRhsB - 1) / kRhsB * kRhsB, diag = kRhsB * kRhsB * (int)sizeof(double2);
+    if (rows <= kRhsRows) {
+        const int smem = diag + rows * kRhsC * (int)sizeof(double2);
+        static const hipError_t e = hipFuncSetAttribute((const void*)k_lu_rhs<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 diag + kRhsRows * kRhsC * (int)sizeof(double2));
+        if (e != hipSuccess) return e;
+        WPCCC_LAUNCH(ev, k_lu_rhs<true>, grid, block, smem, st, a, n_jobs);
+    } else {
+        WPCCC_LAUNCH(ev, k_lu_rhs<false>, grid, block, diag, st, a, n_jobs);
+    }
     return hipGetLastError();
 }
 
