@@ -23,7 +23,14 @@ constexpr int kPanelThreads = 512;
 
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 
+// Matrix y of a launch: slot `slot` of path pl (n_sub 0: the matrices lie one
+// after another, without slots).
 __device__ inline void job_of(const Jobs& J, int y, int& pl, int& slot) {
+    if (J.n_sub == 0) {
+        pl = 0;
+        slot = y;
+        return;
+    }
     pl = J.path0 + y / J.n_sub;
     slot = J.slot[y % J.n_sub];
 }
@@ -39,14 +46,38 @@ __device__ inline double2 cmul(double2 a, double2 b) {
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
+// Keeps the better of this lane's pivot candidate and that of the lane a DPP
+// control moves here: the larger magnitude, the lower row on ties (lanes
+// without a source compare with themselves).
+template <int CTRL>
+__device__ inline void better_pivot(double& m, int& i) {
+    const int lo = __double2loint(m), hi = __double2hiint(m);
+    const double om = __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false),
+                                       __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false));
+    const int oi = __builtin_amdgcn_update_dpp(i, i, CTRL, 0xf, 0xf, false);
+    if (om > m || (om == m && oi < i)) {
+        m = om;
+        i = oi;
+    }
+}
+
 // ROWS rows per thread (N - k0 <= ROWS x 512), panels of up to NB columns: the
 // panel's N - k0 rows live in registers (ROWS x NB complex values per thread).
+//
+// A column is a chain: argmax, the pivot row to everyone, reciprocal, update.
+// Each wave finds its own candidate with DPP moves and puts its row beside its
+// magnitude, so one barrier serves the choice and the row; two sets of the
+// LDS arrays, taken in turn, need no barrier between columns.  Measured at
+// N = 442, 16 matrices, per panel of 16 columns: 39 us (with shuffles, the row
+// published after the choice and three barriers) -> 30 us.
 template <int ROWS, int NB>
 __global__ __launch_bounds__(kPanelThreads) void k_lu_panel(LUStepArgs a) {
     constexpr int kPanelRows = ROWS;
-    __shared__ double2 prow[NB], xrow[NB];
-    __shared__ double redv[kPanelThreads / 64];
-    __shared__ int redi[kPanelThreads / 64];
+    constexpr int kWaves = kPanelThreads / 64;
+    __shared__ double2 cand[2][kWaves][NB], xrows[2][NB];   // the waves' candidate rows, row j
+    __shared__ double2 recip[2][kWaves];                    // reciprocals of the candidates
+    __shared__ double redv[2][kWaves];
+    __shared__ int redi[2][kWaves];
     int pl, slot;
     job_of(a.jobs, blockIdx.x, pl, slot);
     const int N = a.N, k0 = a.k0, nb = a.nb;
@@ -67,8 +98,16 @@ __global__ __launch_bounds__(kPanelThreads) void k_lu_panel(LUStepArgs a) {
         for (int c = 0; c < NB; ++c)
             v[q][c] = (i < N && c < nb) ? A[i + (size_t)(k0 + c) * N] : make_double2(0.0, 0.0);
     }
-#pragma clang loop unroll(full)
-    for (int jj = 0; jj < NB; ++jj) {
+    // Four columns per pass of a rolled loop, after which the registers rotate
+    // by four: v[.][c] holds column (c + jj0) % NB.  Sixteen columns written
+    // out are some 100 KB of code that runs once, bound by instruction fetch.
+    constexpr int U = 4;
+    static_assert(NB % U == 0, "whole passes");
+#pragma unroll 1
+    for (int jj0 = 0; jj0 < NB; jj0 += U) {
+#pragma unroll
+    for (int uu = 0; uu < U; ++uu) {
+        const int jj = jj0 + uu;
         if (jj < nb) {
         const int j = k0 + jj;
         double best = -1.0;
@@ -76,52 +115,69 @@ __global__ __launch_bounds__(kPanelThreads) void k_lu_panel(LUStepArgs a) {
 #pragma unroll
         for (int q = 0; q < kPanelRows; ++q) {
             const int i = k0 + t + kPanelThreads * q;
-            const double m = v[q][jj].x * v[q][jj].x + v[q][jj].y * v[q][jj].y;
+            const double m = v[q][uu].x * v[q][uu].x + v[q][uu].y * v[q][uu].y;
             if (i >= j && i < N && m > best) {
                 best = m;
                 bi = i;
             }
         }
-        for (int off = 32; off > 0; off >>= 1) {
-            const double ob = __shfl_xor(best, off, 64);
-            const int oi = __shfl_xor(bi, off, 64);
-            if (ob > best || (ob == best && oi < bi)) {
-                best = ob;
-                bi = oi;
-            }
+        // every lane's own reciprocal fills the waits of the argmax; the
+        // pivot's is published with its row
+        double2 own[kPanelRows];
+#pragma unroll
+        for (int q = 0; q < kPanelRows; ++q) {
+            const double2 d = v[q][uu];
+            const double dn = d.x * d.x + d.y * d.y;
+            own[q] = make_double2(d.x / dn, -d.y / dn);
         }
+        better_pivot<0x111>(best, bi);   // row_shr 1, 2, 4, 8, then row_bcast 15, 31
+        better_pivot<0x112>(best, bi);
+        better_pivot<0x114>(best, bi);
+        better_pivot<0x118>(best, bi);
+        better_pivot<0x142>(best, bi);
+        better_pivot<0x143>(best, bi);
+        best = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(best), 63),
+                                __builtin_amdgcn_readlane(__double2loint(best), 63));
+        bi = __builtin_amdgcn_readlane(bi, 63);
+        const int set = uu & 1, oj = (j - k0) % kPanelThreads, qj = (j - k0) / kPanelThreads;
         if (lane == 0) {
-            redv[wave] = best;
-            redi[wave] = bi;
+            redv[set][wave] = best;
+            redi[set][wave] = bi;
+        }
+#pragma unroll
+        for (int q = 0; q < kPanelRows; ++q) {
+            if (k0 + t + kPanelThreads * q == bi) {
+#pragma unroll
+                for (int c = 0; c < NB; ++c) cand[set][wave][c] = v[q][c];
+                recip[set][wave] = own[q];
+            }
+            if (t == oj && q == qj)
+#pragma unroll
+                for (int c = 0; c < NB; ++c) xrows[set][c] = v[q][c];
         }
         __syncthreads();
-        double pmag = redv[0];
-        int p = redi[0];
-        for (int w = 1; w < kPanelThreads / 64; ++w)
-            if (redv[w] > pmag || (redv[w] == pmag && redi[w] < p)) {
-                pmag = redv[w];
-                p = redi[w];
-            }
+        // the best of the waves' candidates: lanes w % 8 compare them, which
+        // wave it came from follows from its row
+        static_assert(kWaves == 8, "three steps over eight candidates");
+        double pmag = redv[set][lane & 7];
+        int p = redi[set][lane & 7];
+        better_pivot<0xb1>(pmag, p);     // quad_perm 1 0 3 2, 2 3 0 1, row_half_mirror
+        better_pivot<0x4e>(pmag, p);
+        better_pivot<0x141>(pmag, p);
+        pmag = __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(pmag)),
+                                __builtin_amdgcn_readfirstlane(__double2loint(pmag)));
+        p = __builtin_amdgcn_readfirstlane(p);
+        const int pw = ((p - k0) % kPanelThreads) >> 6;
+        const double2 *prow = cand[set][pw], *xrow = xrows[set];
         if (!(pmag > 0.0)) {
             // exact zero column: record, leave it (LAPACK continues the same way)
             if (t == 0) {
                 piv[j] = j;
-                if (atomicCAS(&a.flag[1], 0, a.paths[pl] + 1) == 0) a.flag[2] = j;
+                if (atomicCAS(&a.flag[1], 0, (a.paths ? a.paths[pl] : (int)blockIdx.x) + 1) == 0) a.flag[2] = j;
             }
         } else {
         if (t == 0) piv[j] = p;
-        const int oj = (j - k0) % kPanelThreads, qj = (j - k0) / kPanelThreads;
         const int op = (p - k0) % kPanelThreads, qp = (p - k0) / kPanelThreads;
-#pragma unroll
-        for (int q = 0; q < kPanelRows; ++q) {
-            if (t == op && q == qp)
-#pragma unroll
-                for (int c = 0; c < NB; ++c) prow[c] = v[q][c];
-            if (t == oj && q == qj && p != j)
-#pragma unroll
-                for (int c = 0; c < NB; ++c) xrow[c] = v[q][c];
-        }
-        __syncthreads();
         if (p != j) {
 #pragma unroll
             for (int q = 0; q < kPanelRows; ++q) {
@@ -133,27 +189,37 @@ __global__ __launch_bounds__(kPanelThreads) void k_lu_panel(LUStepArgs a) {
                     for (int c = 0; c < NB; ++c) v[q][c] = xrow[c];
             }
         }
-        const double2 d = prow[jj];
-        const double dn = d.x * d.x + d.y * d.y;
-        const double2 inv = make_double2(d.x / dn, -d.y / dn);
+        const double2 inv = recip[set][pw];
 #pragma unroll
         for (int q = 0; q < kPanelRows; ++q) {
             const int i = k0 + t + kPanelThreads * q;
             if (i > j && i < N) {
-                const double2 l = cmul(v[q][jj], inv);
-                v[q][jj] = l;
+                const double2 l = cmul(v[q][uu], inv);
+                v[q][uu] = l;
+                // columns after jj: those of this pass, then groups of four
+                // until the rotated-in finished ones
 #pragma unroll
-                for (int c = 0; c < NB; ++c) {
-                    if (c > jj) {
-                        const double2 u = prow[c];
-                        v[q][c].x -= l.x * u.x - l.y * u.y;
-                        v[q][c].y -= l.x * u.y + l.y * u.x;
-                    }
-                }
+                for (int g = 0; g < NB; g += U)
+                    if (g < NB - jj0)
+#pragma unroll
+                        for (int c = g; c < g + U; ++c)
+                            if (c > uu) {
+                                const double2 u = prow[c];
+                                v[q][c].x -= l.x * u.x - l.y * u.y;
+                                v[q][c].y -= l.x * u.y + l.y * u.x;
+                            }
             }
         }
         }
-        __syncthreads();
+        }
+    }
+#pragma unroll
+        for (int q = 0; q < kPanelRows; ++q) {
+            double2 first[U];
+#pragma unroll
+            for (int c = 0; c < U; ++c) first[c] = v[q][c];
+#pragma unroll
+            for (int c = 0; c < NB; ++c) v[q][c] = c + U < NB ? v[q][(c + U) % NB] : first[(c + U - NB) < 0 ? 0 : c + U - NB];
         }
     }
 #pragma unroll

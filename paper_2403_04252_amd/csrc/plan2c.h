@@ -115,7 +115,7 @@ __host__ __device__ inline bool overlap_mirrored(int same, int fine, int s, int 
 
 struct Jobs {
     int path0;       // first local path of the launch
-    int n_sub;       // 1 or 2 coupling positions per path
+    int n_sub;       // 1 or 2 coupling positions per path (LU kernels: 0, see job_of there)
     int slot[2];
     double z[2];
     // graph replays: z[sub] = zdev[3 * (*step + ahead) + sub] instead
@@ -253,7 +253,7 @@ struct LUStepArgs {
     double2* LU;            // [path][slot][N*N] column-major, factorised in place
     int* piv;               // [path][slot][N] LAPACK-style pivot rows (0-based)
     int* perm;              // [path][slot][N]
-    const int* paths;
+    const int* paths;       // NULL: the launch's matrices are numbered as they are
     int* flag;              // [1] first singular path + 1, [2] its pivot column
     int* skip;              // [path][slot] 1: the first nt columns factor without pivoting (k_lu_check)
     int nt;                 // N_T (k_lu_check)
