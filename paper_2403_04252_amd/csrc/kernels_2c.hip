@@ -125,9 +125,12 @@ __global__ __launch_bounds__(256) void k_2c_nodes(NodeArgs a) {
 
 // Interpolated operands of one position.  grid: x = blocks of 64 nodes,
 // y = blocks of 64 radial functions (side T, then side P), z = job.  Each wave
-// takes 16 nodes; per node its 64 lanes are 64 radial functions, so the five
-// stencil values of consecutive functions are consecutive doubles of phiT
-// (coalesced).  The interpolated f_a(r) of the 64 x 64 tile is formed once in
+// takes 16 nodes; its lanes are radial functions, so the five stencil values
+// of consecutive functions are consecutive doubles of phiT (coalesced).  The
+// gathers bound it, by their latency: with four nodes' stencils in flight and
+// two nodes at a time for tiles of up to 32 functions (131072 nodes, 16 jobs,
+// N = 60: 478 -> 332 us, of which the 1 GB written takes 210; N = 764 with
+// FP32 operands, three launches: 1.12 -> 0.89 ms each).  The interpolated f_a(r) of the 64 x 64 tile is formed once in
 // LDS and written, times the Legendre factor, to the rows of every block s
 // whose radial functions (l_a >= s) it holds, row by row with lanes over
 // nodes.  The factors Pbar_l^s of the tile's l range (one contiguous range
@@ -191,18 +194,27 @@ __global__ __launch_bounds__(256) void k_2c_interp(InterpArgs a) {
         sl[tid - 64] = l;
     }
     __syncthreads();
-    // f_a(r) of function f0 + lane at the wave's 16 nodes
-    const int fa = f0 + lane;
-    for (int kk = 0; kk < 16; ++kk) {
-        const int k = wave * 16 + kk;
-        const int j = sj[k];
-        double v = 0.0;
-        if (fa < nf && j >= 0) {
-            const double* f = phiT + (size_t)j * nf + fa;
-            v = sL[k][0] * f[0] + sL[k][1] * f[nf] + sL[k][2] * f[2 * nf] + sL[k][3] * f[3 * nf] +
-                sL[k][4] * f[4 * nf];
+    // f_a(r) at the wave's 16 nodes: a lane is a function, or, where the tile
+    // has at most 32, a function at one of two nodes; the stencils of four
+    // such nodes are loaded before the first is used
+    const bool two = fend - f0 <= 32;
+    const int per = two ? 2 : 1, lf = two ? lane & 31 : lane, sub = two ? lane >> 5 : 0, fa = f0 + lf;
+    const double* ph = phiT + min(fa, nf - 1);
+    for (int kk = 0; kk < 16; kk += 4 * per) {
+        double g[4][5];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double* f = ph + (size_t)max(sj[wave * 16 + kk + u * per + sub], 0) * nf;
+#pragma unroll
+            for (int q = 0; q < 5; ++q) g[u][q] = f[(size_t)q * nf];
         }
-        tile[lane][k] = v;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = wave * 16 + kk + u * per + sub;
+            const double v = sL[k][0] * g[u][0] + sL[k][1] * g[u][1] + sL[k][2] * g[u][2] + sL[k][3] * g[u][3] +
+                             sL[k][4] * g[u][4];
+            tile[lf][k] = (fa < nf && sj[k] >= 0) ? v : 0.0;
+        }
     }
     __syncthreads();
     // the Legendre factors over the stencil weights
