@@ -268,9 +268,11 @@ constexpr int kNodeChunk32 = 2 * kNodeChunk;
 // LDS banks with the fewest passes (pitch 40 for FP64, 48 for FP32).
 struct ContractLds {
     static constexpr int kPitch = 48, NC = kNodeChunk32;
-    float As[NC][kPitch], Bs[NC][kPitch];
-    double fl[kWFields][NC];
-    float wk[NC][kMaxK];   // weights w_k(p), formed in FP64 and stored in the product precision
+    struct Buf {
+        float As[NC][kPitch], Bs[NC][kPitch];
+        double fl[kWFields][NC];
+        float wk[NC][kMaxK];   // weights w_k(p), formed in FP64 and stored in the product precision
+    } buf[2];
 };
 
 __device__ inline int lds_swz(int node) { return 4 * ((node >> 2) & 7); }
@@ -279,14 +281,17 @@ __device__ inline int lds_swz(int node) { return 4 * ((node >> 2) & 7); }
 // mt0 .. mt0 + NA - 1 and column halves 0 .. NV - 1 (subtiles wholly outside
 // the block are left out at compile time, so the k-step loop has no
 // branches), KPW weights from kk0: FP32 products summed over the chunk in
-// FP32 MFMA accumulators, then added to the FP64 ones.
+// FP32 MFMA accumulators (begin, half 0, half 1), then added to the FP64 ones
+// (end).  K-steps go in pairs, set 0 holding the even step's operands and set
+// 1 the odd one's, the next step's read while the current step's MFMAs issue.
 template <int KPW, int NMT, int NA, int NV>
-__device__ __forceinline__ void chunk_mfma(const ContractLds& L, int mt0, int kk0, int li, int lk,
-                                           dbl4 (&acc)[KPW][NMT][2]) {
-    typedef float T;
-    constexpr int NKS = ContractLds::NC / 4;
-    T av[2][NA], bv[2][NV], w[2][KPW];
-    auto load = [&](int ks, int b) {
+struct Chunk32 {
+    static constexpr int NKS = ContractLds::NC / 4;
+    float av[2][NA], bv[2][NV], w[2][KPW];
+    flt4 c32[KPW][NA][NV];
+    int mt0, kk0, li, lk;
+
+    __device__ __forceinline__ void load(const ContractLds::Buf& L, int ks, int b) {
         const int kr = ks * 4 + lk;
         const int sw = lds_swz(kr);
 #pragma unroll
@@ -295,39 +300,39 @@ __device__ __forceinline__ void chunk_mfma(const ContractLds& L, int mt0, int kk
         for (int v = 0; v < NV; ++v) bv[b][v] = L.Bs[kr][(v * 16 + li) ^ sw];
 #pragma unroll
         for (int i = 0; i < KPW; ++i) w[b][i] = L.wk[kr][kk0 + i];
-    };
-    {
-        // FP32: k-steps in pairs, buffer 0 holding the even step and buffer 1
-        // the odd one (NKS is even), the next step's operands read while the
-        // current step's MFMAs issue
-        flt4 c32[KPW][NA][NV];
+    }
+    __device__ __forceinline__ void step(int b) {
+#pragma unroll
+        for (int i = 0; i < KPW; ++i)
+#pragma unroll
+            for (int u = 0; u < NA; ++u) {
+                const float aw = av[b][u] * w[b][i];
+#pragma unroll
+                for (int v = 0; v < NV; ++v)
+                    c32[i][u][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(aw, bv[b][v], c32[i][u][v], 0, 0, 0);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    __device__ __forceinline__ void begin(const ContractLds::Buf& L) {
 #pragma unroll
         for (int i = 0; i < KPW; ++i)
 #pragma unroll
             for (int u = 0; u < NA; ++u)
 #pragma unroll
                 for (int v = 0; v < NV; ++v) c32[i][u][v] = flt4{0.f, 0.f, 0.f, 0.f};
-        auto step = [&](int b) {
-#pragma unroll
-            for (int i = 0; i < KPW; ++i)
-#pragma unroll
-                for (int u = 0; u < NA; ++u) {
-                    const float aw = (float)av[b][u] * (float)w[b][i];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v)
-                        c32[i][u][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(aw, (float)bv[b][v], c32[i][u][v], 0, 0, 0);
-                }
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        load(0, 0);
+        load(L, 0, 0);
+    }
+    __device__ __forceinline__ void half(const ContractLds::Buf& L, int h) {
 #pragma unroll 1
-        for (int ks = 0; ks < NKS; ks += 2) {
-            load(ks + 1, 1);
+        for (int ks = h * NKS / 2; ks < (h + 1) * NKS / 2; ks += 2) {
+            load(L, ks + 1, 1);
             step(0);
-            if (ks + 2 < NKS) load(ks + 2, 0);
+            if (ks + 2 < NKS) load(L, ks + 2, 0);
             step(1);
         }
-        // chunk sums into the FP64 accumulators (register r keeps the FP32 layout)
+    }
+    // chunk sums into the FP64 accumulators (register r keeps the FP32 layout)
+    __device__ __forceinline__ void end(dbl4 (&acc)[KPW][NMT][2]) {
 #pragma unroll
         for (int i = 0; i < KPW; ++i)
 #pragma unroll
@@ -337,22 +342,18 @@ __device__ __forceinline__ void chunk_mfma(const ContractLds& L, int mt0, int kk
 #pragma unroll
                     for (int r = 0; r < 4; ++r) acc[i][u][v][r] += (double)c32[i][u][v][r];
     }
-}
+};
 
 // NA, NV: active row halves (of the wave's NMT) and column halves of the
 // tile, fixed per workgroup: subtiles wholly outside the block are left out
 // at compile time.  SPW = 2: NA = 1 for every wave, and a wave whose row
 // half lies outside the block skips its MFMAs (one branch per chunk).
 template <int KPW, int SPW, int NA, int NV>
-__device__ void contract_tile(const ContractArgs& a, int y, int piece, int s, int t, int a0, int b0, bool upper,
+__device__ __forceinline__ void contract_tile(const ContractArgs& a, int y, int piece, int s, int t, int a0, int b0, bool upper,
                               ContractLds& L) {
     typedef float T;
     constexpr int NC = kNodeChunk32;              // nodes per chunk
     constexpr int NPT = NC / 8;                   // nodes per loader thread and row
-    auto& As = L.As;
-    auto& Bs = L.Bs;
-    auto& fl = L.fl;
-    auto& wk = L.wk;
     const Meta2C& m = *a.m;
     // weights of this block (st_nw) and of this tile: all of them, or the
     // target potential alone (weight 1) above the diagonal of a block (s, s)
@@ -372,7 +373,7 @@ __device__ void contract_tile(const ContractArgs& a, int y, int piece, int s, in
     // loader roles: row (column) lr of A (B), NPT consecutive nodes from kq;
     // up to two node fields of the weights per thread (field ffi + q * 256 / NC)
     const int lr = tid >> 3, kq = (tid & 7) * NPT;
-    const bool okA = a0 + lr < nA, okB = b0 + lr < nB;
+    const bool okA = a0 + lr < nA, okB = b0 + lr < nB;   // rows past the block: nothing reads their sums
     const T* arow = reinterpret_cast<const T*>(a.AT) + ((size_t)y * m.rowsT + m.rowT_off[s] + a0 + (okA ? lr : 0)) * nn;
     const T* brow = reinterpret_cast<const T*>(a.BT) + ((size_t)y * m.rowsP + m.rowP_off[t] + b0 + (okB ? lr : 0)) * nn;
     const int ffi = tid / NC, fk = tid % NC;
@@ -405,16 +406,47 @@ __device__ void contract_tile(const ContractArgs& a, int y, int piece, int s, in
 
     T ra[NPT], rb[NPT];
     double rf[2] = {0.0, 0.0};
+    const bool vec = (nn & 3) == 0;   // 16-byte aligned rows
+    static_assert(NPT == 8, "two 16-byte loads per row");
     auto fetch = [&](int base) {
+        const bool whole = base + NC <= nact;
+        if (vec && whole) {
+            const float4* pa = reinterpret_cast<const float4*>(arow + base + kq);
+            const float4* pb = reinterpret_cast<const float4*>(brow + base + kq);
 #pragma unroll
-        for (int e = 0; e < NPT; ++e) {
-            const int p = base + kq + e;
-            ra[e] = (okA && p < nact) ? arow[p] : (T)0;
-            rb[e] = (okB && p < nact) ? brow[p] : (T)0;
+            for (int e = 0; e < 2; ++e) {
+                const float4 x = pa[e], y = pb[e];
+                ra[4 * e] = x.x, ra[4 * e + 1] = x.y, ra[4 * e + 2] = x.z, ra[4 * e + 3] = x.w;
+                rb[4 * e] = y.x, rb[4 * e + 1] = y.y, rb[4 * e + 2] = y.z, rb[4 * e + 3] = y.w;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < NPT; ++e) {
+                const int p = base + kq + e;
+                ra[e] = p < nact ? arow[p] : (T)0;
+                rb[e] = p < nact ? brow[p] : (T)0;
+            }
         }
 #pragma unroll
         for (int q = 0; q < 2; ++q)
             if (ffi + q * kFStep < kWFields) rf[q] = (base + fk < nact) ? nd[(size_t)fid[q] * nn + base + fk] : 0.0;
+    };
+    auto store = [&](ContractLds::Buf& B) {
+#pragma unroll
+        for (int e = 0; e < NPT; ++e) {
+            B.As[kq + e][lr ^ lds_swz(kq + e)] = ra[e];
+            B.Bs[kq + e][lr ^ lds_swz(kq + e)] = rb[e];
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            if (ffi + q * kFStep < kWFields) B.fl[ffi + q * kFStep][fk] = rf[q];
+    };
+    auto weights = [&](ContractLds::Buf& B) {
+#pragma unroll
+        for (int q = 0; q < kWIt; ++q)
+            if (wsel[q] >= 0)
+                B.wk[fk][ffi + q * kFStep] =
+                    B.fl[wsel[q] & 15][fk] * B.fl[(wsel[q] >> 4) & 15][fk] * B.fl[wsel[q] >> 8][fk];
     };
 
     dbl4 acc[KPW][NMT][2];
@@ -425,25 +457,36 @@ __device__ void contract_tile(const ContractArgs& a, int y, int piece, int s, in
 #pragma unroll
             for (int v = 0; v < 2; ++v) acc[i][u][v] = dbl4{0.0, 0.0, 0.0, 0.0};
 
-    if (p_begin < nact) fetch(p_begin);
-    for (int base = p_begin; base < nact; base += NC) {
-#pragma unroll
-        for (int e = 0; e < NPT; ++e) {
-            As[kq + e][lr ^ lds_swz(kq + e)] = ra[e];
-            Bs[kq + e][lr ^ lds_swz(kq + e)] = rb[e];
+    // staged as in contract_tile64: the next chunk while this one's products run
+    Chunk32<KPW, NMT, NA, NV> C;
+    C.mt0 = mt0;
+    C.kk0 = kk0;
+    C.li = li;
+    C.lk = lk;
+    if (p_begin < nact) {
+        fetch(p_begin);
+        store(L.buf[0]);
+        if (p_begin + NC < nact) fetch(p_begin + NC);
+        __syncthreads();
+        weights(L.buf[0]);
+        __syncthreads();
+    }
+    int b = 0;
+    for (int base = p_begin; base < nact; base += NC, b ^= 1) {
+        const ContractLds::Buf& B = L.buf[b];
+        const bool more = base + NC < nact;
+        if (rows_in) C.begin(B);
+        if (more) {
+            store(L.buf[b ^ 1]);
+            if (base + 2 * NC < nact) fetch(base + 2 * NC);
         }
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-            if (ffi + q * kFStep < kWFields) fl[ffi + q * kFStep][fk] = rf[q];
+        if (rows_in) C.half(B, 0);
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < kWIt; ++q)
-            if (wsel[q] >= 0)
-                wk[fk][ffi + q * kFStep] = fl[wsel[q] & 15][fk] * fl[(wsel[q] >> 4) & 15][fk] * fl[wsel[q] >> 8][fk];
-        __syncthreads();
-        // next chunk's operands in flight during this chunk's MFMA
-        if (base + NC < nact) fetch(base + NC);
-        if (rows_in) chunk_mfma<KPW, NMT, NA, NV>(L, mt0, kk0, li, lk, acc);
+        if (more) weights(L.buf[b ^ 1]);
+        if (rows_in) {
+            C.half(B, 1);
+            C.end(acc);
+        }
         __syncthreads();
     }
     double* out = a.tmol + ((size_t)y * m.n_split + piece) * m.n_tmol + m.st_off[s][t];
@@ -724,6 +767,10 @@ __device__ __forceinline__ void contract_tile64(const ContractArgs& a, int y, in
 // accumulated in FP32 over the 64 nodes of a chunk) and each chunk's partial
 // sums are added to FP64 accumulators, so the FP32 accumulation error stays
 // that of a 64-term sum whatever the number of nodes.
+// Three launches of a step of the N = 764 batch, alone: 9.2 ms for the largest,
+// 51% of the cycles in MFMA; the pass 203 -> 182 ms against staging between
+// barriers with element loads and the tile out of line (its LDS reads then
+// went through flat addresses).
 template <bool MIXED>
 __global__ __launch_bounds__(kStageThreads2C, 2) void k_2c_contract(ContractArgs a) {
     const Meta2C& m = *a.m;
