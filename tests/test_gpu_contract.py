@@ -5,7 +5,8 @@ bases, prior and dagger form), odd numbers of nodes (no 16-byte rows) and node
 ranges that end inside a chunk.
 
 S and H element-wise against the oracle within 1e-11 max|X|, the bar of the
-other coupling checks (same quadrature, other summation order)."""
+other coupling checks (same quadrature, other summation order); the FP32
+products within their 1e-5."""
 import numpy as np
 import pytest
 import torch
@@ -27,14 +28,15 @@ CASES = [
 ]
 
 
+@pytest.mark.parametrize("mixed", [False, True])
 @pytest.mark.parametrize("tspec,pspec,ql,n_eta,n_tau", CASES)
-def test_contraction_edges(tspec, pspec, ql, n_eta, n_tau):
+def test_contraction_edges(tspec, pspec, ql, n_eta, n_tau, mixed):
     tail = (4.0, 400, 40.0, 1.0)
     lt, ot = W.wpccc_basis(W.BasisSpec(*tspec, *tail)), build_basis(OSpec(*tspec, *tail))
     lp, op = (lt, ot) if pspec == tspec else (W.wpccc_basis(W.BasisSpec(*pspec, *tail)), build_basis(OSpec(*pspec, *tail)))
     b, z, v = 1.3, -0.8, 1.2
     q = W.WPCCC_Q_PRIOR if ql == Q_PRIOR else W.WPCCC_Q_DAGGER
-    plan = W.wpccc_plan_create_2c([lt], [lp], 0, [b], [v], q_lower=q, n_eta=n_eta, n_tau=n_tau)
+    plan = W.wpccc_plan_create_2c([lt], [lp], 0, [b], [v], q_lower=q, n_eta=n_eta, n_tau=n_tau, mixed=mixed)
     N, _ = W.wpccc_plan_path_info(plan, 0)
     print(f"{tspec} {pspec} {ql}: N = {N}, {n_eta} x {n_tau} nodes", flush=True)
     H = torch.empty((N, N), dtype=torch.complex128, device="cuda")
@@ -46,4 +48,4 @@ def test_contraction_edges(tspec, pspec, ql, n_eta, n_tau):
     for name, g, o in (("S", S, So), ("H", H, Ho)):
         err = np.abs(g.cpu().numpy() - o).max() / np.abs(o).max()
         print(f"  {name} {err:.1e}", flush=True)
-        assert err <= 1e-11
+        assert err <= (1e-5 if mixed else 1e-11)
