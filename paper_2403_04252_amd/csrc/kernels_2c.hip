@@ -6,7 +6,7 @@
 //                  times each potential weight, the five-point interpolation
 //                  stencils at r_A and r_B and Pbar_l^m at theta_A, theta_B
 //   k_2c_contract  the Eq. K2 integrals as dense real contractions on MFMA
-//                  (v_mfma_f64_16x16x4): for molecular |q'| = s, |q| = t,
+//                  (v_mfma_f64_4x4x4): for molecular |q'| = s, |q| = t,
 //                  T[k][a][b] = sum_p A_s[a](p) B_t[b](p) w_k(p) with
 //                  A_s[a](p) = f_a(r_A) Pbar_{l_a}^s(cos theta_A), B likewise,
 //                  w_k = omega W J_m(X) {cos, sin}((v z / 2) eta tau)

@@ -4,7 +4,8 @@
 //   k_lu_panel      the N - k0 rows of the panel in registers (one to four
 //                   rows per thread, 512 threads): per column an argmax (largest
 //                   |a|^2, ties to the lowest row), the row swap, the scaling
-//                   of L and the rank-1 update of the remaining panel columns
+//                   of L and the rank-1 update of the remaining panel columns,
+//                   behind one barrier
 //   k_lu_swap_trsm  the panel's swaps on every other column (LAPACK getrf
 //                   order) and U12 = L11^-1 A12, one thread per column
 //   k_lu_update     A22 -= L21 U12 on MFMA (v_mfma_f64_16x16x4f64), 64 x 64

@@ -76,7 +76,7 @@ struct wpccc_plan_s {
     // propagation chunks kernel by kernel (WPCCC_LAUNCH_STAGES) or as one
     // persistent k_chunk launch (WPCCC_LAUNCH_PERSISTENT)
     int launch = WPCCC_LAUNCH_STAGES;
-    bool mixed = false;       // scaled FP32 moment table (WPCCC_MIXED): per-stage launches only, no adjoint
+    bool mixed = false;       // scaled FP32 moment table (WPCCC_MIXED): no adjoint
     bool interp = false;      // F on the grid nodes, five-point interpolation (WPCCC_RADIAL_INTERP)
     // chunks by k_chunk: launch is WPCCC_LAUNCH_PERSISTENT, or the FP32-table
     // or interpolated form (which report WPCCC_LAUNCH_STAGES) took it by timing
