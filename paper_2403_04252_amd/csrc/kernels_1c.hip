@@ -848,7 +848,7 @@ __device__ void stage_entry(const StageArgs& a, char* smem) {
 // row tiles ask for registers that leave room for four workgroups per CU
 // (their LDS does), larger ones for three.
 template <int ROWS, bool F32, bool FC, bool GG = false>
-__global__ __launch_bounds__(kStageThreads, ROWS <= 4 ? 4 : 3) void k_stage(StageArgs a) {
+__global__ __launch_bounds__(GG ? kStageThreadsGG : kStageThreads, ROWS <= 4 ? 4 : 3) void k_stage(StageArgs a) {
     extern __shared__ double2 smem2[];
     // work item W of the path-major list of a.n_paths x a.nwg row tiles:
     // consecutive workgroup ids go to the eight XCDs in turn and the items of
@@ -2101,7 +2101,7 @@ hipError_t launch_slot_setup(const SetupArgs& a, const Meta& hm, hipStream_t st,
 
 hipError_t launch_stage(const StageArgs& a, const Meta& hm, int n_traj_launch, int smem, hipStream_t st, const LaunchEv& ev,
                         int rows) {
-    const dim3 grid(8 * ((n_traj_launch * a.nwg + 7) / 8)), block(kStageThreads);
+    const dim3 grid(8 * ((n_traj_launch * a.nwg + 7) / 8)), block(a.gg ? kStageThreadsGG : kStageThreads);
     StageArgs a1 = a;
     a1.n_paths = n_traj_launch;
     if (a.gg) {

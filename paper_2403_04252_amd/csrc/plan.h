@@ -15,6 +15,10 @@ constexpr int kMaxLam = 2 * kMaxL;   // largest multipole order
 constexpr int kMaxPb = (kMaxLam + 1) * (kMaxLam + 2) / 2;
 constexpr int kSlots = 3;            // couplings kept for the diagnostic entry point
 constexpr int kStageThreads = 256;
+// k_stage of the large-basis form: its phase 3 waits on L2, and the LDS leaves two
+// workgroups per CU, so more waves each (N = 2958, 8 paths: 80 us per launch with
+// 256 threads, 59 with 512)
+constexpr int kStageThreadsGG = 512;
 // dynamic LDS a stage workgroup may request: the CU's 160 KB less room for
 // the kernels' few static LDS words
 constexpr int kMaxDynLds = 160 * 1024 - 1024;
