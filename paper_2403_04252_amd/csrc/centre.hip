@@ -87,14 +87,10 @@ void model_blocks(const HostBasis& hb, double a, double c, std::vector<double>& 
     }
 }
 
-int centre_build(const HostBasis& hb, hipStream_t st, Centre& c, double model_a, double model_c, double Zp,
-                 int form) {
-    if (hb.spec.l_max > kMaxL) {
-        set_error("basis l_max %d exceeds %d", hb.spec.l_max, kMaxL);
-        return WPCCC_EINVAL;
-    }
+// Sizes and offsets of a basis (the row layouts of the moment table, the
+// angular factors and x').
+void basis_meta(const HostBasis& hb, Meta& m) {
     const int N = hb.n_states;
-    Meta& m = c.meta;
     m.l_max = hb.spec.l_max;
     m.lam_max = 2 * m.l_max;
     m.n_r = hb.n_r;
@@ -116,11 +112,6 @@ int centre_build(const HostBasis& hb, hipStream_t st, Centre& c, double model_a,
         m.xs_stride[l] = m.n_l[l] | 1;
         m.n_xs += (2 * l + 1) * m.xs_stride[l];
     }
-    std::vector<int> st_xs((size_t)N);
-    for (int l = 0; l <= m.l_max; ++l)
-        for (int q = 0; q <= 2 * l; ++q)
-            for (int n = 0; n < m.n_l[l]; ++n)
-                st_xs[(size_t)m.state_off[l] + q * m.n_l[l] + n] = m.xs_off[l] + q * m.xs_stride[l] + n;
     m.n_frow = m.n_g = m.n_chunks = m.n_cols = m.n_gcols = 0;
     for (int lp = 0; lp <= kMaxL; ++lp) {
         m.nV[lp] = m.gcols[lp] = 0;
@@ -139,6 +130,22 @@ int centre_build(const HostBasis& hb, hipStream_t st, Centre& c, double model_a,
         m.n_gcols += m.gcols[lp];
         m.n_chunks += (m.n_l[lp] + kRowsPerBlock - 1) / kRowsPerBlock;
     }
+}
+
+int centre_build(const HostBasis& hb, hipStream_t st, Centre& c, double model_a, double model_c, double Zp,
+                 int form) {
+    if (hb.spec.l_max > kMaxL) {
+        set_error("basis l_max %d exceeds %d", hb.spec.l_max, kMaxL);
+        return WPCCC_EINVAL;
+    }
+    const int N = hb.n_states;
+    Meta& m = c.meta;
+    basis_meta(hb, m);
+    std::vector<int> st_xs((size_t)N);
+    for (int l = 0; l <= m.l_max; ++l)
+        for (int q = 0; q <= 2 * l; ++q)
+            for (int n = 0; n < m.n_l[l]; ++n)
+                st_xs[(size_t)m.state_off[l] + q * m.n_l[l] + n] = m.xs_off[l] + q * m.xs_stride[l] + n;
     // Frow entries (a, b, lambda) in row layout; column lambda and G column maps
     std::vector<int> da, db, dl, col_lam;
     std::vector<int2> gcol;

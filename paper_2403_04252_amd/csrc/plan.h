@@ -410,6 +410,7 @@ enum RadialForm {
 int centre_build(const HostBasis& hb, hipStream_t st, Centre& c, double model_a = 0.0, double model_c = 0.0,
                  double Zp = 1.0, int form = kRadialMoments);
 // radial blocks va, vc of the model potential (layout of StageArgs::va, vc)
+void basis_meta(const HostBasis& hb, Meta& m);
 void model_blocks(const HostBasis& hb, double a, double c, std::vector<double>& va, std::vector<double>& vc);
 void centre_free(Centre& c);
 

@@ -871,6 +871,26 @@ int wpccc_basis_export(wpccc_basis_t basis, double* r_host, double* w_host, doub
     return WPCCC_OK;
 }
 
+int wpccc_internal_chunk_tables(wpccc_basis_t basis, int G, int threads, int* out, int cap) {
+    if (!basis || G < 1 || (threads != 512 && threads != 1024) || basis->hb.spec.l_max > kMaxL) return 0;
+    Meta m{};
+    basis_meta(basis->hb, m);
+    ChunkTables t;
+    if (!chunk_build(m, G, threads, t)) return 0;
+    std::vector<int> all = {t.G, t.nt, t.fp, t.smem, t.n_xs};
+    constexpr int kParts = 8;
+    const void* src[kParts] = {t.wgs.data(),  t.ents.data(),  t.jobs.data(), t.grps.data(),
+                               t.outs.data(), t.jlane.data(), t.gsrc.data(), t.xpos.data()};
+    const size_t len[kParts] = {t.wgs.size() * sizeof(ChunkWG), t.ents.size() * sizeof(int2), t.jobs.size() * sizeof(int4),
+                                t.grps.size() * sizeof(int2),   t.outs.size() * sizeof(int4), t.jlane.size() * sizeof(int2),
+                                t.gsrc.size() * sizeof(int),    t.xpos.size() * sizeof(int)};
+    for (int k = 0; k < kParts; ++k) all.push_back((int)(len[k] / sizeof(int)));
+    for (int k = 0; k < kParts; ++k)
+        all.insert(all.end(), static_cast<const int*>(src[k]), static_cast<const int*>(src[k]) + len[k] / sizeof(int));
+    if (out) std::copy_n(all.begin(), std::min((size_t)std::max(cap, 0), all.size()), out);
+    return (int)all.size();
+}
+
 int wpccc_basis_destroy(wpccc_basis_t basis) {
     delete basis;
     return WPCCC_OK;

@@ -40,6 +40,13 @@ struct wpccc_basis_s {
     wpccc::HostBasis hb;
 };
 
+// Index tables of k_chunk for a split of `basis` over at most G workgroups of
+// `threads` threads, flattened to ints (for checks on the host): G, threads,
+// entries per thread, LDS bytes, length of x', then the lengths (in ints) of
+// the parts wgs, ents, jobs, grps, outs, jlane, gsrc, xpos, then the parts.
+// Returns the number of ints (written up to `cap`), 0 if the split does not fit.
+extern "C" int wpccc_internal_chunk_tables(wpccc_basis_t basis, int G, int threads, int* out, int cap);
+
 #define WPCCC_HIP_CHECK(expr)                                                   \
     do {                                                                        \
         hipError_t e_ = (expr);                                                 \
