@@ -286,11 +286,28 @@ int wpccc_plan_stage_rows(wpccc_plan_t plan, int* rows);
  * amplitudes (in WPCCC_MIXED the cache holds F in FP32, one more rounding). */
 int wpccc_plan_stage_cache(wpccc_plan_t plan, int* cached);
 
-/* Launch form a one-centre plan's wpccc_propagate uses for its RK4 stages
- * (WPCCC_LAUNCH_STAGES or WPCCC_LAUNCH_PERSISTENT, as requested or as chosen
- * by timing at plan creation); WPCCC_LAUNCH_STAGES for a two-centre plan and
- * for the WPCCC_MIXED and WPCCC_RADIAL_INTERP forms. */
+/* Launch form in which an FP64 exact-R one-centre plan's wpccc_propagate runs
+ * its RK4 stages (WPCCC_LAUNCH_STAGES or WPCCC_LAUNCH_PERSISTENT, as chosen by
+ * timing at plan creation or as asked for where a split fits).  The option
+ * does not apply to two-centre plans nor to the WPCCC_MIXED and
+ * WPCCC_RADIAL_INTERP forms: WPCCC_LAUNCH_STAGES for these, whichever kernel
+ * runs.  wpccc_plan_stage_split tells that for every one-centre plan. */
 int wpccc_plan_stage_launch(wpccc_plan_t plan, int* launch);
+
+/* The split on which a one-centre plan's wpccc_propagate runs the persistent
+ * stage kernel: workgroups per path and paths per launch; 0 and 0 where it
+ * runs one launch per stage (and for a two-centre plan).  Either pointer may
+ * be NULL. */
+int wpccc_plan_stage_split(wpccc_plan_t plan, int* workgroups, int* paths);
+
+/* Sets that split, for runs whose kernels must not follow from a timing: at
+ * most `workgroups` per path (0: one launch per stage) and at most `paths`
+ * paths per launch (0: as many as can be resident).  Synchronises `stream`.
+ * Errors: WPCCC_EINVAL, WPCCC_EHIP, WPCCC_ENOMEM (the plan then runs one
+ * launch per stage), WPCCC_ENOTSUP (no such split fits, or the plan has no
+ * persistent form: two-centre, large bases, WPCCC_MIXED with WPCCC_CACHE_ON);
+ * then nothing changes. */
+int wpccc_plan_set_stage_split(wpccc_plan_t plan, int workgroups, int paths, void* stream);
 
 /* Returns the first device-side error latched since the last call (after
  * synchronising `stream`), then clears it: WPCCC_OK, WPCCC_ENUMERIC, (2C)

@@ -20,7 +20,7 @@ __all__ = [
     "wpccc_plan_path_info", "wpccc_plan_destroy", "WPCCC_Q_DAGGER", "WPCCC_Q_PRIOR",
     "wpccc_plan_status", "wpccc_couplings", "wpccc_couplings_noalloc", "wpccc_step", "wpccc_propagate",
     "wpccc_plan_timing", "wpccc_plan_kernel_time", "wpccc_adjoint", "wpccc_plan_stage_rows",
-    "wpccc_plan_stage_launch", "wpccc_plan_stage_cache", "wpccc_measure_mfma", "wpccc_zgesv_batched", "wpccc_plan_groups", "wpccc_observables", "WPCCC_SOLVE_FACTORED", "WPCCC_SOLVE_EXPLICIT", "WPCCC_LAUNCH_AUTO", "WPCCC_LAUNCH_STAGES", "WPCCC_LAUNCH_PERSISTENT",
+    "wpccc_plan_stage_launch", "wpccc_plan_stage_split", "wpccc_plan_set_stage_split", "wpccc_plan_stage_cache", "wpccc_measure_mfma", "wpccc_zgesv_batched", "wpccc_plan_groups", "wpccc_observables", "WPCCC_SOLVE_FACTORED", "WPCCC_SOLVE_EXPLICIT", "WPCCC_LAUNCH_AUTO", "WPCCC_LAUNCH_STAGES", "WPCCC_LAUNCH_PERSISTENT",
 ]
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -115,6 +115,8 @@ def load_library():
         "wpccc_adjoint": ([vp, pd, i, vp, vp, vp, vp, vp], i),
         "wpccc_plan_stage_rows": ([vp, pi], i),
         "wpccc_plan_stage_launch": ([vp, pi], i),
+        "wpccc_plan_stage_split": ([vp, pi, pi], i),
+        "wpccc_plan_set_stage_split": ([vp, i, i, vp], i),
         "wpccc_plan_stage_cache": ([vp, pi], i),
         "wpccc_plan_timing": ([vp, i], i),
         "wpccc_plan_kernel_time": ([vp, ctypes.c_char_p, pd, ctypes.POINTER(ctypes.c_longlong)], i),
@@ -259,10 +261,25 @@ def wpccc_plan_stage_rows(plan: Plan) -> int:
 
 
 def wpccc_plan_stage_launch(plan: Plan) -> int:
-    """WPCCC_LAUNCH_STAGES or WPCCC_LAUNCH_PERSISTENT: how the plan runs its RK4 stages."""
+    """WPCCC_LAUNCH_STAGES or WPCCC_LAUNCH_PERSISTENT: how an FP64 exact-R plan runs its RK4
+    stages (STAGES for every other form, see wpccc_plan_stage_split)."""
     r = ctypes.c_int()
     _check(load_library().wpccc_plan_stage_launch(plan.handle, ctypes.byref(r)))
     return r.value
+
+
+def wpccc_plan_stage_split(plan: Plan):
+    """(workgroups per path, paths per launch) of the persistent stage kernel as the plan
+    runs it; (0, 0) where it runs one launch per stage."""
+    g, n = ctypes.c_int(), ctypes.c_int()
+    _check(load_library().wpccc_plan_stage_split(plan.handle, ctypes.byref(g), ctypes.byref(n)))
+    return g.value, n.value
+
+
+def wpccc_plan_set_stage_split(plan: Plan, workgroups: int, paths: int = 0, stream=None):
+    """Run the persistent stage kernel on at most `workgroups` per path (0: one launch per
+    stage) and `paths` paths per launch (0: as many as can be resident)."""
+    _check(load_library().wpccc_plan_set_stage_split(plan.handle, int(workgroups), int(paths), _stream_ptr(stream)))
 
 
 def wpccc_plan_stage_cache(plan: Plan) -> bool:

@@ -73,14 +73,9 @@ struct wpccc_plan_s {
     bool apply_ok = true;     // k_apply's LDS fits (wpccc_adjoint is available)
     int stage_rows = kRowsPerBlock;
     int stage_smem_rows = 0;  // k_stage with stage_rows
-    // propagation chunks kernel by kernel (WPCCC_LAUNCH_STAGES) or as one
-    // persistent k_chunk launch (WPCCC_LAUNCH_PERSISTENT)
-    int launch = WPCCC_LAUNCH_STAGES;
     bool mixed = false;       // scaled FP32 moment table (WPCCC_MIXED): no adjoint
     bool interp = false;      // F on the grid nodes, five-point interpolation (WPCCC_RADIAL_INTERP)
-    // chunks by k_chunk: launch is WPCCC_LAUNCH_PERSISTENT, or the FP32-table
-    // or interpolated form (which report WPCCC_LAUNCH_STAGES) took it by timing
-    bool resident = false;
+    bool resident = false;    // propagation chunks by the persistent k_chunk, else kernel by kernel
     int form = kRadialMoments;
     ChunkTables chunk;        // the split k_chunk runs (host copy without the index arrays)
     int chunk_np = 0;         // paths per k_chunk launch
@@ -262,6 +257,7 @@ int set_chunk(wpccc_plan_s* p, int G, bool* ok, hipStream_t st) {
     }
     // launches that read the previous tables
     WPCCC_HIP_CHECK(hipStreamSynchronize(st));
+    p->resident = false;   // until the new tables are complete
     if (tot > p->ctab_cap) {
         if (p->d_ctab) (void)hipFree(p->d_ctab);
         p->d_ctab = nullptr;
@@ -724,11 +720,9 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
         // k_stage's rows (wpccc_step, graph replays, the adjoint): the fastest
         // of those timed, or the default ones where only k_chunk was
         if (!best_rows) best_rows = saved_rows;
-        p->launch = p->form == kRadialMoments ? WPCCC_LAUNCH_PERSISTENT : WPCCC_LAUNCH_STAGES;
     } else if (rc == WPCCC_OK && asked) {
         // no split of a path fits: the same amplitudes kernel by kernel
         best_rows = saved_rows;
-        p->launch = WPCCC_LAUNCH_PERSISTENT;
     }
     p->fcache = best_cache;
     p->timer.on = timing;
@@ -1228,7 +1222,46 @@ int wpccc_plan_stage_launch(wpccc_plan_t plan, int* launch) {
         set_error("wpccc_plan_stage_launch: NULL argument");
         return WPCCC_EINVAL;
     }
-    *launch = plan->p2c ? WPCCC_LAUNCH_STAGES : plan->launch;
+    *launch = !plan->p2c && plan->resident && plan->form == kRadialMoments ? WPCCC_LAUNCH_PERSISTENT : WPCCC_LAUNCH_STAGES;
+    return WPCCC_OK;
+}
+
+int wpccc_plan_stage_split(wpccc_plan_t plan, int* workgroups, int* paths) {
+    if (!plan) {
+        set_error("wpccc_plan_stage_split: NULL plan");
+        return WPCCC_EINVAL;
+    }
+    const bool on = !plan->p2c && plan->resident;
+    if (workgroups) *workgroups = on ? plan->chunk.G : 0;
+    if (paths) *paths = on ? plan->chunk_np : 0;
+    return WPCCC_OK;
+}
+
+int wpccc_plan_set_stage_split(wpccc_plan_t plan, int workgroups, int paths, void* stream) {
+    clear_error();
+    if (!plan || workgroups < 0 || paths < 0) {
+        set_error("wpccc_plan_set_stage_split: NULL plan or negative count");
+        return WPCCC_EINVAL;
+    }
+    if (plan->p2c) {
+        set_error("wpccc_plan_set_stage_split: one-centre plans only");
+        return WPCCC_ENOTSUP;
+    }
+    if (workgroups == 0) {
+        plan->resident = false;
+        return WPCCC_OK;
+    }
+    bool ok = false;
+    if (!plan->gg && !(plan->mixed && plan->cache_req == WPCCC_CACHE_ON)) {
+        const int rc = set_chunk(plan, workgroups, &ok, (hipStream_t)stream);
+        if (rc) return rc;
+    }
+    if (!ok) {
+        set_error("wpccc_plan_set_stage_split: no split into at most %d workgroups fits this plan", workgroups);
+        return WPCCC_ENOTSUP;
+    }
+    if (paths) plan->chunk_np = std::min(plan->chunk_np, paths);
+    plan->resident = true;
     return WPCCC_OK;
 }
 
@@ -1250,7 +1283,7 @@ int wpccc_plan_status(wpccc_plan_t plan, void* stream) {
     WPCCC_HIP_CHECK(hipStreamSynchronize(st));
     WPCCC_HIP_CHECK(hipMemsetAsync(plan->d_flag, 0, sizeof(int), st));
     if (flag & 2) {
-        set_error("a path barrier of the persistent stage kernel timed out (results are incomplete)");
+        set_error("a workgroup of the persistent stage kernel gave up waiting for another (results are incomplete)");
         return WPCCC_EHIP;
     }
     if (flag) {

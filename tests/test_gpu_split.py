@@ -1,0 +1,124 @@
+"""The persistent chunk kernel on every split of a path that a plan may take,
+whichever one timing would choose: workgroups per path, 512 and 1024 threads,
+one launch of all paths and several.  It adds the same products in the same
+order as the stage kernel, so every comparison with that is bitwise; the
+gradient shares of the adjoint are summed in another order (each of their
+4 x steps x rows terms rounds once: 1e-12 of the largest)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2403_04252_amd as W
+
+pytestmark = pytest.mark.gpu
+
+SPLITS = [1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 80, 96]
+# n_max, l_max, n_bins: N = 4, 13, 68, 155, 366, 580, 86 (l_max 8), 1868
+BASES = [(1, 0, 3), (2, 1, 2), (3, 2, 6), (5, 4, 4), (4, 3, 21), (6, 4, 20), (2, 8, 1), (8, 7, 26)]
+FORMS = {"exact": {}, "interp": dict(interp=True), "fp32": dict(mixed=True, stage_cache=W.WPCCC_CACHE_OFF)}
+
+
+def _basis(n_max, l_max, n_bins):
+    return W.wpccc_basis(W.BasisSpec(n_max, l_max, n_bins, 3.0, 300, 60.0, 1.0))
+
+
+def _run(plan, zg):
+    X = torch.zeros((plan.n_traj, plan.n_pad), dtype=torch.complex128, device="cuda")
+    X[:, 0] = 1.0
+    W.wpccc_propagate(plan, zg, X)
+    W.wpccc_plan_status(plan)
+    torch.cuda.synchronize()
+    return X.cpu().numpy()
+
+
+def _splits(plan):
+    """Every split of SPLITS that fits, set on the plan; then two of them a few paths at a time."""
+    seen = []
+    for g in SPLITS:
+        try:
+            W.wpccc_plan_set_stage_split(plan, g)
+        except W.WpcccError as e:
+            assert e.code == -6
+            continue
+        got, paths = W.wpccc_plan_stage_split(plan)
+        assert 1 <= got <= g and 1 <= paths <= plan.n_traj
+        if got in seen:
+            continue
+        seen.append(got)
+        yield got, paths
+    assert seen
+    for g, paths in ((seen[0], 1), (seen[-1], 2)):
+        W.wpccc_plan_set_stage_split(plan, g, paths)
+        assert W.wpccc_plan_stage_split(plan) == (g, min(paths, plan.n_traj))
+        yield g, paths
+
+
+@pytest.mark.parametrize("form", FORMS)
+@pytest.mark.parametrize("n_max,l_max,n_bins", BASES)
+def test_every_split_bitwise(n_max, l_max, n_bins, form):
+    zg = np.linspace(-3.0, 0.5, 68) ** 3 / 9.0   # 67 ragged steps: a full chunk and a short one
+    plan = W.wpccc_plan_create(_basis(n_max, l_max, n_bins), [0.4, 1.5, 6.0], [1.0, 2.0, 1.5], stage_rows=4,
+                               stage_launch=W.WPCCC_LAUNCH_STAGES, **FORMS[form])
+    assert W.wpccc_plan_stage_split(plan) == (0, 0)
+    ref = _run(plan, zg)
+    for g, paths in _splits(plan):
+        print(f"N = {plan.n_states}, {form}: {g} workgroups, {paths} paths a launch", flush=True)
+        assert np.array_equal(_run(plan, zg), ref), (g, paths)
+    W.wpccc_plan_set_stage_split(plan, 0)
+    assert W.wpccc_plan_stage_split(plan) == (0, 0)
+    assert np.array_equal(_run(plan, zg), ref)
+
+
+@pytest.mark.parametrize("n_max,l_max,n_bins", BASES[1:-1])
+def test_every_split_adjoint(n_max, l_max, n_bins):
+    zg = np.linspace(-3.0, 2.0, 68)
+    b = np.array([0.6, 2.0, 4.0])
+    plan = W.wpccc_plan_create(_basis(n_max, l_max, n_bins), b, 1.5, model_a=0.5, model_c=1.2, stage_rows=4,
+                               stage_launch=W.WPCCC_LAUNCH_STAGES)
+    X0 = torch.zeros((3, plan.n_pad), dtype=torch.complex128, device="cuda")
+    X0[:, 0] = 1.0
+    gX = torch.zeros_like(X0)
+    gX[:, :plan.n_states] = torch.exp(1j * torch.arange(plan.n_states, device="cuda", dtype=torch.float64))
+
+    def grads():
+        X, grad = torch.empty_like(X0), torch.empty((3, 3), dtype=torch.float64, device="cuda")
+        W.wpccc_adjoint(plan, zg, X0, gX, grad, X)
+        W.wpccc_plan_status(plan)
+        torch.cuda.synchronize()
+        return X.cpu().numpy(), grad.cpu().numpy()
+
+    X, g0 = grads()
+    for g, paths in _splits(plan):
+        print(f"adjoint, N = {plan.n_states}: {g} workgroups, {paths} paths a launch", flush=True)
+        Xc, gc = grads()
+        assert np.array_equal(Xc, X), (g, paths)
+        assert np.abs(gc - g0).max() <= 1e-12 * np.abs(g0).max(), (g, paths)
+
+
+def test_split_is_what_runs():
+    """The launch query follows the kernel: a plan that asks for the persistent
+    form of a basis no split fits reports one launch per stage, the FP32-table
+    and interpolated forms tell their split, and refusals change nothing."""
+    big = _basis(10, 7, 32)   # N = 2380
+    try:
+        plan = W.wpccc_plan_create(big, [1.0], [1.0], stage_launch=W.WPCCC_LAUNCH_PERSISTENT)
+    except W.WpcccError as e:
+        assert e.code == -6
+        plan = W.wpccc_plan_create(big, [1.0], [1.0])
+    assert W.wpccc_plan_stage_split(plan) == (0, 0)
+    assert W.wpccc_plan_stage_launch(plan) == W.WPCCC_LAUNCH_STAGES
+    with pytest.raises(W.WpcccError) as e:
+        W.wpccc_plan_set_stage_split(plan, 96)
+    assert e.value.code == -6
+    lb = _basis(3, 2, 6)
+    plan = W.wpccc_plan_create(lb, [1.0], [1.0], stage_launch=W.WPCCC_LAUNCH_PERSISTENT)
+    g, n = W.wpccc_plan_stage_split(plan)
+    assert g >= 1 and n == 1 and W.wpccc_plan_stage_launch(plan) == W.WPCCC_LAUNCH_PERSISTENT
+    plan = W.wpccc_plan_create(lb, [1.0], [1.0], interp=True)
+    W.wpccc_plan_set_stage_split(plan, 2)
+    assert W.wpccc_plan_stage_split(plan) == (2, 1) and W.wpccc_plan_stage_launch(plan) == W.WPCCC_LAUNCH_STAGES
+    plan = W.wpccc_plan_create(lb, [1.0], [1.0], mixed=True, stage_cache=W.WPCCC_CACHE_ON)
+    for bad, code in ((2, -6), (-1, -1)):
+        with pytest.raises(W.WpcccError) as e:
+            W.wpccc_plan_set_stage_split(plan, bad)
+        assert e.value.code == code and W.wpccc_plan_stage_split(plan) == (0, 0)
