@@ -283,7 +283,9 @@ int wpccc_plan_stage_rows(wpccc_plan_t plan, int* rows);
  * exact-R forms (FP64 and WPCCC_MIXED), always 1 for the
  * WPCCC_RADIAL_INTERP form and for bases whose angular factors do not fit the
  * LDS; 0 for a two-centre plan.  In FP64 both give bitwise the same
- * amplitudes (in WPCCC_MIXED the cache holds F in FP32, one more rounding). */
+ * amplitudes (in WPCCC_MIXED the cache holds F in FP32, one more rounding; a
+ * WPCCC_MIXED plan that runs the persistent kernel uses no cache in any call,
+ * one with `graph` runs one launch per stage). */
 int wpccc_plan_stage_cache(wpccc_plan_t plan, int* cached);
 
 /* Launch form in which an FP64 exact-R one-centre plan's wpccc_propagate runs
@@ -305,8 +307,9 @@ int wpccc_plan_stage_split(wpccc_plan_t plan, int* workgroups, int* paths);
  * paths per launch (0: as many as can be resident).  Synchronises `stream`.
  * Errors: WPCCC_EINVAL, WPCCC_EHIP, WPCCC_ENOMEM (the plan then runs one
  * launch per stage), WPCCC_ENOTSUP (no such split fits, or the plan has no
- * persistent form: two-centre, large bases, WPCCC_MIXED with WPCCC_CACHE_ON);
- * then nothing changes. */
+ * persistent form: two-centre, large bases, WPCCC_MIXED with WPCCC_CACHE_ON or
+ * graph); then nothing changes.  A WPCCC_MIXED plan uses no radial-integral
+ * cache afterwards. */
 int wpccc_plan_set_stage_split(wpccc_plan_t plan, int workgroups, int paths, void* stream);
 
 /* Returns the first device-side error latched since the last call (after

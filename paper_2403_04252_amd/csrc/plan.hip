@@ -231,6 +231,16 @@ int enqueue_stage(wpccc_plan_s* p, int j0, int nj, int stage, int point, int ste
     return launched(e, "k_stage");
 }
 
+// Whether the plan may run k_chunk.  With the FP32 table it forms F in FP64 at
+// every point, which is the arithmetic without the radial-integral cache (that
+// holds F in FP32): a mixed plan that runs k_chunk runs k_stage without the
+// cache too, so that propagation, single steps and remainders round alike.
+// Graph replays of a mixed plan are k_stage's, with the cache where that is
+// faster, and so are its other calls.
+bool chunk_form(const wpccc_plan_s* p) {
+    return !p->gg && !(p->mixed && (p->cache_req == WPCCC_CACHE_ON || p->use_graph));
+}
+
 // The split of a path that k_chunk runs: at most G workgroups.  *ok: it fits
 // this basis and the device (nothing is changed otherwise).
 int set_chunk(wpccc_plan_s* p, int G, bool* ok, hipStream_t st) {
@@ -663,9 +673,9 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
         }
         return r;
     };
-    float best_ms = 1e30f;
-    int best_rows = 0;
-    bool best_cache = cache_ok;
+    // fastest k_stage without [0] and with [1] the radial-integral cache
+    float stage_ms[2] = {1e30f, 1e30f};
+    int stage_rows[2] = {0, 0};
     const int saved_rows = p->stage_rows, saved_smem = p->stage_smem_rows;
     auto set_rows = [&](int rows) {
         p->stage_rows = rows;
@@ -680,13 +690,15 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
             p->fcache = cache != 0;
             float ms = 0.f;
             rc = time_it(false, &ms);
-            if (rc == WPCCC_OK && ms < best_ms) {
-                best_ms = ms;
-                best_rows = rows;
-                best_cache = cache != 0;
+            if (rc == WPCCC_OK && ms < stage_ms[cache]) {
+                stage_ms[cache] = ms;
+                stage_rows[cache] = rows;
             }
         }
     }
+    bool best_cache = stage_rows[0] || stage_rows[1] ? stage_ms[1] <= stage_ms[0] : cache_ok;
+    float best_ms = stage_ms[best_cache];
+    int best_rows = stage_rows[best_cache];
     // An explicit WPCCC_LAUNCH_PERSISTENT needs a row tiling whose workgroups
     // could be resident at once for all paths.
     bool asked = launch_req == WPCCC_LAUNCH_PERSISTENT;
@@ -697,7 +709,7 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
     // the persistent form on the splits of a path that fit
     float chunk_ms = 1e30f;
     int chunk_G = 0, last_G = 0;
-    const bool chunk_ok = !p->gg && (asked || launch_req == WPCCC_LAUNCH_AUTO) && !(p->mixed && p->cache_req == WPCCC_CACHE_ON);
+    const bool chunk_ok = (asked || launch_req == WPCCC_LAUNCH_AUTO) && chunk_form(p);
     for (int G : kTuneSplits) {
         if (!chunk_ok || rc) break;
         bool ok = false;
@@ -719,6 +731,10 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
         p->resident = ok;
         // k_stage's rows (wpccc_step, graph replays, the adjoint): the fastest
         // of those timed, or the default ones where only k_chunk was
+        if (p->mixed) {
+            best_cache = false;
+            best_rows = stage_rows[0];
+        }
         if (!best_rows) best_rows = saved_rows;
     } else if (rc == WPCCC_OK && asked) {
         // no split of a path fits: the same amplitudes kernel by kernel
@@ -1252,7 +1268,7 @@ int wpccc_plan_set_stage_split(wpccc_plan_t plan, int workgroups, int paths, voi
         return WPCCC_OK;
     }
     bool ok = false;
-    if (!plan->gg && !(plan->mixed && plan->cache_req == WPCCC_CACHE_ON)) {
+    if (chunk_form(plan)) {
         const int rc = set_chunk(plan, workgroups, &ok, (hipStream_t)stream);
         if (rc) return rc;
     }
@@ -1262,6 +1278,7 @@ int wpccc_plan_set_stage_split(wpccc_plan_t plan, int workgroups, int paths, voi
     }
     if (paths) plan->chunk_np = std::min(plan->chunk_np, paths);
     plan->resident = true;
+    if (plan->mixed) plan->fcache = false;
     return WPCCC_OK;
 }
 

@@ -122,3 +122,29 @@ def test_split_is_what_runs():
         with pytest.raises(W.WpcccError) as e:
             W.wpccc_plan_set_stage_split(plan, bad)
         assert e.value.code == code and W.wpccc_plan_stage_split(plan) == (0, 0)
+
+
+@pytest.mark.parametrize("n_max,l_max,n_bins,n_paths", [(2, 1, 3, 1), (3, 2, 8, 3), (6, 4, 20, 5)])
+def test_mixed_plan_has_one_arithmetic(n_max, l_max, n_bins, n_paths):
+    """An FP32-table plan with the default choices rounds alike in every call:
+    steps one by one, a propagation and a second one on other chunk borders;
+    the same for a graph plan, whose full chunks are replays and whose
+    remainder is not."""
+    lb = _basis(n_max, l_max, n_bins)
+    b, zg = np.linspace(0.5, 4.0, n_paths), np.arange(76) / 8.0 - 4.0   # z + h is the next grid point exactly
+    for kw in ({}, dict(graph=True)):
+        plan = W.wpccc_plan_create(lb, b, 1.5, mixed=True, **kw)
+        split, cache = W.wpccc_plan_stage_split(plan), W.wpccc_plan_stage_cache(plan)
+        print(f"N = {plan.n_states} {kw}: split {split}, cache {cache}", flush=True)
+        start = torch.zeros((n_paths, plan.n_pad), dtype=torch.complex128, device="cuda")
+        start[:, 0] = 1.0
+        whole, parts, steps = start.clone(), start.clone(), start.clone()
+        W.wpccc_propagate(plan, zg, whole)
+        W.wpccc_propagate(plan, zg[:4], parts)
+        W.wpccc_propagate(plan, zg[3:], parts)
+        for z in zg[:-1]:
+            W.wpccc_step(plan, steps, z, 0.125)
+        W.wpccc_plan_status(plan)
+        torch.cuda.synchronize()
+        assert torch.equal(whole, steps) and torch.equal(whole, parts)
+        assert not (split[0] and cache)
