@@ -938,11 +938,11 @@ __global__ __launch_bounds__(256) void k_fpoint(const Meta* __restrict__ mp_, Ta
 // number beside half a double (chunk_put, chunk_take): a reader polls the
 // data itself, so there is no barrier, no fence and no second round trip, and
 // each word is consistent by itself whatever order the words arrive in.  With
-// G = 1 x' stays in LDS.
+// G = 1 x' stays in LDS.  The wait is for workgroups of the same launch, which
+// a cooperative launch brings onto the device together; kernels of other
+// streams can hold their places up meanwhile, so it lasts as long as a queued
+// launch would (kChunkSpin) before it ends with an error.
 // ---------------------------------------------------------------------------
-
-// polls of one word group (0.1 s or more) before a workgroup gives up
-constexpr int kChunkSpin = 1 << 18;
 
 // Words [4][N] of one path and buffer: the two halves of an amplitude's
 // components tagged with the stage number.  Every word is written and read by
@@ -1291,7 +1291,7 @@ __global__ __launch_bounds__(NT) void k_chunk(ChunkArgs c) {
 #pragma unroll
                 for (int i = 0; i < FP; ++i) asm volatile("" : "+v"(entx[i]));
             if (!local && !(step == 0 && stage == 1) &&
-                !chunk_take<NT>(exch + (size_t)((tag - 1) & 1) * 4 * N, N, tag - 1, sx, c.xpos, xs, alive ? kChunkSpin : 1, tid)) {
+                !chunk_take<NT>(exch + (size_t)((tag - 1) & 1) * 4 * N, N, tag - 1, sx, c.xpos, xs, alive ? c.spin : 1, tid)) {
                 alive = false;
                 gave_up = 1;
             }

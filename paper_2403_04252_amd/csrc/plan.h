@@ -204,6 +204,9 @@ struct ApplyArgs {
 // radial functions, and exchange the stage inputs through tagged words.
 constexpr int kChunkWaves = 16;   // most waves of a workgroup of k_chunk
 constexpr int kChunkGroups = 2;   // groups of a wave's chain run side by side
+// polls of one word group before a workgroup gives up: some ten seconds (a
+// poll takes 0.5 us or more)
+constexpr int kChunkSpin = 1 << 24;
 // the tags of a chunk's stages: the prologue that precedes every k_chunk
 // launch advances the plan's epoch by this much
 constexpr int kChunkEpoch = 4 * kChunkSteps + 4;
@@ -243,6 +246,7 @@ struct ChunkArgs {
     int n_steps;
     double h[kChunkSteps];
     int n_traj, G, n_xs;
+    int spin;             // polls before a workgroup gives up waiting
     const ChunkWG* wgs;
     const int2* ents;
     const int4* jobs;

@@ -79,6 +79,7 @@ struct wpccc_plan_s {
     int form = kRadialMoments;
     ChunkTables chunk;        // the split k_chunk runs (host copy without the index arrays)
     int chunk_np = 0;         // paths per k_chunk launch
+    int spin = kChunkSpin;    // polls before a workgroup of it gives up
     char* d_ctab = nullptr;   // its index tables
     size_t ctab_off[8] = {}, ctab_cap = 0;
     unsigned long long* d_exch = nullptr;  // [n_traj][2][4][N] tagged words of k_chunk
@@ -313,6 +314,7 @@ int enqueue_chunk(wpccc_plan_s* p, double2* X, int j0, int nj, const double* h, 
     c.gsrc = reinterpret_cast<const int*>(p->d_ctab + p->ctab_off[6]);
     c.xpos = reinterpret_cast<const int*>(p->d_ctab + p->ctab_off[7]);
     c.n_xs = p->chunk.n_xs;
+    c.spin = p->spin;
     c.exch = p->d_exch;
     c.epoch = p->d_epoch;
     for (int j = j0; j < j0 + nj; j += np) {
@@ -718,7 +720,8 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
         last_G = p->chunk.G;
         float ms = 0.f;
         rc = time_it(true, &ms);
-        if (rc == WPCCC_OK && ms < chunk_ms) {
+        if (rc) break;
+        if (ms < chunk_ms) {
             chunk_ms = ms;
             chunk_G = G;
         }
@@ -1279,6 +1282,12 @@ int wpccc_plan_set_stage_split(wpccc_plan_t plan, int workgroups, int paths, voi
     if (paths) plan->chunk_np = std::min(plan->chunk_np, paths);
     plan->resident = true;
     if (plan->mixed) plan->fcache = false;
+    return WPCCC_OK;
+}
+
+int wpccc_internal_chunk_spin(wpccc_plan_t plan, int polls) {
+    if (!plan || plan->p2c) return WPCCC_EINVAL;
+    plan->spin = polls < 0 ? kChunkSpin : polls;
     return WPCCC_OK;
 }
 

@@ -47,6 +47,10 @@ struct wpccc_basis_s {
 // Returns the number of ints (written up to `cap`), 0 if the split does not fit.
 extern "C" int wpccc_internal_chunk_tables(wpccc_basis_t basis, int G, int threads, int* out, int cap);
 
+// For checks of the wait of k_chunk: polls before a workgroup gives up (below
+// 0: the default; 0: at once, where it has to wait at all).
+extern "C" int wpccc_internal_chunk_spin(wpccc_plan_t plan, int polls);
+
 #define WPCCC_HIP_CHECK(expr)                                                   \
     do {                                                                        \
         hipError_t e_ = (expr);                                                 \
