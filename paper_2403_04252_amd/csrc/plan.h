@@ -205,8 +205,9 @@ struct ApplyArgs {
 constexpr int kChunkWaves = 16;   // most waves of a workgroup of k_chunk
 constexpr int kChunkGroups = 2;   // groups of a wave's chain run side by side
 // polls of one word group before a workgroup gives up: some ten seconds (a
-// poll takes 0.5 us or more)
+// poll takes 0.5 us or more), and a fifth of a second while splits are timed
 constexpr int kChunkSpin = 1 << 24;
+constexpr int kTuneSpin = 1 << 18;
 // the tags of a chunk's stages: the prologue that precedes every k_chunk
 // launch advances the plan's epoch by this much
 constexpr int kChunkEpoch = 4 * kChunkSteps + 4;

@@ -647,6 +647,7 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
     for (int i = 0; i < kTuneSteps; ++i) hs[i] = 0.01;
     const bool timing = p->timer.on;
     p->timer.on = false;
+    p->resident = false;
     const bool direct_ok = !p->interp && !p->gg && p->cache_req != WPCCC_CACHE_ON;
     const bool cache_ok = p->cache_req != WPCCC_CACHE_OFF;
     // a warm-up pass of one step, then the fastest of kTunePasses timed passes;
@@ -709,6 +710,8 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
         for (int ci = 0; ci < n_cand; ++ci) asked = asked || tiles_resident(m, nj, cand[ci]);
     }
     // the persistent form on the splits of a path that fit
+    const int spin = p->spin;
+    p->spin = std::min(p->spin, kTuneSpin);
     float chunk_ms = 1e30f;
     int chunk_G = 0, last_G = 0;
     const bool chunk_ok = (asked || launch_req == WPCCC_LAUNCH_AUTO) && chunk_form(p);
@@ -720,7 +723,17 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
         last_G = p->chunk.G;
         float ms = 0.f;
         rc = time_it(true, &ms);
-        if (rc) break;
+        // a split whose workgroups gave up waiting (a device busy with other
+        // work) is not a candidate, nor are the finer ones, and leaves no error
+        int flag = 0;
+        hipError_t ef = rc ? hipSuccess : hipMemcpyAsync(&flag, p->d_flag, sizeof(int), hipMemcpyDeviceToHost, st);
+        if (ef == hipSuccess) ef = hipStreamSynchronize(st);
+        if (ef == hipSuccess && flag) ef = hipMemsetAsync(p->d_flag, 0, sizeof(int), st);
+        if (ef != hipSuccess) {
+            set_error("stage tuning failed: %s", hipGetErrorString(ef));
+            rc = WPCCC_EHIP;
+        }
+        if (rc || (flag & 2)) break;
         if (ms < chunk_ms) {
             chunk_ms = ms;
             chunk_G = G;
@@ -728,6 +741,7 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
         // finer splits exchange more and, past the device, take more launches
         if (ms > 1.4f * chunk_ms) break;
     }
+    p->spin = spin;
     if (rc == WPCCC_OK && chunk_G && chunk_ms < best_ms) {
         bool ok = false;
         rc = set_chunk(p, chunk_G, &ok, st);
@@ -1289,6 +1303,11 @@ int wpccc_internal_chunk_spin(wpccc_plan_t plan, int polls) {
     if (!plan || plan->p2c) return WPCCC_EINVAL;
     plan->spin = polls < 0 ? kChunkSpin : polls;
     return WPCCC_OK;
+}
+
+int wpccc_internal_tune(wpccc_plan_t plan, void* stream) {
+    if (!plan || plan->p2c || plan->gg) return WPCCC_EINVAL;
+    return tune_stage(plan, kStageRowsList, kNumStageRows, WPCCC_LAUNCH_AUTO, (hipStream_t)stream);
 }
 
 int wpccc_plan_destroy(wpccc_plan_t plan) {

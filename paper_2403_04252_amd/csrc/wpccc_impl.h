@@ -47,9 +47,11 @@ struct wpccc_basis_s {
 // Returns the number of ints (written up to `cap`), 0 if the split does not fit.
 extern "C" int wpccc_internal_chunk_tables(wpccc_basis_t basis, int G, int threads, int* out, int cap);
 
-// For checks of the wait of k_chunk: polls before a workgroup gives up (below
-// 0: the default; 0: at once, where it has to wait at all).
+// Checks of the wait of k_chunk: polls before a workgroup gives up (below 0:
+// the default; 0: at once, where it has to wait at all), and the timing of the
+// stage kernels as at plan creation, again.
 extern "C" int wpccc_internal_chunk_spin(wpccc_plan_t plan, int polls);
+extern "C" int wpccc_internal_tune(wpccc_plan_t plan, void* stream);
 
 #define WPCCC_HIP_CHECK(expr)                                                   \
     do {                                                                        \

@@ -29,6 +29,12 @@ def _spin(plan, polls):
     assert f(plan.handle, polls) == 0
 
 
+def _tune(plan):
+    f = W.load_library().wpccc_internal_tune
+    f.argtypes, f.restype = [ctypes.c_void_p, ctypes.c_void_p], ctypes.c_int
+    assert f(plan.handle, ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+
+
 @pytest.fixture(scope="module")
 def n580():
     return _basis(6, 4, 20)
@@ -51,6 +57,26 @@ def test_give_up_is_reported_once(n580):
     assert torch.equal(X, _start(plan))
     W.wpccc_plan_status(plan)   # read once
     _spin(plan, -1)
+    W.wpccc_propagate(plan, zg, X)
+    W.wpccc_plan_status(plan)
+    assert torch.equal(X, ref)
+
+
+def test_tuning_leaves_no_error(n580):
+    """Splits whose workgroups gave up while they were timed are not chosen and
+    leave no error on the plan."""
+    zg = np.linspace(-3.0, 0.0, 71)
+    plan = W.wpccc_plan_create(n580, [0.5, 2.0, 5.0], 1.5)
+    _spin(plan, 0)
+    _tune(plan)
+    assert W.wpccc_plan_stage_split(plan)[0] <= 1
+    W.wpccc_plan_status(plan)
+    ref = _start(plan)
+    W.wpccc_propagate(plan, zg, ref)
+    W.wpccc_plan_status(plan)
+    _spin(plan, -1)
+    _tune(plan)
+    X = _start(plan)
     W.wpccc_propagate(plan, zg, X)
     W.wpccc_plan_status(plan)
     assert torch.equal(X, ref)
