@@ -180,7 +180,9 @@ typedef struct {
                        creation when the row tiles of all paths could not be
                        resident at once; a basis that no split fits runs
                        kernel by kernel).
-                       Both forms give bitwise the same amplitudes. */
+                       Both forms give bitwise the same amplitudes.  A call
+                       captured into a graph of the caller's runs one launch
+                       per stage where workgroups would wait for each other. */
     int radial;     /* 1C: how the radial integrals F of Eq. D2 are evaluated at R:
                        WPCCC_RADIAL_EXACT (default): the r-grid quadrature at the
                        exact R, from prefix/suffix moment tables;

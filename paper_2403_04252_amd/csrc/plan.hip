@@ -294,6 +294,17 @@ int set_chunk(wpccc_plan_s* p, int G, bool* ok, hipStream_t st) {
     return WPCCC_OK;
 }
 
+// Whether a call on `st` runs k_chunk.  Not into a caller's graph if its
+// workgroups wait for each other: what a replay of it guarantees about their
+// residency, beside replays of other graphs, is not known.  k_stage gives the
+// same amplitudes bitwise.
+bool runs_chunk(const wpccc_plan_s* p, hipStream_t st) {
+    if (!p->resident) return false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (p->chunk.G > 1 && hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
+    return cs == hipStreamCaptureStatusNone;
+}
+
 // Steps 0..ns-1 of the current prologue chunk (step lengths h[i]) for paths
 // [j0, j0+nj) by k_chunk, chunk_np paths per launch.  A prologue precedes
 // every call: it advances the epoch that the exchanged words are tagged with.
@@ -1510,6 +1521,7 @@ int wpccc_propagate(wpccc_plan_t plan, const double* zgrid_host, int n_points, v
         }
     double2* X = (double2*)X_dev;
     const int chunk = plan->batched ? plan->n_traj : 1;
+    const bool resident = runs_chunk(plan, st);
     int first = 0;  // first grid point of the kernel-by-kernel part
     if (plan->use_graph && plan->batched && (n_points - 1) >= kChunkSteps) {
         const int n_full = (n_points - 1) / kChunkSteps;
@@ -1530,7 +1542,7 @@ int wpccc_propagate(wpccc_plan_t plan, const double* zgrid_host, int n_points, v
             if ((rc = enqueue_prologue(plan, pts, 2 * ns + 1, j0, nj, st))) return rc;
             double hs[kChunkSteps];
             for (int i = 0; i < ns; ++i) hs[i] = zgrid_host[c0 + i + 1] - zgrid_host[c0 + i];
-            if (plan->resident) {
+            if (resident) {
                 if ((rc = enqueue_chunk(plan, X, j0, nj, hs, ns, st))) return rc;
                 continue;
             }
@@ -1616,7 +1628,7 @@ int wpccc_adjoint(wpccc_plan_t plan, const double* zgrid_host, int n_points, con
     // adjoint inputs is sequential, the gradient shares of a run of up to 64
     // steps follow it in one launch (16 paths, N = 86, 800 steps: 49.7 ms with
     // four launches per step and sweep, 23.7 this way).
-    const int np = plan->resident && plan->form == kRadialMoments ? chunk_paths(plan->chunk, plan->form, plan->n_traj, true) : 0;
+    const int np = plan->form == kRadialMoments && runs_chunk(plan, st) ? chunk_paths(plan->chunk, plan->form, plan->n_traj, true) : 0;
     const int n_share = 4 * kChunkSteps * stage_chunks(plan->c.meta, plan->apply_rows);
     if (np > 0 && !plan->d_mu &&
         ((rc = dev_alloc(&plan->d_mu, 4 * kChunkSteps * V, plan->bytes)) ||

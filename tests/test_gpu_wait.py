@@ -141,3 +141,48 @@ def test_beside_a_full_device(n580):
     W.wpccc_plan_status(plan)
     W.wpccc_plan_status(many)
     assert torch.equal(X, ref) and torch.isfinite(XM.abs()).all()
+
+
+def test_captured_calls_do_not_wait(n580):
+    """A propagation and an adjoint captured into the caller's graphs, replayed
+    on two streams beside each other: no workgroup of them waits for another
+    (with a limit of no polls any wait would be an error), and every replay
+    gives the eager amplitudes bitwise."""
+    zg = np.linspace(-3.0, 0.0, 71)
+    plans, refs, graphs, outs, streams = [], [], [], [], []
+    for n in (3, 5):
+        plan = W.wpccc_plan_create(n580, np.linspace(0.5, 5.0, n), 1.5, model_a=0.4, model_c=1.1, stage_rows=8,
+                                   stage_launch=W.WPCCC_LAUNCH_STAGES)
+        W.wpccc_plan_set_stage_split(plan, 8)
+        ref, Xa, grad = _start(plan), torch.empty_like(_start(plan)), torch.empty((n, 3), dtype=torch.float64, device="cuda")
+        gX = _start(plan)
+        W.wpccc_propagate(plan, zg, ref)
+        W.wpccc_adjoint(plan, zg, _start(plan), gX, grad, Xa)   # allocates its workspace
+        W.wpccc_plan_status(plan)
+        assert torch.equal(Xa, ref)
+        _spin(plan, 0)
+        X0, X = _start(plan), _start(plan)
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            W.wpccc_propagate(plan, zg, X)
+            W.wpccc_adjoint(plan, zg, X0, gX, grad, Xa)
+        plans.append(plan)
+        refs.append(ref)
+        graphs.append(graph)
+        outs.append((X, Xa, grad, X0, gX))
+        streams.append(torch.cuda.Stream())
+    for rep in range(4):
+        for X, Xa, grad, _, _ in outs:
+            X.zero_()
+            X[:, 0] = 1.0
+            Xa.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for graph, stream in zip(graphs, streams):
+            with torch.cuda.stream(stream):
+                graph.replay()
+        torch.cuda.synchronize()
+        for plan, ref, (X, Xa, grad, _, _) in zip(plans, refs, outs):
+            W.wpccc_plan_status(plan)
+            assert torch.equal(X, ref) and torch.equal(Xa, ref), rep
+            assert torch.isfinite(grad).all()
