@@ -378,7 +378,11 @@ int wpccc_propagate(wpccc_plan_t plan, const double* zgrid_host, int n_points,
  *   X_dev     complex [n_traj][n_pad], final amplitudes (written; may be NULL)
  *   gX_dev    complex [n_traj][n_pad], dL/d conj(X) at the last point (read)
  *   grad_dev  double  [n_traj][3], per path dL/da, dL/dc, dL/db (written)
- * Device memory for the checkpoints is allocated by the first call.  Errors:
+ * Device memory is allocated by the first call: the checkpoints, four vectors
+ * [n_traj][n_pad] per step between them and, where the persistent kernel takes
+ * the sweeps (it does not where that memory is not to be had), four more per
+ * step of up to 64 and 16 doubles per row tile, path and step of up to 64 of
+ * the grid.  Errors:
  * WPCCC_EINVAL (grid as wpccc_propagate), WPCCC_ENOTSUP (two-centre plan, a
  * WPCCC_MIXED or WPCCC_RADIAL_INTERP plan, or a basis whose operator kernel does not fit the LDS:
  * it takes 8 rows per workgroup, 4 where 8 do not fit, and 4, 2 or 1 with the

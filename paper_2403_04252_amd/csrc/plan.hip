@@ -85,8 +85,9 @@ struct wpccc_plan_s {
     unsigned long long* d_exch = nullptr;  // [n_traj][2][4][N] tagged words of k_chunk
     int* d_epoch = nullptr;
     double* d_gpart = nullptr;  // [n_traj][kGradSlots][n_chunks] per-workgroup gradient shares (k_apply)
-    double2* d_mu = nullptr;    // adjoint by k_chunk: adjoint inputs of a run, [4 kChunkSteps][n_traj][n_pad]
-    double* d_gshare = nullptr; // and its shares, [n_traj][kGradSlots][4 kChunkSteps][n_chunks]
+    double2* d_mu = nullptr;    // adjoint by k_chunk: adjoint inputs of a run, [4 adj_run][n_traj][n_pad]
+    double* d_gshare = nullptr; // and the shares of a chunk's steps, [n_traj][kGradSlots][4 adj_share][n_chunks]
+    int adj_run = 0, adj_share = 0;  // steps that they hold
     StageTile* d_tiles = nullptr;  // the row tiles of every tiling in kStageRowsList, one after another
     Observables obs;               // channel codes and path groups (wpccc_observables)
     int tile_off[kNumStageRows] = {}, tile_n[kNumStageRows] = {};
@@ -487,11 +488,48 @@ int enqueue_reverse_stage(wpccc_plan_s* p, int pt, double z, const double2* v1, 
     return launched(launch_apply(a, 3, p->c.meta, p->n_traj, p->stage_smem, p->apply_rows, p->gg, st), "k_apply");
 }
 
+// Workspace of the adjoint by k_chunk: inputs for runs of up to `run` steps (a
+// run ends with its chunk and its segment, so it is no longer than the steps
+// between checkpoints) and shares for `share` steps of a chunk.  Without the
+// memory for it *np becomes 0: the sweeps then go kernel by kernel.
+int adjoint_runs(wpccc_plan_s* p, int run, int share, hipStream_t st, int* np) {
+    if (run <= p->adj_run && share <= p->adj_share) return WPCCC_OK;
+    (void)hipStreamSynchronize(st);
+    const size_t mu = 4 * (size_t)p->n_traj * p->n_pad;
+    const size_t gs = (size_t)p->n_traj * kGradSlots * 4 * stage_chunks(p->c.meta, p->apply_rows);
+    run = std::max(run, p->adj_run);
+    share = std::max(share, p->adj_share);
+    auto release = [&]() {
+        if (p->d_mu) (void)hipFree(p->d_mu);
+        if (p->d_gshare) (void)hipFree(p->d_gshare);
+        p->d_mu = nullptr;
+        p->d_gshare = nullptr;
+        p->bytes -= (long long)(p->adj_run * mu * sizeof(double2) + p->adj_share * gs * sizeof(double));
+        p->adj_run = p->adj_share = 0;
+    };
+    release();
+    long long tot = 0;
+    int rc = dev_alloc(&p->d_mu, run * mu, tot);
+    if (!rc) rc = dev_alloc(&p->d_gshare, share * gs, tot);
+    if (rc) {
+        release();
+        *np = 0;
+        if (rc != WPCCC_ENOMEM) return rc;
+        clear_error();
+        return WPCCC_OK;
+    }
+    p->bytes += tot;
+    p->adj_run = run;
+    p->adj_share = share;
+    return WPCCC_OK;
+}
+
 // The adjoint's steps [na, nb) of zg by k_chunk in the form of `c` (or, with
 // c.adjoint 0, forward on X in place), one launch per 64-step chunk of the grid
 // they touch, backwards for kChunkReverse.  c's vectors are those of step na.
 // With `grad` (reverse) the gradient shares of each run follow; its vectors
-// are those of step na too.
+// are those of step na too.  A step's shares go to the slots of its place in
+// the chunk, so that the order of their sum does not depend on the segments.
 int adjoint_steps(wpccc_plan_s* p, double2* X, const double* zg, int na, int nb, ChunkArgs c, const GradArgs* grad, int np,
                   hipStream_t st) {
     const bool rev = c.adjoint == kChunkReverse;
@@ -1628,12 +1666,9 @@ int wpccc_adjoint(wpccc_plan_t plan, const double* zgrid_host, int n_points, con
     // adjoint inputs is sequential, the gradient shares of a run of up to 64
     // steps follow it in one launch (16 paths, N = 86, 800 steps: 49.7 ms with
     // four launches per step and sweep, 23.7 this way).
-    const int np = plan->form == kRadialMoments && runs_chunk(plan, st) ? chunk_paths(plan->chunk, plan->form, plan->n_traj, true) : 0;
-    const int n_share = 4 * kChunkSteps * stage_chunks(plan->c.meta, plan->apply_rows);
-    if (np > 0 && !plan->d_mu &&
-        ((rc = dev_alloc(&plan->d_mu, 4 * kChunkSteps * V, plan->bytes)) ||
-         (rc = dev_alloc(&plan->d_gshare, (size_t)plan->n_traj * kGradSlots * n_share, plan->bytes))))
-        return rc;
+    int np = plan->form == kRadialMoments && runs_chunk(plan, st) ? chunk_paths(plan->chunk, plan->form, plan->n_traj, true) : 0;
+    if (np > 0 && (rc = adjoint_runs(plan, std::min(K, kChunkSteps), std::min(n_steps, kChunkSteps), st, &np))) return rc;
+    const int n_share = 4 * plan->adj_share * stage_chunks(plan->c.meta, plan->apply_rows);
     ChunkArgs keep{};
     keep.v = V;
     GradArgs grad{};

@@ -148,3 +148,67 @@ def test_mixed_plan_has_one_arithmetic(n_max, l_max, n_bins, n_paths):
         torch.cuda.synchronize()
         assert torch.equal(whole, steps) and torch.equal(whole, parts)
         assert not (split[0] and cache)
+
+
+def _adjoint(plan, zg):
+    n = plan.n_traj
+    X0 = torch.zeros((n, plan.n_pad), dtype=torch.complex128, device="cuda")
+    X0[:, 0] = 1.0
+    gX = torch.zeros_like(X0)
+    gX[:, :plan.n_states] = torch.exp(1j * torch.arange(plan.n_states, device="cuda", dtype=torch.float64))
+    X, grad = torch.empty_like(X0), torch.empty((n, 3), dtype=torch.float64, device="cuda")
+    W.wpccc_adjoint(plan, zg, X0, gX, grad, X)
+    W.wpccc_plan_status(plan)
+    return X, grad
+
+
+@pytest.mark.parametrize("every", [1, 5, 64, 70])
+def test_adjoint_memory_follows_checkpoints(every):
+    """What the adjoint by the persistent kernel holds beside the segments:
+    four vectors per step of a run, which is no longer than the steps between
+    checkpoints, and the 16 shares of each row tile and path for a chunk's
+    steps; gradients as kernel by kernel (the bar above), also after a call on
+    a longer grid grew the workspace."""
+    lb, zg = _basis(3, 2, 8), np.linspace(-4.0, 4.0, 141)
+    b = np.linspace(0.6, 4.0, 16)
+    plan = W.wpccc_plan_create(lb, b, 1.5, model_a=0.5, model_c=1.2, checkpoint_every=every, stage_rows=4,
+                               stage_launch=W.WPCCC_LAUNCH_STAGES)
+    Xs, gs = _adjoint(plan, zg)
+    held = W.wpccc_plan_info(plan)[3]
+    W.wpccc_plan_set_stage_split(plan, 2)
+    tables = W.wpccc_plan_info(plan)[3] - held
+    for steps in (every, 140):   # one segment, then all
+        X, g = _adjoint(plan, zg[:steps + 1])
+    assert torch.equal(X, Xs) and (g - gs).abs().max() <= 1e-12 * gs.abs().max()
+    grown = W.wpccc_plan_info(plan)[3] - held - tables
+    tiles = sum((n + 7) // 8 for n in (11, 10, 9))
+    assert grown <= 16 * plan.n_traj * plan.n_pad * 4 * min(every, 64) + 8 * plan.n_traj * 16 * 64 * tiles
+
+
+def test_adjoint_without_memory_for_runs():
+    """Where the device has room for the segments but not for the persistent
+    kernel's runs, the sweeps go kernel by kernel, in this call and the next."""
+    lb, zg, n = _basis(6, 4, 20), np.linspace(-1.0, 1.0, 65), 1700
+    b = np.linspace(0.6, 4.0, n)
+    make = lambda: W.wpccc_plan_create(lb, b, 1.5, model_a=0.5, model_c=1.2, checkpoint_every=64, stage_rows=8,
+                                       stage_launch=W.WPCCC_LAUNCH_STAGES)
+    ref = make()
+    Xs, gs = _adjoint(ref, zg)
+    W.wpccc_plan_set_stage_split(ref, 8)   # every kernel has run before memory gets short
+    _adjoint(ref, zg)
+    W.wpccc_plan_destroy(ref)
+    plan = make()
+    W.wpccc_plan_set_stage_split(plan, 8)
+    torch.cuda.empty_cache()
+    vector = 16 * n * plan.n_pad
+    runs, segments = 256 * vector, (4 * 64 + 1 + 2 + 3 + 1) * vector
+    free = torch.cuda.mem_get_info()[0]
+    fill = torch.empty(free - segments - runs // 2, dtype=torch.uint8, device="cuda")
+    print(f"{free >> 20} MiB free, {segments >> 20} for segments, {runs >> 20} for runs", flush=True)
+    for rep in range(2):
+        X, g = _adjoint(plan, zg)
+        assert torch.equal(X, Xs) and torch.equal(g, gs), rep
+    del fill
+    torch.cuda.empty_cache()
+    X, g = _adjoint(plan, zg)
+    assert torch.equal(X, Xs) and (g - gs).abs().max() <= 1e-12 * gs.abs().max()
