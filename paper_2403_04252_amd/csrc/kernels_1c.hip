@@ -1434,6 +1434,10 @@ __global__ __launch_bounds__(kStageThreads) void k_grad(GradArgs g) {
     stage_entry<1, ROWS, false>(a, reinterpret_cast<char*>(smem2));
 }
 
+__global__ __launch_bounds__(256) void k_clear(double* __restrict__ p, size_t n) {
+    for (size_t i = blockIdx.x * size_t(256) + threadIdx.x; i < n; i += gridDim.x * size_t(256)) p[i] = 0.0;
+}
+
 __global__ void k_chunk_counter(int* chunk, int reset) {
     if (reset) *chunk = 0;
     else *chunk += 1;
@@ -2051,6 +2055,11 @@ hipError_t launch_apply(const ApplyArgs& a, int n_ops, const Meta& hm, int n_tra
 
 hipError_t launch_chunk_counter(int* chunk, int reset, hipStream_t st) {
     hipLaunchKernelGGL(k_chunk_counter, dim3(1), dim3(1), 0, st, chunk, reset);
+    return hipGetLastError();
+}
+
+hipError_t launch_clear(double* p, size_t n, hipStream_t st) {
+    hipLaunchKernelGGL(k_clear, dim3((unsigned)std::min<size_t>((n + 255) / 256, 2048)), dim3(256), 0, st, p, n);
     return hipGetLastError();
 }
 

@@ -494,6 +494,8 @@ hipError_t launch_grad(const GradArgs& a, const Meta& host_meta, int n_traj, int
 // paths of one launch (all workgroups resident at once), 0: not one
 int chunk_paths(const ChunkTables& t, int form, int n_traj, bool adjoint = false);
 hipError_t chunk_set_smem_limit(int bytes);
+// n zeros to p, by a kernel: a caller's graph may hold it
+hipError_t launch_clear(double* p, size_t n, hipStream_t st);
 // gg: the large-basis form (no angular factors in LDS)
 int stage_smem_bytes(const Meta& m, int rows = kRowsPerBlock, bool gg = false);
 // the row tiles of one path for `rows` rows per workgroup, l' order

@@ -1712,7 +1712,7 @@ int wpccc_adjoint(wpccc_plan_t plan, const double* zgrid_host, int n_points, con
     WPCCC_HIP_CHECK(hipMemcpyAsync(lam, gX_dev, VB, hipMemcpyDeviceToDevice, st));
     double* shares = np > 0 ? plan->d_gshare : plan->d_gpart;
     const int n_part = np > 0 ? n_share : stage_chunks(plan->c.meta, plan->apply_rows);
-    WPCCC_HIP_CHECK(hipMemsetAsync(shares, 0, (size_t)plan->n_traj * kGradSlots * n_part * sizeof(double), st));
+    if ((rc = launched(launch_clear(shares, (size_t)plan->n_traj * kGradSlots * n_part, st), "k_clear"))) return rc;
     for (int s = n_ck - 1; s >= 0; --s) {
         const int n0 = s * K, n1 = std::min(n0 + K, n_steps);
         const void* x0 = n_ck > 1 ? (const void*)(plan->d_ckpt + (size_t)s * V) : X0_dev;
