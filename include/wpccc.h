@@ -300,13 +300,15 @@ int wpccc_plan_stage_launch(wpccc_plan_t plan, int* launch);
 
 /* The split on which a one-centre plan's wpccc_propagate runs the persistent
  * stage kernel: workgroups per path and paths per launch; 0 and 0 where it
- * runs one launch per stage (and for a two-centre plan).  Either pointer may
- * be NULL. */
+ * runs one launch per stage (and for a two-centre plan).  A call of a few
+ * steps runs one launch per stage where timing found that faster, with the
+ * same amplitudes.  Either pointer may be NULL. */
 int wpccc_plan_stage_split(wpccc_plan_t plan, int* workgroups, int* paths);
 
 /* Sets that split, for runs whose kernels must not follow from a timing: at
  * most `workgroups` per path (0: one launch per stage) and at most `paths`
- * paths per launch (0: as many as can be resident).  Synchronises `stream`.
+ * paths per launch (0: as many as can be resident), for calls of any length.
+ * Synchronises `stream`.
  * Errors: WPCCC_EINVAL, WPCCC_EHIP, WPCCC_ENOMEM (the plan then runs one
  * launch per stage), WPCCC_ENOTSUP (no such split fits, or the plan has no
  * persistent form: two-centre, large bases, WPCCC_MIXED with WPCCC_CACHE_ON or

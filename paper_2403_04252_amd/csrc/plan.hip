@@ -80,6 +80,7 @@ struct wpccc_plan_s {
     ChunkTables chunk;        // the split k_chunk runs (host copy without the index arrays)
     int chunk_np = 0;         // paths per k_chunk launch
     int spin = kChunkSpin;    // polls before a workgroup of it gives up
+    int chunk_min = 1;        // least steps for it; fewer go kernel by kernel
     char* d_ctab = nullptr;   // its index tables
     size_t ctab_off[8] = {}, ctab_cap = 0;
     unsigned long long* d_exch = nullptr;  // [n_traj][2][4][N] tagged words of k_chunk
@@ -701,11 +702,11 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
     const bool cache_ok = p->cache_req != WPCCC_CACHE_OFF;
     // a warm-up pass of one step, then the fastest of kTunePasses timed passes;
     // the prologue before each pass (untimed) advances k_chunk's epoch
-    auto time_it = [&](bool resident, float* ms) -> int {
+    auto time_it = [&](bool resident, float* ms, int steps = kTuneSteps) -> int {
         int r = WPCCC_OK;
         *ms = 1e30f;
         for (int pass = 0; pass <= kTunePasses && r == WPCCC_OK; ++pass) {
-            const int n = pass ? kTuneSteps : 1;
+            const int n = pass ? steps : 1;
             r = enqueue_prologue(p, pts, 2 * n + 1, 0, nj, st);
             if (r == WPCCC_OK && pass > 0 && hipEventRecord(ev.e0, st) != hipSuccess) r = WPCCC_EHIP;
             if (resident) {
@@ -795,6 +796,15 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
         bool ok = false;
         rc = set_chunk(p, chunk_G, &ok, st);
         p->resident = ok;
+        // A launch reads its tables and fills its LDS before the first step:
+        // with many paths, in several rounds of workgroups, k_stage has done a
+        // step or more meanwhile (N = 580, 256 paths, one step: 0.40 ms
+        // against 0.27).  From where on it is ahead follows from the times of
+        // one step and of kTuneSteps.
+        float one = 0.f;
+        if (rc == WPCCC_OK && ok && best_ms < 1e30f) rc = time_it(true, &one, 1);
+        const float more = (chunk_ms - one) / (kTuneSteps - 1), stage = best_ms / kTuneSteps;
+        for (p->chunk_min = 1; p->chunk_min < kTuneSteps && one + (p->chunk_min - 1) * more > p->chunk_min * stage;) ++p->chunk_min;
         // k_stage's rows (wpccc_step, graph replays, the adjoint): the fastest
         // of those timed, or the default ones where only k_chunk was
         if (p->mixed) {
@@ -1344,6 +1354,7 @@ int wpccc_plan_set_stage_split(wpccc_plan_t plan, int workgroups, int paths, voi
     }
     if (paths) plan->chunk_np = std::min(plan->chunk_np, paths);
     plan->resident = true;
+    plan->chunk_min = 1;
     if (plan->mixed) plan->fcache = false;
     return WPCCC_OK;
 }
@@ -1580,7 +1591,7 @@ int wpccc_propagate(wpccc_plan_t plan, const double* zgrid_host, int n_points, v
             if ((rc = enqueue_prologue(plan, pts, 2 * ns + 1, j0, nj, st))) return rc;
             double hs[kChunkSteps];
             for (int i = 0; i < ns; ++i) hs[i] = zgrid_host[c0 + i + 1] - zgrid_host[c0 + i];
-            if (resident) {
+            if (resident && ns >= plan->chunk_min) {
                 if ((rc = enqueue_chunk(plan, X, j0, nj, hs, ns, st))) return rc;
                 continue;
             }

@@ -212,3 +212,16 @@ def test_adjoint_without_memory_for_runs():
     torch.cuda.empty_cache()
     X, g = _adjoint(plan, zg)
     assert torch.equal(X, Xs) and (g - gs).abs().max() <= 1e-12 * gs.abs().max()
+
+
+def test_short_calls_bitwise():
+    """Calls of one to nine steps, which run one launch per stage where that is
+    faster (many paths), and the short end of a longer one: as the stage kernel."""
+    lb = _basis(6, 4, 20)
+    b = np.linspace(0.3, 6.0, 256)
+    zg = np.linspace(-3.0, 0.5, 68) ** 3 / 9.0
+    auto = W.wpccc_plan_create(lb, b, 1.5)
+    ref = W.wpccc_plan_create(lb, b, 1.5, stage_rows=4, stage_launch=W.WPCCC_LAUNCH_STAGES)
+    print(f"split {W.wpccc_plan_stage_split(auto)}", flush=True)
+    for steps in (1, 2, 3, 5, 9, 66):
+        assert np.array_equal(_run(auto, zg[:steps + 1]), _run(ref, zg[:steps + 1])), steps
