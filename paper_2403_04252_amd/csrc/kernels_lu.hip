@@ -423,7 +423,11 @@ __global__ __launch_bounds__(1024) void k_lu_check(LUStepArgs a) {
 // registers a tile ahead; the 16 columns stay in LDS (ONCHIP, up to kRhsRows
 // rows; beyond that in M), where one 16-byte read gives the real and imaginary
 // B operand.  In the diagonal block a lane holds one element (32 rows x two
-// columns per wave) and the solved row is broadcast by lane reads.
+// columns per wave) and the solved row is broadcast by lane reads.  The four
+// real products of a block are summed from zero, each by itself, and
+// subtracted from Y once: with the products added to Y one after another Y is
+// rounded twice per term (root mean square error of overlap-like systems of
+// n = 442: 2.5e-15 that way, 1.8e-15 rounded once per term, 0.83e-15 this way).
 //
 // The chain of 2 N such rows bounds small batches, the products large ones.
 // Column blocks of 32 staged in LDS and solved with vector FMAs, one launch
@@ -493,22 +497,21 @@ __global__ __launch_bounds__(kRhsThreads) void k_lu_rhs(RhsArgs a, int n_jobs) {
         for (; q < q1; q += kRhsThreads / 64) {
             double2 fn[8];
             load_tile(16 * min(q + kRhsThreads / 64, q1 - 1), kb0, fn);
-            dbl4 re, im;
+            double2 v[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const double2 v = get(16 * q + 4 * r + lk, li);
-                re[r] = v.x;
-                im[r] = v.y;
-            }
+            for (int r = 0; r < 4; ++r) v[r] = get(16 * q + 4 * r + lk, li);
+            const dbl4 zero = {0.0, 0.0, 0.0, 0.0};
+            dbl4 xx = zero, xy = zero, yy = zero, yx = zero;
 #pragma unroll
             for (int s = 0; s < 8; ++s) {
-                re = __builtin_amdgcn_mfma_f64_16x16x4f64(-f[s].x, y[s].x, re, 0, 0, 0);
-                im = __builtin_amdgcn_mfma_f64_16x16x4f64(-f[s].x, y[s].y, im, 0, 0, 0);
-                re = __builtin_amdgcn_mfma_f64_16x16x4f64(f[s].y, y[s].y, re, 0, 0, 0);
-                im = __builtin_amdgcn_mfma_f64_16x16x4f64(-f[s].y, y[s].x, im, 0, 0, 0);
+                xx = __builtin_amdgcn_mfma_f64_16x16x4f64(f[s].x, y[s].x, xx, 0, 0, 0);
+                xy = __builtin_amdgcn_mfma_f64_16x16x4f64(f[s].x, y[s].y, xy, 0, 0, 0);
+                yy = __builtin_amdgcn_mfma_f64_16x16x4f64(f[s].y, y[s].y, yy, 0, 0, 0);
+                yx = __builtin_amdgcn_mfma_f64_16x16x4f64(f[s].y, y[s].x, yx, 0, 0, 0);
             }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) put(16 * q + 4 * r + lk, li, make_double2(re[r], im[r]));
+            for (int r = 0; r < 4; ++r)
+                put(16 * q + 4 * r + lk, li, make_double2(v[r].x - (xx[r] - yy[r]), v[r].y - (xy[r] + yx[r])));
 #pragma unroll
             for (int s = 0; s < 8; ++s) f[s] = fn[s];
         }
