@@ -518,8 +518,8 @@ __device__ __forceinline__ void contract_tile(const ContractArgs& a, int y, int 
 // v_mfma_f64_4x4x4: four 4 x 4 products of four nodes each, the same rate as
 // the 16 x 16 form, whose four blocks here are four weights of one group of
 // four rows (nk = 4, 8, 12), or two weights of two row groups (nk = 2, 6).
-// Edge tiles are then padded to 8 rows and columns instead of 16, and each
-// wave holds nk * 4 QR * 4 CB sums of its QR row sets and CB column groups.
+// Edge tiles are then padded to 8 columns and 8 rows (16 with two row groups)
+// instead of 16, and each wave holds nk * 4 QR * 4 CB sums of its QR row sets and CB column groups.
 // The MFMA adds its four terms one after another, so a sum over nodes is the
 // same chain whatever the tile.
 //
@@ -596,10 +596,13 @@ struct Chunk64 {
     }
 };
 
-// PAIR: the blocks of an MFMA are two weights of two row groups.
+// PAIR: the blocks of an MFMA are two weights of two row groups, so a wave's
+// rows go in sixteens: a tile of three groups of eight is padded to 32 rows.
+// r8: the tile's row groups; its own rows alone are loaded and stored, those
+// past them belong to the next tile.
 template <int QW, bool PAIR, int QR, int CB>
-__device__ __forceinline__ void contract_tile64(const ContractArgs& a, int y, int piece, int s, int t, int a0, int b0, bool upper,
-                                Contract64Lds& L) {
+__device__ __forceinline__ void contract_tile64(const ContractArgs& a, int y, int piece, int s, int t, int a0, int b0, int r8,
+                                bool upper, Contract64Lds& L) {
     constexpr int NC = kNodeChunk, RP = Contract64Lds::kPitch, WP = Contract64Lds::kWPitch;
     constexpr int rs = PAIR ? 8 : 4, ws = PAIR ? 2 : 4;
     const Meta2C& m = *a.m;
@@ -610,6 +613,7 @@ __device__ __forceinline__ void contract_tile64(const ContractArgs& a, int y, in
     const int nk = st_nk(s, t, n_w);
     const int o1 = abs(s - t), o2 = s + t;
     const int nA = m.nA[s], nB = m.nB[t];
+    const int a_end = min(a0 + 8 * r8, nA), b_end = min(b0 + 8 * CB, nB);   // past the tile's rows and columns
     const size_t nn = m.n_nodes;
     const double* nd = a.nodes + (size_t)y * m.n_fields * nn;
     // this work item's node range [p_begin, nact) (whole chunks)
@@ -622,8 +626,8 @@ __device__ __forceinline__ void contract_tile64(const ContractArgs& a, int y, in
     // (rows past the tile repeat its last: nothing reads their sums); up to
     // one node field of the weights per thread
     const int lr = tid >> 3, kq = (tid & 7) * 4;
-    const double* arow = static_cast<const double*>(a.AT) + ((size_t)y * m.rowsT + m.rowT_off[s] + min(a0 + min(lr, 2 * QR * rs - 1), nA - 1)) * nn;
-    const double* brow = static_cast<const double*>(a.BT) + ((size_t)y * m.rowsP + m.rowP_off[t] + min(b0 + min(lr, 8 * CB - 1), nB - 1)) * nn;
+    const double* arow = static_cast<const double*>(a.AT) + ((size_t)y * m.rowsT + m.rowT_off[s] + min(a0 + lr, a_end - 1)) * nn;
+    const double* brow = static_cast<const double*>(a.BT) + ((size_t)y * m.rowsP + m.rowP_off[t] + min(b0 + lr, b_end - 1)) * nn;
     const bool vec = (nn & 1) == 0;   // 16-byte aligned rows
     const int ffi = tid / NC, fk = tid % NC;
     constexpr int kFStep = kStageThreads2C / NC;
@@ -749,7 +753,7 @@ __device__ __forceinline__ void contract_tile64(const ContractArgs& a, int y, in
 #pragma unroll
             for (int c = 0; c < CB; ++c) {
                 const int ii = a0 + r0 + r * rs + (PAIR ? 4 * (blk >> 1) : 0) + lk, jj = b0 + c0 + 4 * c + (lane & 3);
-                if (ii < nA && jj < nB) out[((size_t)ko * nA + ii) * nB + jj] = C.acc[q][r][c];
+                if (ii < a_end && jj < b_end) out[((size_t)ko * nA + ii) * nB + jj] = C.acc[q][r][c];
             }
     }
 }
@@ -791,10 +795,10 @@ __global__ __launch_bounds__(kStageThreads2C, 2) void k_2c_contract(ContractArgs
         // row sets and column groups of a wave
         const int r8 = ((tl.x >> 17) & 3) + 1, cb = ((tl.x >> 19) & 3) + 1;
 #define WPCCC_COLS(QW, PAIR, QR)                                                                       \
-    if (cb == 4) contract_tile64<QW, PAIR, QR, 4>(a, y, piece, s, t, a0, b0, upper, L);                \
-    else if (cb == 3) contract_tile64<QW, PAIR, QR, 3>(a, y, piece, s, t, a0, b0, upper, L);           \
-    else if (cb == 2) contract_tile64<QW, PAIR, QR, 2>(a, y, piece, s, t, a0, b0, upper, L);           \
-    else contract_tile64<QW, PAIR, QR, 1>(a, y, piece, s, t, a0, b0, upper, L);
+    if (cb == 4) contract_tile64<QW, PAIR, QR, 4>(a, y, piece, s, t, a0, b0, r8, upper, L);                \
+    else if (cb == 3) contract_tile64<QW, PAIR, QR, 3>(a, y, piece, s, t, a0, b0, r8, upper, L);           \
+    else if (cb == 2) contract_tile64<QW, PAIR, QR, 2>(a, y, piece, s, t, a0, b0, r8, upper, L);           \
+    else contract_tile64<QW, PAIR, QR, 1>(a, y, piece, s, t, a0, b0, r8, upper, L);
 #define WPCCC_PAIRS(QW)                                                                                \
     if (r8 > 2) { WPCCC_COLS(QW, true, 2) } else { WPCCC_COLS(QW, true, 1) }
 #define WPCCC_QUADS(QW)                                                                                \

@@ -49,3 +49,24 @@ def test_contraction_edges(tspec, pspec, ql, n_eta, n_tau, mixed):
         err = np.abs(g.cpu().numpy() - o).max() / np.abs(o).max()
         print(f"  {name} {err:.1e}", flush=True)
         assert err <= (1e-5 if mixed else 1e-11)
+
+
+@pytest.mark.parametrize("pspec", [(6, 3, 20), (5, 2, 9)])
+def test_contraction_tiles_of_three_row_groups(pspec):
+    """Blocks of 98 functions, split into tiles of 32, 24, 24 and 18 rows, with
+    two (above the diagonal of equal bases) and six weights: tiles of three
+    row groups, next to others of the same block.  Bar as above."""
+    tail, tspec = (4.0, 400, 40.0, 1.0), (6, 3, 20)
+    lt, ot = W.wpccc_basis(W.BasisSpec(*tspec, *tail)), build_basis(OSpec(*tspec, *tail))
+    lp, op = (lt, ot) if pspec == tspec else (W.wpccc_basis(W.BasisSpec(*pspec, *tail)), build_basis(OSpec(*pspec, *tail)))
+    plan = W.wpccc_plan_create_2c([lt], [lp], 0, [1.3], [1.2], q_lower=W.WPCCC_Q_PRIOR, n_eta=12, n_tau=16)
+    N, _ = W.wpccc_plan_path_info(plan, 0)
+    print(f"{tspec} {pspec}: N = {N}", flush=True)
+    H, S = (torch.empty((N, N), dtype=torch.complex128, device="cuda") for _ in range(2))
+    W.wpccc_couplings(plan, 0, -0.8, H, S)
+    W.wpccc_plan_status(plan)
+    So, Ho = two_centre_matrices(ot, op, 1.3, -0.8, 1.2, 12, 16, q_lower=Q_PRIOR)
+    for name, g, o in (("S", S, So), ("H", H, Ho)):
+        err = np.abs(g.cpu().numpy() - o).max() / np.abs(o).max()
+        print(f"  {name} {err:.1e}", flush=True)
+        assert err <= 1e-11
