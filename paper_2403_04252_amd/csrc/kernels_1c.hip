@@ -24,7 +24,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <mutex>
 #include <type_traits>
 
 #include "plan.h"
@@ -1661,14 +1660,8 @@ int stage_smem_bytes(const Meta& m, int rows, bool gg) {
 
 bool stage_rows_fit(const Meta& m, int rows) { return phase3_fits(rows, 2 * m.l_max + 1); }
 
-// The dynamic-LDS attribute is per kernel and process-wide: it is only ever
-// raised (to the largest size any plan has asked for), so that a plan created
-// later with a smaller basis does not lower it under an earlier plan's launches.
 hipError_t stage_set_smem_limit(int, int bytes) {
-    static std::mutex mu;
-    static int set_bytes = 0;
-    std::lock_guard<std::mutex> lk(mu);
-    if (bytes <= set_bytes) return hipSuccess;
+    static SmemLimit limit(0);
 #define WPCCC_FN_PAIR(R)                                                                        \
     (const void*)k_stage<R, false, false>, (const void*)k_stage<R, false, true>,                 \
         (const void*)k_stage<R, true, true>, (const void*)k_stage<R, true, false>,
@@ -1679,11 +1672,12 @@ hipError_t stage_set_smem_limit(int, int bytes) {
                          (const void*)k_apply<2, true>, (const void*)k_apply<1, true>};
 #undef WPCCC_FN_PAIR
 #undef WPCCC_FN_GG
-    hipError_t e = hipSuccess;
-    for (const void* f : fns)
-        if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess) set_bytes = bytes;
-    return e;
+    return limit.raise(bytes, [&]() {
+        hipError_t e = hipSuccess;
+        for (const void* f : fns)
+            if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        return e;
+    });
 }
 
 int stage_wgs_per_cu(int rows, int smem) {
@@ -2023,23 +2017,20 @@ hipError_t launch_chunk(const ChunkArgs& a, const ChunkTables& t, int form, hipS
     return e;
 }
 
-// The dynamic-LDS attribute of every k_chunk instance (raised only, as
-// stage_set_smem_limit).
+// The dynamic-LDS attribute of every k_chunk instance.
 hipError_t chunk_set_smem_limit(int bytes) {
-    static std::mutex mu;
-    static int set_bytes = 64 * 1024;
-    std::lock_guard<std::mutex> lk(mu);
-    if (bytes <= set_bytes) return hipSuccess;
-    hipError_t e = hipSuccess;
+    static SmemLimit limit(64 * 1024);
+    return limit.raise(bytes, [&]() {
+        hipError_t e = hipSuccess;
 #define WPCCC_CASE(F, T, P) \
     if (e == hipSuccess) \
         e = hipFuncSetAttribute((const void*)k_chunk<F, T, P, false>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); \
     if (e == hipSuccess && F == kRadialMoments) \
         e = hipFuncSetAttribute((const void*)k_chunk<F, T, P, F == kRadialMoments>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    WPCCC_CHUNK_FORMS(WPCCC_CASE)
+        WPCCC_CHUNK_FORMS(WPCCC_CASE)
 #undef WPCCC_CASE
-    if (e == hipSuccess) set_bytes = bytes;
-    return e;
+        return e;
+    });
 }
 
 hipError_t launch_grad(const GradArgs& a, const Meta& hm, int n_traj, int n_steps, int smem, int rows, hipStream_t st,

@@ -634,11 +634,14 @@ hipError_t launch_lu_update(const LUStepArgs& a, int n_jobs, hipStream_t st, con
 hipError_t launch_lu_rhs(const RhsArgs& a, int n_jobs, hipStream_t st, const LaunchEv& ev) {
     const int n = (a.N + kRhsC - 1) / kRhsC * n_jobs;
     const dim3 grid(8 * ((n + 7) / 8)), block(kRhsThreads);
-    const int rows = (a.N + kRhsB - 1) / kRhsB * kRhsB, diag = kRhsB * kRhsB * (int)sizeof(double2);
+    constexpr int diag = kRhsB * kRhsB * (int)sizeof(double2), most = diag + kRhsRows * kRhsC * (int)sizeof(double2);
+    const int rows = (a.N + kRhsB - 1) / kRhsB * kRhsB;
     if (rows <= kRhsRows) {
         const int smem = diag + rows * kRhsC * (int)sizeof(double2);
-        static const hipError_t e = hipFuncSetAttribute((const void*)k_lu_rhs<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 diag + kRhsRows * kRhsC * (int)sizeof(double2));
+        static SmemLimit limit(64 * 1024);
+        const hipError_t e = limit.raise(most, [] {
+            return hipFuncSetAttribute((const void*)k_lu_rhs<true>, hipFuncAttributeMaxDynamicSharedMemorySize, most);
+        });
         if (e != hipSuccess) return e;
         WPCCC_LAUNCH(ev, k_lu_rhs<true>, grid, block, smem, st, a, n_jobs);
     } else {

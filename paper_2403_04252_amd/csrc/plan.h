@@ -4,6 +4,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <mutex>
 #include <vector>
 
 #include "wpccc_impl.h"
@@ -19,6 +20,35 @@ constexpr int kStageThreads = 256;
 // workgroups per CU, so more waves each (N = 2958, 8 paths: 80 us per launch with
 // 256 threads, 59 with 512)
 constexpr int kStageThreadsGG = 512;
+constexpr int kMaxDevices = 64;      // devices with tables of their own in this library
+
+// The dynamic LDS that a set of kernels may request is an attribute of the
+// kernel on one device.  It is only ever raised there, so that a later plan
+// with a smaller basis does not lower it under an earlier one's launches.
+class SmemLimit {
+  public:
+    explicit SmemLimit(int initial) {
+        for (int& b : set_) b = initial;
+    }
+    // calls set() where the current device's limit is below `bytes`
+    template <class F>
+    hipError_t raise(int bytes, const F& set) {
+        int dev = 0;
+        hipError_t e = hipGetDevice(&dev);
+        if (e != hipSuccess) return e;
+        const bool known = dev >= 0 && dev < kMaxDevices;
+        std::lock_guard<std::mutex> lk(mu_);
+        if (known && bytes <= set_[dev]) return hipSuccess;
+        e = set();
+        if (e == hipSuccess && known) set_[dev] = bytes;
+        return e;
+    }
+
+  private:
+    std::mutex mu_;
+    int set_[kMaxDevices];
+};
+
 // dynamic LDS a stage workgroup may request: the CU's 160 KB less room for
 // the kernels' few static LDS words
 constexpr int kMaxDynLds = 160 * 1024 - 1024;

@@ -1452,7 +1452,6 @@ int couplings_1c(wpccc_plan_t plan, int j, double z, double* Frow, double* G, do
     return launched(e, "k_couplings_dense");
 }
 
-constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[kMaxDevices] = {};
 
