@@ -1385,11 +1385,14 @@ int lu_solve_batched(int n, int batch, const void* A, const void* B, void* X, hi
         return WPCCC_EINVAL;
     }
     const size_t NN = (size_t)n * n, bytes = NN * batch * sizeof(double2);
-    // the caller's arrays serve as they are; one buffer holds the factors (A
-    // is read only), the pivots, the permutations and the flags
+    // the caller's arrays serve as they are where the kernels can load them (16
+    // bytes at a time; complex128 needs no more than 8); one buffer holds the
+    // factors (A is read only), copies of B and X if need be, the pivots, the
+    // permutations and the flags
     const char *bc = static_cast<const char*>(B), *xc = static_cast<const char*>(X);
-    const bool overlap = bc < xc + bytes && xc < bc + bytes;   // B then needs a copy
-    const size_t ints = ((size_t)2 * n * batch + 4) * sizeof(int), n_buf = (size_t)(overlap ? 2 : 1) * bytes + ints;
+    const bool copy_x = ((uintptr_t)X & 15) != 0;
+    const bool copy_b = ((uintptr_t)B & 15) != 0 || (bc < xc + bytes && xc < bc + bytes);
+    const size_t ints = ((size_t)2 * n * batch + 4) * sizeof(int), n_buf = (size_t)(1 + copy_b + copy_x) * bytes + ints;
     char* buf = nullptr;
     int rc = WPCCC_OK;
     long long tot = 0;
@@ -1399,11 +1402,12 @@ int lu_solve_batched(int n, int batch, const void* A, const void* B, void* X, hi
         if ((r = dev_alloc(&buf, n_buf, tot))) return r;
         double2* lu = reinterpret_cast<double2*>(buf);
         double2* hb = lu + NN * batch;
+        double2* mb = hb + (copy_b ? NN * batch : 0);
         int* piv = reinterpret_cast<int*>(buf + n_buf - ints);
         int *perm = piv + (size_t)n * batch, *flag = perm + (size_t)n * batch;
         WPCCC_HIP_CHECK(hipMemsetAsync(flag, 0, 4 * sizeof(int), st));
         WPCCC_HIP_CHECK(hipMemcpyAsync(lu, A, bytes, hipMemcpyDeviceToDevice, st));
-        if (overlap) WPCCC_HIP_CHECK(hipMemcpyAsync(hb, B, bytes, hipMemcpyDeviceToDevice, st));
+        if (copy_b) WPCCC_HIP_CHECK(hipMemcpyAsync(hb, B, bytes, hipMemcpyDeviceToDevice, st));
         LUStepArgs a{};
         a.N = n;
         a.jobs.n_sub = 0;   // matrices one after another
@@ -1427,9 +1431,10 @@ int lu_solve_batched(int n, int batch, const void* A, const void* B, void* X, hi
         ra.jobs = a.jobs;
         ra.LU = lu;
         ra.perm = perm;
-        ra.H = overlap ? hb : static_cast<const double2*>(B);
-        ra.M = static_cast<double2*>(X);
+        ra.H = copy_b ? hb : static_cast<const double2*>(B);
+        ra.M = copy_x ? mb : static_cast<double2*>(X);
         if ((r = launched(launch_lu_rhs(ra, batch, st), "k_lu_rhs"))) return r;
+        if (copy_x) WPCCC_HIP_CHECK(hipMemcpyAsync(X, mb, bytes, hipMemcpyDeviceToDevice, st));
         WPCCC_HIP_CHECK(hipMemcpyAsync(hflag, flag, sizeof hflag, hipMemcpyDeviceToHost, st));
         WPCCC_HIP_CHECK(hipStreamSynchronize(st));
         return WPCCC_OK;

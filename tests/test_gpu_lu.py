@@ -103,3 +103,31 @@ def test_solve_error_of_one_rounding_per_term(n):
     ratio = np.sqrt(np.sum(got) / np.sum(model))
     print(f"n = {n}: error {np.sqrt(np.mean(got)):.2e}, {ratio:.2f} of one rounding per term", flush=True)
     assert ratio <= 1.05
+
+
+@pytest.mark.parametrize("n,batch", [(5, 3), (33, 2), (600, 1)])
+def test_solve_of_arrays_at_any_place(n, batch):
+    """Matrices that start 8 bytes past a multiple of 16, and X in the place of
+    B or across it: the bits of the solve of arrays of their own."""
+    rng = np.random.default_rng(n)
+    z = lambda: rng.standard_normal((batch, n, n)) + 1j * rng.standard_normal((batch, n, n))
+    A, B, size = z(), z(), 2 * batch * n * n
+    At, Bt = (torch.as_tensor(np.ascontiguousarray(m), device="cuda") for m in (A.transpose(0, 2, 1), B))
+    X = torch.empty_like(Bt)
+    W.wpccc_zgesv_batched(At, Bt, X)
+    ref = torch.view_as_real(X).flatten()
+    flat = lambda t: torch.view_as_real(t).flatten()
+    solve = W.load_library().wpccc_zgesv_batched
+    stream = torch.cuda.current_stream().cuda_stream
+    for a, b, x in ((1, 0, 0), (0, 1, 0), (0, 0, 1), (1, 1, 1)):
+        bufs = [torch.full((size + 1,), float("nan"), dtype=torch.float64, device="cuda") for _ in range(3)]
+        va, vb, vx = (t[o:o + size] for t, o in zip(bufs, (a, b, x)))
+        va.copy_(flat(At))
+        vb.copy_(flat(Bt))
+        assert solve(n, batch, va.data_ptr(), vb.data_ptr(), vx.data_ptr(), stream) == 0
+        assert torch.equal(vx, ref) and torch.equal(vb, flat(Bt)), (a, b, x)
+    for shift in (0, 1, 2, size // 2):
+        both = torch.empty(size + shift, dtype=torch.float64, device="cuda")
+        both[shift:].copy_(flat(Bt))
+        assert solve(n, batch, At.data_ptr(), both[shift:].data_ptr(), both.data_ptr(), stream) == 0
+        assert torch.equal(both[:size], ref), shift
