@@ -246,7 +246,7 @@ bool chunk_form(const wpccc_plan_s* p) {
 
 // The split of a path that k_chunk runs: at most G workgroups.  *ok: it fits
 // this basis and the device (nothing is changed otherwise).
-int set_chunk(wpccc_plan_s* p, int G, bool* ok, hipStream_t st) {
+int set_chunk(wpccc_plan_s* p, int G, bool* ok, hipStream_t st) try {
     ChunkTables t;
     *ok = false;
     if (!chunk_build(p->c.meta, G, 1024, t) && !chunk_build(p->c.meta, G, 512, t)) return WPCCC_OK;
@@ -294,6 +294,9 @@ int set_chunk(wpccc_plan_s* p, int G, bool* ok, hipStream_t st) {
     p->chunk_np = np;
     *ok = true;
     return WPCCC_OK;
+} catch (const std::bad_alloc&) {
+    set_error("out of host memory for the persistent stage kernel's tables");
+    return WPCCC_ENOMEM;
 }
 
 // Whether a call on `st` runs k_chunk.  Not into a caller's graph if its

@@ -225,3 +225,22 @@ def test_short_calls_bitwise():
     print(f"split {W.wpccc_plan_stage_split(auto)}", flush=True)
     for steps in (1, 2, 3, 5, 9, 66):
         assert np.array_equal(_run(auto, zg[:steps + 1]), _run(ref, zg[:steps + 1])), steps
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+def test_nonfinite_path_stays_alone(value):
+    """A non-finite amplitude of one path, on every split: that path ends
+    non-finite and is reported, the others are as without it, bitwise."""
+    zg = np.linspace(-2.0, 1.0, 20)
+    plan = W.wpccc_plan_create(_basis(5, 4, 4), [0.4, 1.5, 6.0], 1.5, stage_rows=4, stage_launch=W.WPCCC_LAUNCH_STAGES)
+    ref = _run(plan, zg)
+    for g, paths in _splits(plan):
+        X = torch.zeros((3, plan.n_pad), dtype=torch.complex128, device="cuda")
+        X[:, 0] = 1.0
+        X[1, 7] = value
+        W.wpccc_propagate(plan, zg, X)
+        with pytest.raises(W.WpcccError) as e:
+            W.wpccc_plan_status(plan)
+        assert e.value.code == -5, (g, paths)
+        X = X.cpu().numpy()
+        assert np.array_equal(X[[0, 2]], ref[[0, 2]]) and not np.isfinite(X[1]).all(), (g, paths)
