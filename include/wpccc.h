@@ -158,7 +158,9 @@ typedef struct {
                        either form, as timed. */
     int graph;      /* 1C, batched: replay each 64-step chunk of wpccc_propagate
                        from a captured HIP graph (step lengths and positions
-                       read from device memory); 2C: replay the steps of
+                       read from device memory), one launch per stage: where
+                       the persistent form is the faster one (stage_launch),
+                       a plan without this is faster too; 2C: replay the steps of
                        wpccc_propagate from captured graphs, every group's
                        launches in one graph: with batched = 1 and
                        WPCCC_SOLVE_FACTORED each graph step runs the stages

@@ -129,7 +129,7 @@ __global__ __launch_bounds__(256) void k_2c_nodes(NodeArgs a) {
 // of consecutive functions are consecutive doubles of phiT (coalesced).  The
 // gathers bound it, by their latency: with four nodes' stencils in flight and
 // two nodes at a time for tiles of up to 32 functions (131072 nodes, 16 jobs,
-// N = 60: 478 -> 332 us, of which the 1 GB written takes 210; N = 764 with
+// N = 60: 478 -> 330 us, of which the 1 GB written takes 210; N = 764 with
 // FP32 operands, three launches: 1.12 -> 0.89 ms each).  The interpolated f_a(r) of the 64 x 64 tile is formed once in
 // LDS and written, times the Legendre factor, to the rows of every block s
 // whose radial functions (l_a >= s) it holds, row by row with lanes over
@@ -1194,9 +1194,9 @@ __device__ inline double lane_read(double x, int lane) {
 // staged in LDS and solved by one wave, a row per lane, then all waves update
 // the rows below (above) it from the column-major factors.  The chain of rows
 // bounds it: solved rows go out by lane reads, and the reciprocals of the
-// diagonal are formed side by side before it (N = 60, 8 paths, kernel by
-// kernel: 54 -> 45 us with shuffles and a division per row before, 38.7 ->
-// 37.2 ms per pass; N = 764 beside the couplings 592 -> 494 us).
+// diagonal are formed side by side before it (with shuffles and a division per
+// row before; N = 60, 8 paths: alone 28 -> 19 us, in graph replays beside the
+// couplings 85 -> 46 us; N = 764 beside the couplings 592 -> 494 us).
 __global__ __launch_bounds__(kSolveThreads) void k_2c_solve(Stage2CArgs a) {
     extern __shared__ double2 ys[];      // [N]
     __shared__ double2 blk[kSolveBlock][kSolveBlock + 1];

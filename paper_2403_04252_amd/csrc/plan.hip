@@ -1678,7 +1678,7 @@ int wpccc_adjoint(wpccc_plan_t plan, const double* zgrid_host, int n_points, con
     // Where wpccc_propagate runs k_chunk, so do both sweeps: only the chain of
     // adjoint inputs is sequential, the gradient shares of a run of up to 64
     // steps follow it in one launch (16 paths, N = 86, 800 steps: 49.7 ms with
-    // four launches per step and sweep, 23.7 this way).
+    // four launches per step and sweep, 23.5 this way).
     int np = plan->form == kRadialMoments && runs_chunk(plan, st) ? chunk_paths(plan->chunk, plan->form, plan->n_traj, true) : 0;
     if (np > 0 && (rc = adjoint_runs(plan, std::min(K, kChunkSteps), std::min(n_steps, kChunkSteps), st, &np))) return rc;
     const int n_share = 4 * plan->adj_share * stage_chunks(plan->c.meta, plan->apply_rows);
