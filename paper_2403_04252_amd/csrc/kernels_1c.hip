@@ -254,7 +254,7 @@ __global__ __launch_bounds__(64) void k_prologue(PrologueArgs a) {
     const Meta& m = *a.meta;
     const int j = a.traj0 + blockIdx.y;
     const int p = blockIdx.x;
-    if (p == 0 && blockIdx.y == 0 && threadIdx.x == 0) *a.epoch += kChunkEpoch;
+    if (a.epoch && p == 0 && blockIdx.y == 0 && threadIdx.x == 0) *a.epoch += kChunkEpoch;
     const double z = a.zdev ? a.zdev[(size_t)(*a.chunk) * kChunkPoints + p] : a.z[p];
     const double b = a.tb.bvec[j], v = a.tb.vvec[j];
     const double R = sqrt(b * b + z * z);
@@ -1206,6 +1206,8 @@ __global__ __launch_bounds__(NT) void k_chunk(ChunkArgs c) {
     const size_t j0 = (size_t)j * a.pt.n_pts;
     const double sc = a.Zp / T.vvec[j];
     const unsigned tag0 = (unsigned)*c.epoch;
+    int spin = c.spin;
+    asm volatile("" : "+s"(spin));   // stays in its register: no reload on the way to a poll
     unsigned long long* exch = c.exch + (size_t)j * 8 * N;   // [2][4][N]
 
     // What the next new point needs, in registers before its use: a stage
@@ -1307,7 +1309,7 @@ __global__ __launch_bounds__(NT) void k_chunk(ChunkArgs c) {
 #pragma unroll
                 for (int i = 0; i < FP; ++i) asm volatile("" : "+v"(entx[i]));
             if (!local && !(step == 0 && stage == 1) &&
-                !chunk_take<NT>(exch + (size_t)((tag - 1) & 1) * 4 * N, N, tag - 1, sx, c.xpos, xs, alive ? c.spin : 1, tid)) {
+                !chunk_take<NT>(exch + (size_t)((tag - 1) & 1) * 4 * N, N, tag - 1, sx, c.xpos, xs, alive ? spin : 1, tid)) {
                 alive = false;
                 gave_up = 1;
             }

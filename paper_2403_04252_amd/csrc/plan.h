@@ -239,7 +239,8 @@ constexpr int kChunkGroups = 2;   // groups of a wave's chain run side by side
 constexpr int kChunkSpin = 1 << 24;
 constexpr int kTuneSpin = 1 << 18;
 // the tags of a chunk's stages: the prologue that precedes every k_chunk
-// launch advances the plan's epoch by this much
+// launch, and no other, advances the plan's epoch by this much, so that words
+// left from a path's last chunk are never an epoch's wrap away
 constexpr int kChunkEpoch = 4 * kChunkSteps + 4;
 
 // One workgroup of a path: where its index tables start, their lengths, and
@@ -335,7 +336,7 @@ struct PrologueArgs {
     // graph replays: z = zdev[*chunk * kChunkPoints + p] instead of z[p]
     const double* zdev;
     const int* chunk;
-    int* epoch;              // advanced by kChunkEpoch
+    int* epoch;              // advanced by kChunkEpoch (NULL: no k_chunk follows)
 };
 
 // Device tables of one centre's basis (moment tables, column maps, angular

@@ -143,7 +143,7 @@ void free_plan(wpccc_plan_s* p) {
 }
 
 // Per-point quantities for z[0..n) of paths [j0, j0+nj) into point slots 0..n-1.
-int enqueue_prologue(wpccc_plan_s* p, const double* z, int n, int j0, int nj, hipStream_t st) {
+int enqueue_prologue(wpccc_plan_s* p, const double* z, int n, int j0, int nj, hipStream_t st, bool for_chunk = false) {
     PrologueArgs a;
     a.meta = p->c.d_meta;
     a.tb = p->tables();
@@ -153,7 +153,7 @@ int enqueue_prologue(wpccc_plan_s* p, const double* z, int n, int j0, int nj, hi
     a.traj0 = j0;
     a.zdev = p->capturing ? p->d_zall : nullptr;
     a.chunk = p->capturing ? p->d_chunk : nullptr;
-    a.epoch = p->d_epoch;
+    a.epoch = for_chunk ? p->d_epoch : nullptr;
     hipError_t e = launch_prologue(a, nj, st, p->timer.open(kPrologue));
     return launched(e, "k_prologue");
 }
@@ -549,7 +549,7 @@ int adjoint_steps(wpccc_plan_s* p, double2* X, const double* zg, int na, int nb,
             pts[2 * i + 1] = 0.5 * (zg[m] + zg[m + 1]);
             hs[i] = zg[m + 1] - zg[m];
         }
-        int rc = enqueue_prologue(p, pts, 2 * ns + 1, 0, p->n_traj, st);
+        int rc = enqueue_prologue(p, pts, 2 * ns + 1, 0, p->n_traj, st, true);
         if (rc) return rc;
         ChunkArgs r = c;
         double2* x = X;
@@ -710,7 +710,7 @@ int tune_stage(wpccc_plan_s* p, const int* cand, int n_cand, int launch_req, hip
         *ms = 1e30f;
         for (int pass = 0; pass <= kTunePasses && r == WPCCC_OK; ++pass) {
             const int n = pass ? steps : 1;
-            r = enqueue_prologue(p, pts, 2 * n + 1, 0, nj, st);
+            r = enqueue_prologue(p, pts, 2 * n + 1, 0, nj, st, resident);
             if (r == WPCCC_OK && pass > 0 && hipEventRecord(ev.e0, st) != hipSuccess) r = WPCCC_EHIP;
             if (resident) {
                 if (r == WPCCC_OK) r = enqueue_chunk(p, X, 0, nj, hs, n, st);
@@ -1590,10 +1590,11 @@ int wpccc_propagate(wpccc_plan_t plan, const double* zgrid_host, int n_points, v
                 pts[2 * i] = zgrid_host[c0 + i];
                 if (i < ns) pts[2 * i + 1] = 0.5 * (zgrid_host[c0 + i] + zgrid_host[c0 + i + 1]);
             }
-            if ((rc = enqueue_prologue(plan, pts, 2 * ns + 1, j0, nj, st))) return rc;
+            const bool by_chunk = resident && ns >= plan->chunk_min;
+            if ((rc = enqueue_prologue(plan, pts, 2 * ns + 1, j0, nj, st, by_chunk))) return rc;
             double hs[kChunkSteps];
             for (int i = 0; i < ns; ++i) hs[i] = zgrid_host[c0 + i + 1] - zgrid_host[c0 + i];
-            if (resident && ns >= plan->chunk_min) {
+            if (by_chunk) {
                 if ((rc = enqueue_chunk(plan, X, j0, nj, hs, ns, st))) return rc;
                 continue;
             }

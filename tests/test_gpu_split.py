@@ -244,3 +244,28 @@ def test_nonfinite_path_stays_alone(value):
         assert e.value.code == -5, (g, paths)
         X = X.cpu().numpy()
         assert np.array_equal(X[[0, 2]], ref[[0, 2]]) and not np.isfinite(X[1]).all(), (g, paths)
+
+
+def test_chunks_among_other_calls():
+    """Propagations by the persistent kernel with single steps, short calls and
+    an adjoint between them (calls that do not advance its tags): bitwise the
+    stage kernel's amplitudes throughout."""
+    lb, b = _basis(6, 4, 20), np.array([0.5, 1.5, 3.0, 5.0])
+    zg = np.arange(140) / 16.0 - 4.0
+    out = []
+    for split in (0, 8):
+        plan = W.wpccc_plan_create(lb, b, 1.5, model_a=0.5, model_c=1.2, stage_rows=8, stage_launch=W.WPCCC_LAUNCH_STAGES)
+        W.wpccc_plan_set_stage_split(plan, split)
+        X = torch.zeros((4, plan.n_pad), dtype=torch.complex128, device="cuda")
+        X[:, 0] = 1.0
+        seen = []
+        for lo, hi in ((0, 1), (1, 67), (67, 68), (68, 139)):
+            W.wpccc_propagate(plan, zg[lo:hi + 1], X)
+            seen.append(X.clone())
+            for _ in range(3):
+                W.wpccc_step(plan, X, zg[hi], 0.0625)
+            seen.append(X.clone())
+            seen.append(_adjoint(plan, zg[lo:hi + 1])[0])
+        W.wpccc_plan_status(plan)
+        out.append([t.cpu().numpy() for t in seen])
+    assert all(np.array_equal(x, y) for x, y in zip(*out))
