@@ -932,9 +932,9 @@ __global__ __launch_bounds__(256) void k_fpoint(const Meta* __restrict__ mp_, Ta
 // bytes of it cost 4 us a step at N = 580).  Which G is best
 // depends on basis and batch and is timed at plan creation.  Measured per
 // pass on the propagation cases, one launch per stage -> this kernel:
-// N = 86, 1 path, 800 steps: 12.8 -> 7.5 ms (G = 1); N = 580, 32 paths, 800:
-// 35.5 -> 19.5 ms (G = 8); N = 580, 64 paths, 400, FP32 table: 28.9 ->
-// 18.1 ms; N = 1855, 8 paths, 100, interpolated: 15.1 -> 9.3 ms (G = 48).
+// N = 86, 1 path, 800 steps: 12.8 -> 7.4 ms (G = 1); N = 580, 32 paths, 800:
+// 35.5 -> 19.6 ms (G = 8); N = 580, 64 paths, 400, FP32 table: 28.9 ->
+// 18.1 ms; N = 1855, 8 paths, 100, interpolated: 15.1 -> 9.2 ms (G = 48).
 //
 // Both sums of a stage run on v_mfma_f64_4x4x4 (four 4 x 4 products of four
 // terms each, at the FP64 MFMA peak, with a granularity that fits 2l+1 and
